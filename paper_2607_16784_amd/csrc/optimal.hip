@@ -11,28 +11,42 @@
 // the smallest total drop of the models in mask m on k GPUs (each partition
 // of m is counted once: the block holding m's lowest model is split off
 // last).  The optimum is min over k <= min(G, n) of f_k[all] / n.
+//  * Layers are dense: an entry's place is its mask's rank among the kept
+//    masks of its popcount (colexicographic over the positions
+//    e = n - 1 - model, so that the kept masks are the first C(n - j, p)
+//    ranks whatever j).  Indexed by the mask itself the few kept entries lay
+//    spread over 2^n, and every read was a page of its own: 24 models on 8
+//    GPUs of 3 took 0.61 ms that way.
 //  * cost_kernel: one lane per candidate set S (|S| <= C, by combinatorial
-//    rank), its members' drops in the aggregation's order and arithmetic.
-//  * layer_kernel: one launch per k over the masks that can hold k
-//    non-empty GPUs and leave a remainder the other GPUs can take -- the
-//    masks of each admissible popcount, enumerated densely: a lane unranks
-//    its first mask (masks of equal popcount in increasing order) and steps
-//    to the next ones with Gosper's rule, so no lane idles on a mask outside
-//    the layer.  A lane reads f_{k-1} only inside that layer's range, so no
-//    layer needs initialising.  The 2^n-entry layers stay in HBM (1.5 GiB
-//    with the recorded choices at n = 24, G = 8).
-//    Each evaluated mask also records its chosen set (the first in the
-//    enumeration order that attains the minimum).
-//  * finish_kernel: the minimum over k and a backtrack through the recorded
-//    sets to one optimal placement (GPUs numbered in order of their first
-//    model).
+//    rank), its members' drops in the aggregation's order and arithmetic;
+//    the costs are also layer 1.
+//  * layer_kernel: one launch per k = 2 .. G - 1 over the masks that can
+//    hold k non-empty GPUs and leave a remainder the other GPUs can take.  A
+//    group of lanes unranks its mask, and on the way tabulates per member
+//    what it adds to the rank of a remainder and to the rank of a candidate
+//    set in each role it can have (Members); a candidate's two addresses are
+//    then sums of one table entry per member.  The group's lanes share the
+//    candidates, and each mask records its chosen set (the first by size,
+//    then by members, that attains the minimum).
+//    A layer is a few million such reads out of the L2s: its chain of
+//    launch, unranking and a few read batches bounds it, so a mask gets as
+//    many lanes as keep the chip's lanes busy.
+//  * finish_kernel: layer G's one mask (`all`), the minimum over k and a
+//    backtrack through the recorded sets to one optimal placement (GPUs
+//    numbered in order of their first model), in one wave.
 #include <cmath>
 
 #include "rm_common.h"
 
 namespace rm {
 
-constexpr int kOptBlock = 256;
+constexpr int kOptBlock = 256, kCostBlock = 64;
+// Lanes a layer launch aims at: two waves on every SIMD of the 256 CUs.
+// Every lane of a mask unranks it, so more lanes add more work than they
+// share: 24 models on 8 GPUs of 3 take 0.118 ms so, 0.16 ms with half as
+// many, 0.131 ms with twice and 0.147 ms with four times as many (1.18 ms
+// with every mask of a layer's popcounts, one lane each).
+constexpr int64_t kLayerLanes = 256 * 4 * 2 * 64;
 
 // Binomial coefficient C(x, y) for 0 <= y <= 4, 0 <= x <= 31 (closed forms
 // with constant divisors; the products fit 32 bits).
@@ -64,10 +78,69 @@ __host__ __device__ inline int32_t n_sets_upto(int32_t n, int32_t C)
 
 // Masks on k GPUs that can still be completed: k <= popcount <= C k and
 // the n - popcount models left fit the G - k other GPUs.
-__device__ inline bool layer_holds(int32_t k, int32_t p, int32_t n, int32_t C, int32_t G)
+__host__ __device__ inline bool layer_holds(int32_t k, int32_t p, int32_t n, int32_t C, int32_t G)
 {
     if (k == 0) return p == 0;
     return p >= k && p <= C * k && n - p <= C * (G - k);
+}
+
+// Sets split off before a mask of popcount p is left, at least: each holds
+// the lowest model still there, so the mask lies above that many models.
+__host__ __device__ inline int32_t sets_before(int32_t n, int32_t C, int32_t p)
+{
+    return (n - p + C - 1) / C;
+}
+
+// Binomial coefficients C(x, y), x <= 24, y <= 24, with three zero columns
+// before y = 0 (y = -3 .. -1), and the colexicographic lists of pairs
+// a < b and triples a < b < c of 0 .. 22, five bits a member from the low
+// end.
+constexpr int kOptN = RM_MAX_OPT_MODELS;
+constexpr int kBinomRow = kOptN + 4;
+constexpr int kPairs = (kOptN - 1) * (kOptN - 2) / 2;
+constexpr int kTriples = (kOptN - 1) * (kOptN - 2) * (kOptN - 3) / 6;
+
+struct OptTables {
+    int32_t binom[(kOptN + 1) * kBinomRow];
+    uint16_t pair[kPairs], triple[kTriples];
+};
+
+constexpr OptTables make_tables()
+{
+    OptTables t = {};
+    for (int x = 0; x <= kOptN; ++x)
+        for (int y = 0; y <= x; ++y)
+            t.binom[x * kBinomRow + y + 3] =
+                (y == 0 || y == x) ? 1
+                                   : t.binom[(x - 1) * kBinomRow + y + 2] +
+                                         t.binom[(x - 1) * kBinomRow + y + 3];
+    int np = 0, nt = 0;
+    for (int c = 0; c < kOptN - 1; ++c)
+        for (int b = 0; b < c; ++b) {
+            t.pair[np++] = (uint16_t)(b | (c << 5));
+            for (int a = 0; a < b; ++a) t.triple[nt++] = (uint16_t)(a | (b << 5) | (c << 10));
+        }
+    return t;
+}
+
+__device__ const OptTables d_tables = make_tables();
+static constexpr OptTables h_tables = make_tables();
+
+// Entries of layer k below those of popcount p.
+struct LayerPlan {
+    int32_t start[kOptN + 2];   // start[p]; start[n + 1] = entries in all
+};
+
+static LayerPlan layer_plan(int32_t k, int32_t n, int32_t C, int32_t G)
+{
+    LayerPlan plan;
+    int32_t at = 0;
+    for (int32_t p = 0; p < kOptN + 2; ++p) {
+        plan.start[p] = at;
+        if (p <= n && layer_holds(k, p, n, C, G))
+            at += h_tables.binom[(n - sets_before(n, C, p)) * kBinomRow + p + 3];
+    }
+    return plan;
 }
 
 struct OptArgs {
@@ -96,17 +169,24 @@ __device__ inline double drop_of_set(double T_agg, double T_iso, int32_t drop_mo
 // c(S) for every candidate set: its members' drops summed in ascending
 // position, each from T~_p = T_p + sum over the other members r (ascending)
 // of gamma_pr * Delta_pr -- the aggregation's expressions in its order.
-__global__ __launch_bounds__(kOptBlock) void cost_kernel(OptArgs a, int32_t n_sets)
+// Layer 1 holds the cost of the whole mask on one GPU, for the masks it
+// keeps.
+__global__ __launch_bounds__(kCostBlock) void cost_kernel(OptArgs a, int32_t n_sets,
+                                                          LayerPlan first)
 {
-    const int32_t x = (int32_t)(blockIdx.x * kOptBlock + threadIdx.x);
+    const int32_t x = (int32_t)(blockIdx.x * kCostBlock + threadIdx.x);
     if (x >= n_sets) return;
     int32_t s = 1;
     while (s < a.C && x >= size_base(a.n, s + 1)) ++s;
     int32_t r = x - size_base(a.n, s);
-    int32_t c[4];
-    // unrank: largest c_i with C(c_i, i + 1) <= r, from the top element down
+    // unrank: largest c_i with C(c_i, i + 1) <= r, from the top element down.
+    // Every loop below runs over all four members and skips those past s, so
+    // that the members stay in registers and their reads go out together.
+    int32_t c[4] = {0, 0, 0, 0};
     int32_t hi = a.n;
-    for (int32_t i = s - 1; i >= 0; --i) {
+#pragma unroll
+    for (int32_t i = 3; i >= 0; --i) {
+        if (i >= s) continue;
         int32_t v = hi - 1;
         while (binom_small(v, i + 1) > r) --v;
         c[i] = v;
@@ -115,229 +195,357 @@ __global__ __launch_bounds__(kOptBlock) void cost_kernel(OptArgs a, int32_t n_se
     }
     const int64_t N = a.N;
     bool ok = true;
-    int32_t m[4];
-    for (int32_t i = 0; i < s; ++i) {
-        m[i] = a.models[c[i]];
-        ok = ok && m[i] >= 0 && m[i] < a.N;
+    int32_t m[4], q[4];
+    double T[4], dl[4][4];
+#pragma unroll
+    for (int32_t i = 0; i < 4; ++i) m[i] = a.models[c[i]];
+#pragma unroll
+    for (int32_t i = 0; i < 4; ++i) {
+        ok = ok && (i >= s || (m[i] >= 0 && m[i] < a.N));
+        if (!(m[i] >= 0 && m[i] < a.N)) m[i] = 0;
+    }
+#pragma unroll
+    for (int32_t i = 0; i < 4; ++i) {
+        T[i] = a.iso[m[i]];
+        q[i] = a.q[m[i]];
+#pragma unroll
+        for (int32_t t = 0; t < 4; ++t)
+            dl[i][t] = (i < s && t < s && t != i) ? a.delay[m[i] * N + m[t]] : 0.0;
     }
     double sum = 0.0;
     bool bad_delay = false;
-    if (ok) {
-        for (int32_t p = 0; p < s; ++p) {
-            const double Tp = a.iso[m[p]];
-            double T_agg = Tp;
-            for (int32_t t = 0; t < s; ++t) {
-                if (t == p) continue;
-                const double g = overlap_scale(a.q[m[p]], a.q[m[t]]);
-                const double dl = a.delay[m[p] * N + m[t]];
-                bad_delay = bad_delay || !(dl >= 0.0 && dl <= 1.7976931348623157e308);
-                T_agg = T_agg + g * dl;
-            }
-            sum = sum + drop_of_set(T_agg, Tp, a.drop_mode);
+#pragma unroll
+    for (int32_t p = 0; p < 4; ++p) {
+        if (p >= s) continue;
+        double T_agg = T[p];
+#pragma unroll
+        for (int32_t t = 0; t < 4; ++t) {
+            if (t == p || t >= s) continue;
+            bad_delay = bad_delay || !(dl[p][t] >= 0.0 && dl[p][t] <= 1.7976931348623157e308);
+            T_agg = T_agg + overlap_scale(q[p], q[t]) * dl[p][t];
         }
-    } else {
+        sum = sum + drop_of_set(T_agg, T[p], a.drop_mode);
+    }
+    if (!ok) {
         sum = __builtin_nan("");
+        bad_delay = false;
     }
     if (bad_delay && a.status) atomicOr(a.status, RM_ST_BAD_DELAY);
     a.cost[x] = sum;
+    if (!layer_holds(1, s, a.n, a.C, a.G) || c[0] < sets_before(a.n, a.C, s)) return;
+    // rank over the positions n - 1 - c, the highest model first
+    int32_t at = first.start[s];
+    uint32_t mask = 0;
+#pragma unroll
+    for (int32_t i = 0; i < 4; ++i) {
+        if (i >= s) continue;
+        at += binom_small(a.n - 1 - c[i], s - i);
+        mask |= 1u << c[i];
+    }
+    // no placement through a cost that is not finite
+    const bool finite = sum < __builtin_inf();
+    a.layers[at] = finite ? sum : __builtin_inf();
+    a.choice[at] = finite ? mask & (mask - 1) : 0u;
 }
 
-// Value of splitting S = {u} + t off mask m on layer k, f_{k-1}[m \ S] + c(S)
-// (`rank`: S's index in the cost table), +inf when m \ S is outside layer
-// k - 1 or the slot is unused.  The loads are unconditional (clamped to
-// entry 0) so that a batch of candidates has all its loads in flight.
-__device__ inline double candidate(const OptArgs& a, int32_t k, uint32_t m, int32_t u, uint32_t t,
-                                   int32_t rank, bool use)
+// What a member of a mask adds, by its ordinal o (position order: the
+// highest model has ordinal 0, the lowest, u, ordinal p - 1) and its role in
+// a candidate set.  With T_j[o] the sum of C(e_i, i + 1 - j) over the
+// ordinals i in [o, p - 1) -- the members from o up, j of those above them
+// taken away -- the remainder's rank is
+//   R                                  without u alone (R: rank of the mask
+//                                      minus u's own term),
+//   r01[l], r01[l] + r12[h], r01[l] + r12[m] + r23[h]
+//                                      without u and one, two, three others
+//                                      (l < m < h the ordinals),
+// with r01[o] = R - T_0[o] + T_1[o + 1], r12[o] = T_2[o + 1] - T_1[o],
+// r23[o] = T_3[o + 1] - T_2[o]; the candidate's cost rank is its size's base
+// plus u plus C(c, 2), C(c, 3), C(c, 4) of the others from the lowest model
+// (highest ordinal) up.
+// Tables that only larger capacities read are left out (C: the capacity).
+template <int C>
+struct Members {
+    int32_t r01[kOptN], c2[kOptN];
+    int32_t r12[C >= 3 ? kOptN : 1], c3[C >= 3 ? kOptN : 1];
+    int32_t r23[C >= 4 ? kOptN : 1], c4[C >= 4 ? kOptN : 1];
+};
+
+// The binomials and the list of member pairs or triples that capacity C
+// reads, in LDS.
+template <int C>
+struct LdsTables {
+    int32_t binom[(kOptN + 1) * kBinomRow];
+    uint16_t pair[C >= 3 ? kPairs : 1], triple[C >= 4 ? kTriples : 1];
+};
+
+template <int C>
+__device__ inline void stage_tables(LdsTables<C>& tab)
 {
-    const uint32_t rest = m ^ ((1u << u) | t);
-    const bool ok = use && layer_holds(k - 1, __builtin_popcount(rest), a.n, a.C, a.G);
-    const double c = a.cost[ok ? rank : 0];
-    const double f = k == 1 ? 0.0 : a.layers[(int64_t)(k - 2) * ((int64_t)1 << a.n) + (ok ? rest : 0u)];
-    return ok ? f + c : __builtin_inf();
+    for (int32_t x = threadIdx.x; x < (kOptN + 1) * kBinomRow; x += blockDim.x)
+        tab.binom[x] = d_tables.binom[x];
+    if (C >= 3)
+        for (int32_t x = threadIdx.x; x < kPairs; x += blockDim.x) tab.pair[x] = d_tables.pair[x];
+    if (C >= 4)
+        for (int32_t x = threadIdx.x; x < kTriples; x += blockDim.x)
+            tab.triple[x] = d_tables.triple[x];
 }
 
-constexpr int kBatch = 8;   // candidate sets evaluated together
+// The best candidate so far: its value, its place in the enumeration (size,
+// then the others' offsets p - 2 - ordinal, five bits each, the lowest model
+// first), which also names the set.
+struct BestSet {
+    double v;
+    uint32_t order;
+};
 
-// The candidates S = {u} + {b1, b2, b3 below} + one more member taken from
-// the set bits of x (the innermost loop of the enumeration), kBatch at a
-// time: their loads are issued before any of their values is used, and the
-// minimum keeps the first candidate in enumeration order on ties.
-__device__ inline void consider_bits(const OptArgs& a, int32_t k, uint32_t m, int32_t u,
-                                     uint32_t t_fixed, int32_t rank_fixed, int32_t size, uint32_t x,
-                                     double& best, uint32_t& tb)
+__device__ inline void keep_first_min(BestSet& b, double v, uint32_t order)
 {
-    while (x) {
-        uint32_t tt[kBatch];
-        int32_t rk[kBatch];
-        bool use[kBatch];
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
-            use[i] = x != 0;
-            const int32_t b = use[i] ? __builtin_ctz(x) : 0;
-            tt[i] = t_fixed | (use[i] ? 1u << b : 0u);
-            rk[i] = rank_fixed + binom_small(b, size);
-            x &= x - 1;
-        }
-        double v[kBatch];
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i) v[i] = candidate(a, k, m, u, tt[i], rk[i], use[i]);
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i)
-            if (v[i] < best) {
-                best = v[i];
-                tb = tt[i];
-            }
+    if (v < b.v || (v == b.v && order < b.order)) {
+        b.v = v;
+        b.order = order;
     }
 }
 
-// Enumerate the sets S = {lowest(m)} + t, t a subset of the other models of m
-// with |t| <= C - 1, in a fixed order (by size, then by members), with S's
-// rank sum of C(c_i, i + 1) over its sorted members c_0 < c_1 < ... built up
-// member by member.  Returns the smallest value; *chosen = the first t that
-// attains it.
-__device__ inline double best_split(const OptArgs& a, int32_t k, uint32_t m, uint32_t* chosen)
+constexpr int kBatch = 4;   // candidates of a lane with their reads in flight together
+
+// Unranks mask number r of popcount p on `bits` positions into the member
+// tables (every lane of the group writes the same values) and finds the
+// best split of the mask on layer k > 1, shared by the group's L lanes (lane
+// t): f_{k-1}[m \ S] + c(S) over the sets S = {u} + others, |S| <= C, by
+// size and then by members.  Returns the smallest value and the first set
+// that attains it; `mask` the mask over the models.
+template <int C>
+__device__ inline BestSet best_split(const OptArgs& a, int32_t k, const LdsTables<C>& tab,
+                                     const LayerPlan& prev, Members<C>& mb, int32_t bits,
+                                     int32_t p, int32_t r, int32_t t, int32_t L, uint32_t& mask)
 {
-    const int32_t u = __builtin_ctz(m);
-    const uint32_t others = m & (m - 1);
-    const int32_t base2 = a.n, base3 = base2 + binom_small(a.n, 2),
-                  base4 = base3 + binom_small(a.n, 3);
-    double best = __builtin_inf();
-    uint32_t tb = 0;
-    {
-        const double v = candidate(a, k, m, u, 0u, u, true);
-        if (v < best) best = v;
-    }
-    if (a.C >= 2) consider_bits(a, k, m, u, 0u, base2 + u, 2, others, best, tb);
-    if (a.C >= 3)
-        for (uint32_t x1 = others; x1; x1 &= x1 - 1) {
-            const int32_t i1 = __builtin_ctz(x1);
-            consider_bits(a, k, m, u, 1u << i1, base3 + u + binom_small(i1, 2), 3, x1 & (x1 - 1),
-                          best, tb);
-        }
-    if (a.C >= 4)
-        for (uint32_t x1 = others; x1; x1 &= x1 - 1) {
-            const int32_t i1 = __builtin_ctz(x1);
-            const int32_t r1 = u + binom_small(i1, 2);
-            for (uint32_t x2 = x1 & (x1 - 1); x2; x2 &= x2 - 1) {
-                const int32_t i2 = __builtin_ctz(x2);
-                consider_bits(a, k, m, u, (1u << i1) | (1u << i2),
-                              base4 + r1 + binom_small(i2, 3), 4, x2 & (x2 - 1), best, tb);
+    const int32_t* binom = tab.binom;
+    mask = 0;
+    int32_t i = p, u = 0, R = 0;
+    int32_t t0 = 0, t1 = 0, t2 = 0, t3 = 0;
+    for (int32_t e = bits - 1; e >= 0 && i > 0; --e) {
+        const int32_t* row = binom + e * kBinomRow + 3 + i;   // row[0] = C(e, i)
+        const int32_t b0 = row[0], b1 = row[-1], b2 = C >= 3 ? row[-2] : 0,
+                      b3 = C >= 4 ? row[-3] : 0;
+        if (r < b0) continue;
+        r -= b0;
+        const int32_t c = a.n - 1 - e;
+        mask |= 1u << c;
+        if (i == p) {   // u, the lowest model
+            u = c;
+            R = r;
+        } else {
+            const int32_t o = i - 1;
+            const int32_t* rc = binom + c * kBinomRow + 3;
+            mb.r01[o] = R - (t0 + b0) + t1;
+            mb.c2[o] = rc[2];
+            if (C >= 3) {
+                mb.r12[o] = t2 - (t1 + b1);
+                mb.c3[o] = rc[3];
             }
+            if (C >= 4) {
+                mb.r23[o] = t3 - (t2 + b2);
+                mb.c4[o] = rc[4];
+            }
+            t0 += b0;
+            t1 += b1;
+            t2 += b2;
+            t3 += b3;
         }
-    *chosen = tb;
+        --i;
+    }
+    __builtin_amdgcn_wave_barrier();
+    const double* f = a.layers + (int64_t)(k - 2) * ((int64_t)1 << a.n);
+    const int32_t P = p - 1;   // members besides u
+    BestSet best = {__builtin_inf(), 0u};
+    if (layer_holds(k - 1, p - 1, a.n, C, a.G) && t == 0)
+        keep_first_min(best, f[prev.start[p - 1] + R] + a.cost[u], 1u << 15);
+    if (C >= 2 && p >= 2 && layer_holds(k - 1, p - 2, a.n, C, a.G)) {
+        const double* f2 = f + prev.start[p - 2];
+        const double* g2 = a.cost + size_base(a.n, 2) + u;
+        for (int32_t o = t; o < P; o += L)
+            keep_first_min(best, f2[mb.r01[o]] + g2[mb.c2[o]],
+                           (2u << 15) | (uint32_t)(P - 1 - o));
+    }
+    if (C >= 3 && p >= 3 && layer_holds(k - 1, p - 3, a.n, C, a.G)) {
+        const double* f3 = f + prev.start[p - 3];
+        const double* g3 = a.cost + size_base(a.n, 3) + u;
+        const int32_t total = P * (P - 1) / 2;
+        for (int32_t x0 = t; x0 < total; x0 += kBatch * L) {
+            double fv[kBatch], gv[kBatch];
+            uint32_t od[kBatch];
+#pragma unroll
+            for (int32_t b = 0; b < kBatch; ++b) {
+                const int32_t x = x0 + b * L;
+                const uint32_t w = tab.pair[x < total ? x : x0];
+                const int32_t l = (int32_t)(w & 31u), h = (int32_t)(w >> 5);
+                fv[b] = f3[mb.r01[l] + mb.r12[h]];
+                gv[b] = g3[mb.c2[h] + mb.c3[l]];
+                od[b] = (3u << 15) | (uint32_t)((P - 1 - h) << 5) | (uint32_t)(P - 1 - l);
+            }
+#pragma unroll
+            for (int32_t b = 0; b < kBatch; ++b) keep_first_min(best, fv[b] + gv[b], od[b]);
+        }
+    }
+    if (C >= 4 && p >= 4 && layer_holds(k - 1, p - 4, a.n, C, a.G)) {
+        const double* f4 = f + prev.start[p - 4];
+        const double* g4 = a.cost + size_base(a.n, 4) + u;
+        const int32_t total = P * (P - 1) * (P - 2) / 6;
+        for (int32_t x0 = t; x0 < total; x0 += kBatch * L) {
+            double fv[kBatch], gv[kBatch];
+            uint32_t od[kBatch];
+#pragma unroll
+            for (int32_t b = 0; b < kBatch; ++b) {
+                const int32_t x = x0 + b * L;
+                const uint32_t w = tab.triple[x < total ? x : x0];
+                const int32_t l = (int32_t)(w & 31u), m = (int32_t)((w >> 5) & 31u),
+                              h = (int32_t)(w >> 10);
+                fv[b] = f4[mb.r01[l] + mb.r12[m] + mb.r23[h]];
+                gv[b] = g4[mb.c2[h] + mb.c3[m] + mb.c4[l]];
+                od[b] = (4u << 15) | (uint32_t)((P - 1 - h) << 10) |
+                        (uint32_t)((P - 1 - m) << 5) | (uint32_t)(P - 1 - l);
+            }
+#pragma unroll
+            for (int32_t b = 0; b < kBatch; ++b) keep_first_min(best, fv[b] + gv[b], od[b]);
+        }
+    }
+    for (int32_t o = L >> 1; o > 0; o >>= 1) {
+        const double v = __shfl_xor(best.v, o, 64);
+        const uint32_t od = (uint32_t)__shfl_xor((int)best.order, o, 64);
+        keep_first_min(best, v, od);
+    }
     return best;
 }
 
-// Masks of each popcount per lane of the layer kernel.
-constexpr int kMasksPerLane = 1;
-
-// Lanes of one layer launch: for each admissible popcount p, lane_start[p]
-// is the first lane of its masks (lanes [lane_start[p], lane_start[p + 1])
-// enumerate the C(n, p) masks of popcount p, kMasksPerLane each).
-struct LayerPlan {
-    int32_t lane_start[RM_MAX_OPT_MODELS + 2];
-};
-
-// C(x, y) for 0 <= x, y <= 24 from the LDS table (Pascal's triangle).
-__device__ inline int32_t binom_tab(const int32_t* tab, int32_t x, int32_t y)
+// The members of a chosen set besides the mask's lowest model: offset x in
+// the order's fields names the x-th lowest of the others.
+__device__ inline uint32_t chosen_members(uint32_t mask, uint32_t order)
 {
-    return (y < 0 || y > x) ? 0 : tab[x * (RM_MAX_OPT_MODELS + 1) + y];
+    const uint32_t size = order >> 15;
+    uint32_t t = 0;
+    for (uint32_t s = 2; s <= size; ++s) {
+        uint32_t x = (order >> (5 * (s - 2))) & 31u, w = mask & (mask - 1);
+        while (x--) w &= w - 1;
+        t |= w & (0u - w);
+    }
+    return t;
 }
 
-__global__ __launch_bounds__(kOptBlock) void layer_kernel(OptArgs a, int32_t k, LayerPlan plan)
+// Group g of 2^log2_lanes lanes takes entry g of layer k.
+template <int C>
+__global__ __launch_bounds__(kOptBlock) void layer_kernel(OptArgs a, int32_t k, int32_t log2_lanes,
+                                                          LayerPlan plan, LayerPlan prev)
 {
-    constexpr int32_t T = RM_MAX_OPT_MODELS + 1;
-    __shared__ int32_t tab[T * T];
-    if (threadIdx.x < T) {   // row x of Pascal's triangle: C(x, y) = C(x, y-1) (x-y+1) / y
-        const int32_t x = threadIdx.x;
-        int32_t c = 1;
-        for (int32_t y = 0; y < T; ++y) {
-            tab[x * T + y] = y <= x ? c : 0;
-            c = y < x ? c * (x - y) / (y + 1) : 0;
-        }
-    }
+    extern __shared__ int32_t lds[];
+    Members<C>* members = reinterpret_cast<Members<C>*>(lds);   // one per group of lanes
+    __shared__ LdsTables<C> tab;
+    stage_tables(tab);
     __syncthreads();
-    const int64_t full = (int64_t)1 << a.n;
-    const int32_t lane = (int32_t)(blockIdx.x * kOptBlock + threadIdx.x);
+    const int32_t L = 1 << log2_lanes;
+    const int32_t group = (int32_t)((blockIdx.x * kOptBlock + threadIdx.x) >> log2_lanes);
+    const int32_t t = (int32_t)threadIdx.x & (L - 1);
     int32_t p = 0;
-    while (p <= a.n && lane >= plan.lane_start[p + 1]) ++p;
-    if (p > a.n) return;
-    const int32_t count = binom_tab(tab, a.n, p);
-    int32_t r = (lane - plan.lane_start[p]) * kMasksPerLane;
-    if (r >= count) return;
-    // unrank r among the masks of popcount p in increasing order: the top
-    // bit is the largest b with C(b, p) <= r, and so on down
-    uint32_t m = 0;
-    {
-        int32_t rr = r, hi = a.n - 1;
-        for (int32_t i = p; i >= 1; --i) {
-            int32_t b = hi;
-            while (binom_tab(tab, b, i) > rr) --b;
-            m |= 1u << b;
-            rr -= binom_tab(tab, b, i);
-            hi = b - 1;
-        }
-    }
-    const int32_t last = (r + kMasksPerLane < count ? r + kMasksPerLane : count);
-    for (; r < last; ++r) {
-        uint32_t t = 0;
-        const double v = best_split(a, k, m, &t);
-        a.layers[(int64_t)(k - 1) * full + m] = v;
-        a.choice[(int64_t)(k - 1) * full + m] = t;
-        // Gosper's rule: the next larger mask with the same popcount
-        const uint32_t c = m & (0u - m), up = m + c;
-        m = p == 0 ? m : ((((up ^ m) >> 2) >> __builtin_ctz(c)) | up);
+    while (p <= a.n && group >= plan.start[p + 1]) ++p;
+    if (p > a.n) return;   // the group's lanes leave together
+    uint32_t mask;
+    const BestSet best = best_split(a, k, tab, prev, members[threadIdx.x >> log2_lanes],
+                                    a.n - sets_before(a.n, C, p), p, group - plan.start[p], t, L,
+                                    mask);
+    if (t == 0) {
+        const int64_t at = (int64_t)(k - 1) * ((int64_t)1 << a.n) + group;
+        a.layers[at] = best.v;
+        a.choice[at] = chosen_members(mask, best.order);
     }
 }
 
-// One lane: the optimum over k and one placement attaining it.
-__global__ void finish_kernel(OptArgs a)
+// One wave: layer G's mask (`all`, split over the 64 lanes; layer 1 comes
+// from the costs), the optimum over k and one placement attaining it.
+template <int C>
+__global__ __launch_bounds__(64) void finish_kernel(OptArgs a, LayerPlan prev)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int32_t n = a.n;
-    bool ok = true;
-    for (int32_t p = 0; p < n; ++p) ok = ok && a.models[p] >= 0 && a.models[p] < a.N;
-    if (!ok) {
-        if (a.status) atomicOr(a.status, RM_ST_BAD_MODEL_ID);
-        *a.best_mean = __builtin_nan("");
-        for (int32_t p = 0; p < n; ++p) a.best_device[p] = -1;
+    __shared__ Members<C> members;
+    __shared__ LdsTables<C> tab;
+    const int32_t n = a.n, lane = threadIdx.x;
+    bool mine = true;
+    for (int32_t p = lane; p < n; p += 64) mine = mine && a.models[p] >= 0 && a.models[p] < a.N;
+    if (__ballot(!mine)) {
+        if (lane == 0) {
+            if (a.status) atomicOr(a.status, RM_ST_BAD_MODEL_ID);
+            *a.best_mean = __builtin_nan("");
+        }
+        for (int32_t p = lane; p < n; p += 64) a.best_device[p] = -1;
         return;
     }
     if (n == 0) {
-        *a.best_mean = 0.0;
+        if (lane == 0) *a.best_mean = 0.0;
         return;
     }
+    stage_tables(tab);
+    __syncthreads();
     const int64_t full = (int64_t)1 << n;
     const uint32_t all = (uint32_t)(full - 1);
+    // place of the entry of mask m (popcount p) in layer k
+    auto place_of = [&](int32_t k, uint32_t m, int32_t p) {
+        int32_t x = 0;
+        if (lane < p && layer_holds(k, lane, n, C, a.G))   // popcounts below p
+            x = tab.binom[(n - sets_before(n, C, lane)) * kBinomRow + lane + 3];
+        if (lane < n && ((m >> lane) & 1u)) {   // model `lane`: members above it rank below
+            const int32_t above = __builtin_popcount(m >> lane) - 1;
+            x += tab.binom[(n - 1 - lane) * kBinomRow + above + 1 + 3];
+        }
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+        return (int64_t)(k - 1) * full + x;
+    };
+    BestSet last = {__builtin_inf(), 0u};
+    uint32_t mask = all;
+    if (a.G > 1) last = best_split(a, a.G, tab, prev, members, n, n, 0, lane, 64, mask);
     double best = __builtin_inf();
     int32_t kb = 0;
     for (int32_t k = 1; k <= a.G; ++k) {
-        if (!layer_holds(k, n, n, a.C, a.G)) continue;
-        const double v = a.layers[(int64_t)(k - 1) * full + all];
+        if (!layer_holds(k, n, n, C, a.G)) continue;
+        const double v = (k == a.G && k > 1) ? last.v : a.layers[place_of(k, all, n)];
         if (v < best) {
             best = v;
             kb = k;
         }
     }
-    *a.best_mean = best / (double)n;
-    for (int32_t p = 0; p < n; ++p) a.best_device[p] = -1;
+    if (lane == 0) *a.best_mean = best / (double)n;
+    // lane p: GPU of model p
+    int32_t device = -1, block = 0;
     uint32_t m = all;
-    int32_t block = 0;
     for (int32_t k = kb; k >= 1 && m; --k, ++block) {
-        const uint32_t t = a.choice[(int64_t)(k - 1) * full + m];
+        const uint32_t t = (k == a.G && k > 1)
+                               ? chosen_members(all, last.order)
+                               : a.choice[place_of(k, m, __builtin_popcount(m))];
         const uint32_t S = (m & (0u - m)) | t;
-        for (uint32_t x = S; x; x &= x - 1) a.best_device[__builtin_ctz(x)] = block;
+        if (lane < n && ((S >> lane) & 1u)) device = block;
         m ^= S;
     }
+    if (lane < n) a.best_device[lane] = device;
 }
 
-// C(n, p) for n <= 24 on the host.
-static int32_t binom_small_any(int32_t n, int32_t p)
+// Layers 2 .. G - 1 and the finish, for capacity C.
+template <int C>
+static hipError_t launch_layers(const OptArgs& a, LayerPlan prev, hipStream_t s)
 {
-    if (p < 0 || p > n) return 0;
-    int64_t c = 1;
-    for (int32_t t = 0; t < p; ++t) c = c * (n - t) / (t + 1);
-    return (int32_t)c;
+    for (int32_t k = 2; k < a.G; ++k) {
+        const LayerPlan plan = layer_plan(k, a.n, C, a.G);
+        const int32_t masks = plan.start[a.n + 1];
+        if (masks > 0) {
+            int32_t log2_lanes = 0;
+            while (log2_lanes < 6 && ((int64_t)masks << log2_lanes) < kLayerLanes) ++log2_lanes;
+            const int64_t lanes = (int64_t)masks << log2_lanes;
+            hipLaunchKernelGGL(layer_kernel<C>,
+                               dim3((unsigned)((lanes + kOptBlock - 1) / kOptBlock)),
+                               dim3(kOptBlock), (kOptBlock >> log2_lanes) * sizeof(Members<C>), s,
+                               a, k, log2_lanes, plan, prev);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        prev = plan;
+    }
+    hipLaunchKernelGGL(finish_kernel<C>, dim3(1), dim3(64), 0, s, a, prev);
+    return hipGetLastError();
 }
 
 size_t place_optimal_cost_entries(int32_t n, int32_t C)
@@ -367,31 +575,20 @@ hipError_t launch_place_optimal(int32_t n_models, const double* delay, const dou
     a.best_mean = best_mean;
     a.best_device = best_device;
     a.status = status;
+    const LayerPlan first = layer_plan(1, n, C, G);
     if (n > 0) {
         const int32_t sets = n_sets_upto(n, C);
-        hipLaunchKernelGGL(cost_kernel, dim3((unsigned)((sets + kOptBlock - 1) / kOptBlock)),
-                           dim3(kOptBlock), 0, s, a, sets);
-        hipError_t e = hipGetLastError();
+        hipLaunchKernelGGL(cost_kernel, dim3((unsigned)((sets + kCostBlock - 1) / kCostBlock)),
+                           dim3(kCostBlock), 0, s, a, sets, first);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        for (int32_t k = 1; k <= G; ++k) {
-            // admissible popcounts of layer k (as layer_holds) and their lanes
-            LayerPlan plan;
-            int32_t lanes = 0;
-            for (int32_t p = 0; p <= n; ++p) {
-                plan.lane_start[p] = lanes;
-                const bool in = p >= k && p <= C * k && n - p <= C * (G - k);
-                if (in) lanes += (binom_small_any(n, p) + kMasksPerLane - 1) / kMasksPerLane;
-            }
-            plan.lane_start[n + 1] = lanes;
-            for (int32_t p = n + 2; p < RM_MAX_OPT_MODELS + 2; ++p) plan.lane_start[p] = lanes;
-            if (lanes == 0) continue;
-            hipLaunchKernelGGL(layer_kernel, dim3((unsigned)((lanes + kOptBlock - 1) / kOptBlock)),
-                               dim3(kOptBlock), 0, s, a, k, plan);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
     }
-    hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, s, a);
-    return hipGetLastError();
+    switch (C) {   // capacities up to RM_MAX_OPT_CAPACITY
+    case 1: return launch_layers<1>(a, first, s);
+    case 2: return launch_layers<2>(a, first, s);
+    case 3: return launch_layers<3>(a, first, s);
+    default: return launch_layers<4>(a, first, s);
+    }
 }
 
 }  // namespace rm
