@@ -279,9 +279,12 @@ int pair_matrix(const rm_device_desc* dev, int32_t n_models, const int64_t* kern
     rm::ModelInfo* info = reinterpret_cast<rm::ModelInfo*>(ws + L.info);
     rm::SimRecord* sim = adjusted ? reinterpret_cast<rm::SimRecord*>(ws + L.sim) : nullptr;
 
+    rm::SimForm form;
+    form.general = rm::sim_general(d, n_kernels);
+    form.half = opts->policy == RM_POLICY_EQUAL;
     hipError_t e = rm::launch_prepare(d, pk, n_models, kernel_offsets, n_kernels, grid, threads,
-                                      regs, smem, duration, records, sim, first, kernel_count,
-                                      iso_time, info, status, s);
+                                      regs, smem, duration, records, sim, form, first,
+                                      kernel_count, iso_time, info, status, s);
     if (e != hipSuccess) return launch_failed(e);
 
     rm::SweepArgs a;
@@ -307,7 +310,6 @@ int pair_matrix(const rm_device_desc* dev, int32_t n_models, const int64_t* kern
     a.starts = starts;
     a.status = status;
     a.sim = sim;
-    a.dur = duration;
     a.align_scratch = reinterpret_cast<double*>(ws + L.scratch);
     a.draws = opts->start_draws;
     a.cap_w = d.W;
@@ -315,6 +317,8 @@ int pair_matrix(const rm_device_desc* dev, int32_t n_models, const int64_t* kern
     a.cap_m = d.smem;
     a.cap_b = d.max_blocks;
     a.policy = opts->policy;
+    a.max_beta = rm::sim_max_beta(d);
+    a.sim_general = form.general;
 
     if (opts->sweep_event_begin) {
         e = hipEventRecord((hipEvent_t)opts->sweep_event_begin, s);

@@ -66,12 +66,52 @@ __device__ inline double add_chain(const double* buf, double* start, int len, do
     return run;
 }
 
+// What a kernel of footprint `used` leaves of an SM capacity for its partner.
+__device__ inline uint32_t left_of(uint32_t cap, uint32_t used, bool half)
+{
+    const uint32_t held = half && used > cap / 2u ? cap / 2u : used;
+    return cap - held;
+}
+
+__device__ inline SimRecord sim_record(const Desc& d, SimForm form, double dur, uint32_t beta,
+                                       uint32_t wb, uint64_t rt, uint64_t m)
+{
+    SimRecord r;
+    r.d = dur;
+    if (form.general) {
+        const uint64_t shape = pack_shape(beta, wb, rt, m);
+        r.shape.shape_lo = (uint32_t)shape;
+        r.shape.shape_hi = (uint32_t)(shape >> 32);
+        // division constants of the (clamped) packed demands
+        uint32_t s0, s1, s2;
+        div_constant(wb & 0xffu, r.shape.mag_wb, s0);
+        div_constant((uint32_t)(shape >> 16) & 0xffffffu, r.shape.mag_rt, s1);
+        div_constant((uint32_t)(shape >> 40), r.shape.mag_m, s2);
+        r.shape.shifts = s0 | (s1 << 8) | (s2 << 16);
+        return r;
+    }
+    // a kernel with resident blocks demands at most the capacities
+    const float inf = __builtin_inff();
+    const uint32_t rt32 = beta ? (uint32_t)rt : 0u, m32 = beta ? (uint32_t)m : 0u;
+    const uint32_t lw = left_of((uint32_t)d.W, beta * wb, form.half);
+    const uint32_t lr = left_of((uint32_t)d.regs, beta * rt32, form.half);
+    const uint32_t lm = left_of((uint32_t)d.smem, beta * m32, form.half);
+    const uint32_t lb = left_of((uint32_t)d.max_blocks, beta, form.half);
+    r.ready.bytes = beta | ((2u * lw + 1u) << 8) | (lb << 16) | ((beta ? beta : 1u) << 24);
+    r.ready.inv_w = beta ? 1.0f / (float)(2u * wb) : inf;
+    r.ready.inv_r = rt32 ? 1.0f / (float)rt32 : inf;
+    r.ready.inv_m = m32 ? 1.0f / (float)m32 : inf;
+    r.ready.left_r = (float)lr + 0.5f;
+    r.ready.left_m = (float)lm + 0.5f;
+    return r;
+}
+
 __global__ __launch_bounds__(kPrepareThreads) void prepare_kernel(
     Desc d, Packing pk, int32_t n_models, const int64_t* __restrict__ offsets,
     int64_t n_kernels, const int32_t* __restrict__ grid, const int32_t* __restrict__ threads,
     const int32_t* __restrict__ regs, const int32_t* __restrict__ smem,
     const double* __restrict__ dur, Record* __restrict__ records, SimRecord* __restrict__ sim,
-    int64_t* __restrict__ model_first, int32_t* __restrict__ kernel_count,
+    SimForm form, int64_t* __restrict__ model_first, int32_t* __restrict__ kernel_count,
     double* __restrict__ iso_time, ModelInfo* __restrict__ info, int32_t* status)
 {
     __shared__ double buf[kBufSlots];
@@ -136,18 +176,7 @@ __global__ __launch_bounds__(kPrepareThreads) void prepare_kernel(
                                 const uint64_t rt = (uint64_t)(R[u] > 0 ? R[u] : 0) *
                                                     (uint64_t)(T[u] > 0 ? T[u] : 0);
                                 const uint64_t mm = (uint64_t)(M[u] > 0 ? M[u] : 0);
-                                SimRecord sr;
-                                sr.d = dur[x];
-                                sr.shape = pack_shape(o.beta, wb, rt, mm);
-                                // division constants of the (clamped) packed demands
-                                const uint32_t rtc = (uint32_t)(sr.shape >> 16) & 0xffffffu;
-                                const uint32_t mc = (uint32_t)(sr.shape >> 40);
-                                uint32_t s0, s1, s2;
-                                div_constant(wb & 0xffu, sr.mag_wb, s0);
-                                div_constant(rtc, sr.mag_rt, s1);
-                                div_constant(mc, sr.mag_m, s2);
-                                sr.shifts = s0 | (s1 << 8) | (s2 << 16);
-                                sim[x] = sr;
+                                sim[x] = sim_record(d, form, dur[x], o.beta, wb, rt, mm);
                             }
                         }
                     }
@@ -185,14 +214,14 @@ __global__ __launch_bounds__(kPrepareThreads) void prepare_kernel(
 hipError_t launch_prepare(const Desc& d, const Packing& pk, int32_t n_models,
                           const int64_t* offsets, int64_t n_kernels, const int32_t* grid,
                           const int32_t* threads, const int32_t* regs, const int32_t* smem,
-                          const double* duration, Record* records, SimRecord* sim,
+                          const double* duration, Record* records, SimRecord* sim, SimForm form,
                           int64_t* model_first, int32_t* kernel_count, double* iso_time,
                           ModelInfo* info, int32_t* status, hipStream_t s)
 {
     const unsigned blocks = (unsigned)(n_models < 65536 ? n_models : 65536);
     hipLaunchKernelGGL(prepare_kernel, dim3(blocks), dim3(kPrepareThreads), 0, s, d, pk,
                        n_models, offsets, n_kernels, grid, threads, regs, smem, duration,
-                       records, sim, model_first, kernel_count, iso_time, info, status);
+                       records, sim, form, model_first, kernel_count, iso_time, info, status);
     return hipGetLastError();
 }
 

@@ -36,22 +36,70 @@ struct alignas(16) ModelInfo {
 static_assert(sizeof(ModelInfo) == 16, "ModelInfo must be 16 bytes");
 
 // One kernel as the adjusted-occupancy simulation sees it: its isolated
-// duration, its launch shape on the busiest SM, packed as
+// duration and, on the busiest SM, its resident blocks beta, its per-block
+// demands (W_b warps, R T registers, M shared bytes) and its footprint, in
+// one of two forms that the launcher picks by the device's capacities and the
+// table's size (sim_general).
+// The usual form holds what an event needs ready to use, as floats:
+//   bytes   bits 0..7 beta, 8..15 2 left_w + 1, 16..23 left_b,
+//           24..31 max(beta, 1)
+//   left_r, left_m   + 1/2
+//   inv_w = 1 / (2 W_b), inv_r = 1 / (R T), inv_m = 1 / M, correctly rounded
+//           (infinite for no demand, and for a kernel with beta = 0)
+// where left_* is what the kernel leaves of each SM capacity for its partner:
+// capacity minus footprint, or at least the upper half of the capacity under
+// equal partitioning.  floor(left / x) = floor((left + 1/2) (1/x)): the
+// exact product is at least 1 / (2x) away from every integer, and the two
+// roundings shift it by less than 2^-23 (left + 1/2) / x, which is smaller
+// for left < 2^22 - 1.
+// The general form holds the launch shape, packed as
 //   bits  0..7   beta (resident blocks)      bits  8..15  W_b (warps/block)
 //   bits 16..39  R*T (registers/block)       bits 40..63  M (shared bytes/block)
 // (per-block demands are clamped to 2^24 - 1; only kernels with beta = 0 can
 // exceed the capacities, and those never interfere), and for each of the
 // three per-block demands the constant of an exact division by it
-// (div_constant), from which the block counts of Sec. 3.2 are floor
-// quotients: the multipliers, and their shifts one byte each in `shifts`
-// (W_b, R*T, M from the low byte up).
-struct alignas(16) SimRecord {
-    double d;
-    uint64_t shape;
+// (div_constant): the multipliers, and their shifts one byte each in
+// `shifts` (W_b, R*T, M from the low byte up).
+struct SimReady {
+    uint32_t bytes;
+    float inv_w, inv_r, inv_m;
+    float left_r, left_m;
+};
+struct SimShape {
+    uint32_t shape_lo, shape_hi;
     uint32_t mag_wb, mag_rt, mag_m;
     uint32_t shifts;
 };
+struct alignas(16) SimRecord {
+    double d;
+    union {
+        SimReady ready;
+        SimShape shape;
+    };
+};
 static_assert(sizeof(SimRecord) == 32, "SimRecord must be 32 bytes");
+
+// How prepare writes the SimRecords.
+struct SimForm {
+    bool general;   // the general form
+    bool half;      // equal partitioning: at least half of each capacity is left
+};
+
+// Most blocks a kernel can have on an SM (every block holds a warp).
+inline int32_t sim_max_beta(const Desc& d)
+{
+    return d.max_blocks < d.W ? d.max_blocks : d.W;
+}
+
+// Whether the simulation needs the general form: a capacity too large for
+// the float quotients, more blocks per SM than its LDS table of quotients is
+// built for (56 KB at 58), or a table of records past 32-bit offsets.  No
+// descriptor of a real GPU does.
+inline bool sim_general(const Desc& d, int64_t n_kernels)
+{
+    return d.regs >= (1 << 22) - 1 || d.smem >= (1 << 22) - 1 || sim_max_beta(d) > 58 ||
+           n_kernels > (int64_t(1) << 27) - 8;
+}
 
 // Multiplier and shift that divide every integer n < 2^23 by x exactly:
 // with l = ceil(log2 x) and k = 23 + l, mag = floor(2^k / x) + 1 gives
@@ -118,13 +166,13 @@ hipError_t launch_occupancy(const Desc& d, int64_t n, const int32_t* grid,
 // Per model: sequential prefix sums of the durations into records[u].end
 // and the packed footprints into records[u].fp, plus the model's first
 // kernel index, kernel count and isolated time (also packed into `info`).
-// `sim` (may be null) receives every kernel's SimRecord.
+// `sim` (may be null) receives every kernel's SimRecord in the given form.
 hipError_t launch_prepare(const Desc& d, const Packing& pk, int32_t n_models,
                           const int64_t* offsets, int64_t n_kernels,
                           const int32_t* grid, const int32_t* threads,
                           const int32_t* regs, const int32_t* smem,
                           const double* duration, Record* records,
-                          SimRecord* sim, int64_t* model_first,
+                          SimRecord* sim, SimForm form, int64_t* model_first,
                           int32_t* kernel_count, double* iso_time,
                           ModelInfo* info, int32_t* status, hipStream_t s);
 
@@ -148,12 +196,13 @@ struct SweepArgs {
     int32_t* status;
     // adjusted-occupancy simulation
     const SimRecord* sim;    // per-kernel duration and launch shape
-    const double* dur;       // isolated durations (the caller's array)
     double* align_scratch;   // OFFSETS, SAMPLED_STARTS: N*N*K per-alignment delays
     // SAMPLED_STARTS: K draws per unordered pair {i <= j}, row-major pairs
     const uint64_t* draws;
     int32_t cap_w, cap_r, cap_m, cap_b;   // SM capacities
     int32_t policy;          // RM_POLICY_* of the adjusted-occupancy simulation
+    int32_t max_beta;        // most blocks a kernel can have on an SM
+    bool sim_general;        // form of the SimRecords
 };
 
 // *ok = the byte-addressed sweep kernels (FIRST, OFFSETS, sampled) declare

@@ -28,110 +28,231 @@
 //    (no contraction), so the result equals the sequential definition bit
 //    for bit.
 //
-// Design (gfx950): the simulation is sequential in time, so one lane runs
-// one (pair, alignment) from start to end; lanes of a wave run different
-// pairs (FIRST: consecutive unordered pairs, both directions from one run)
-// or different pairs at the same offset (OFFSETS), so their trip counts are
-// alike.  Each lane streams its two models' 32-byte records from memory in
-// order, each model's next record in flight while the current event is
-// simulated (an event takes far longer than an L2 load).  The
-// quotients b~/beta and beta/b~ use a 256-entry LDS table of reciprocals and
-// one correction step (correctly rounded for integers up to 255, checked
-// exhaustively); the block counts are integer floor quotients by the
-// per-kernel division constants of the record (one 32 x 32 -> 64-bit
-// multiply and a shift; exact below 2^23).  The quotients of an event are
-// always computed and the results selected; only the move to a model's next
-// kernel branches.
+// Design (gfx950): the simulation is sequential in time, so a run -- one
+// (pair, alignment) from start to end -- is a chain of events.  Two
+// neighbouring lanes run it, each one model's side: a lane holds its model's
+// running kernel, the work left on it and its delay, and reads what it needs
+// of the partner's (what the partner's kernel leaves of each SM resource, its
+// wall time to completion) with DPP lane swaps, most of them operands of the
+// instructions that use them.  One lane for both sides took 165 to 180 VALU
+// instructions an event and wave: every event in some lane either side moves
+// on to its next kernel, so both moves were issued each time.  256 x 2000
+// FIRST is 32,896 runs: with two lanes each they fill every SIMD with one
+// wave (514 waves before).
+//  * Block counts: prepare writes 1/x of each per-block demand x and what
+//    the kernel leaves of each resource, as floats, so an event's three
+//    floor quotients are three products, their minimum with beta and the
+//    slots one integer minimum (the floats are positive, so their bits order
+//    as they do) and one conversion (exact, see SimRecord).
+//  * The quotients beta / b~ and b~ / beta of every block count come from an
+//    LDS table (16 bytes per entry), filled once per
+//    workgroup with correctly rounded quotients.  Kernels that do not interfere
+//    need no test of Eq. (2): what the partner leaves then holds all beta
+//    blocks, and beta / beta = 1.
+//  * Each lane streams its model's 32-byte records from memory in order, the
+//    next one in flight while the current event is simulated.
+// Devices and tables beyond the usual form's range (sim_general) run the
+// same events with integer division constants and fp64 divisions.
+#include <type_traits>
+
 #include "rm_common.h"
 
 namespace rm {
 
-constexpr int kSimBlock = 64;    // one wave per workgroup: waves spread over all SIMDs
-constexpr int kAhead = 1;        // records of each model requested ahead of use
+// Workgroup of many runs (few runs: one wave, see launch_runs).
+constexpr int kSimBlock = 256;
 
-// The running kernel of one model and the next kAhead records of its
-// sequence (loads in flight while earlier events are simulated).
-struct SimSide {
-    const SimRecord* rec;   // the model's records
-    int32_t q, k;           // kernel count, running kernel
-    double r;               // isolated work left of kernel k
-    uint32_t beta, wb, rt, m;
-    uint32_t fw, fr, fm;    // footprint: beta W_b warps, beta R T registers, beta M bytes
-    uint32_t mag_wb, mag_rt, mag_m;   // division constants of the three demands
-    uint32_t sh_wb, sh_rt, sh_m;
-    SimRecord next[kAhead]; // records k + 1 .. k + kAhead (clamped to the last)
-    double delay;
-    // constants of the running kernel that every event reads: beta as a
-    // double and its tabulated reciprocal, and what it leaves of each SM
-    // resource for the partner under equal partitioning (capacity minus the
-    // smaller of its footprint and half the capacity)
-    double tbeta, rbeta;
-    uint32_t lw, lr, lm, lb;
+// The partner lane's value (lanes 2r and 2r + 1 hold the two sides of a run).
+__device__ inline uint32_t other(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppXor1, 0xF, 0xF, true);
+}
+
+__device__ inline double other(double v)
+{
+    return dpp_take<kDppXor1>(v);
+}
+
+__device__ inline uint32_t bits_of(float v)
+{
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+__device__ inline float float_of(uint32_t b)
+{
+    return __builtin_bit_cast(float, b);
+}
+
+// A SimRecord is read as two vectors of four words: {d, d, bytes, inv_w} and
+// {inv_r, inv_m, left_r, left_m} (or the general form's words).  A side holds
+// its next record in such registers, and when it moves on it takes every word
+// out of them (taken) before it loads the record after next over them: left
+// to itself the compiler loads into other registers and copies them over at
+// once, which waits for the load in the same event.
+typedef uint32_t Words __attribute__((ext_vector_type(4)));
+
+// A copy of a word into another register, made where it stands.
+__device__ inline uint32_t taken(uint32_t v)
+{
+    uint32_t r;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
+__device__ inline double duration_of(Words lo)
+{
+    return __builtin_bit_cast(double, ((uint64_t)taken(lo.y) << 32) | taken(lo.x));
+}
+
+// Table of the quotients of an adjusted occupancy, at LDS address 0 (the
+// kernels have no static LDS): row beta holds {beta / b, b / beta} for b = 1
+// .. beta, before them at index 0 the entry of two kernels that cannot share
+// the SM in space and alternate, {2, 1/2}, and at index -1 that of a kernel
+// that waits for a partner's whole footprint, {inf, 0}.  Row 0 (a kernel with
+// no resident block, which never interferes) is {1, 1} throughout.
+typedef double Quotients __attribute__((ext_vector_type(2)));   // o/o~ and o~/o
+typedef __attribute__((address_space(3))) Quotients* LdsQuotients;
+
+__host__ __device__ constexpr uint32_t quotient_row_bytes(uint32_t max_beta)
+{
+    return (max_beta + 2u) * (uint32_t)sizeof(Quotients);
+}
+
+__host__ __device__ constexpr uint32_t quotient_bytes(uint32_t max_beta)
+{
+    return (max_beta + 1u) * quotient_row_bytes(max_beta);
+}
+
+// The reciprocals 1 / n go to LDS first (in row 0, filled last); a quotient
+// is then a product and one correction step, the correctly rounded quotient
+// for integers up to 255 (checked exhaustively).
+__device__ inline void build_quotients(int32_t max_beta)
+{
+    const auto at = [](int32_t x) { return (LdsQuotients)(size_t)(16u * (uint32_t)x); };
+    const int32_t row = max_beta + 2, n = row * (max_beta + 1);
+    for (int32_t x = threadIdx.x; x < row; x += blockDim.x) {
+        Quotients y;
+        y.x = y.y = 1.0 / (double)(x ? x : 1);
+        *at(x) = y;
+    }
+    __syncthreads();
+    for (int32_t x = row + (int32_t)threadIdx.x; x < n; x += blockDim.x) {
+        const int32_t beta = x / row, b = x - beta * row - 1;
+        const double yb = at(b > 0 ? b : 1)->x, ybeta = at(beta)->x;
+        Quotients e;
+        e.x = b > 0 ? div_by_recip((double)beta, (double)b, yb) : 2.0;
+        e.y = b > 0 ? div_by_recip((double)b, (double)beta, ybeta) : 0.5;
+        if (b < 0) {
+            e.x = __builtin_inf();
+            e.y = 0.0;
+        }
+        *at(x) = e;
+    }
+    __syncthreads();
+    for (int32_t x = threadIdx.x; x < row; x += blockDim.x) {
+        Quotients one;
+        one.x = one.y = 1.0;
+        *at(x) = one;
+    }
+    __syncthreads();
+}
+
+// How a lane's kernel runs beside its partner's: the two together, or one of
+// them first (it has priority or was running before).
+constexpr int kTogether = 0, kOwnFirst = 1, kOtherFirst = 2;
+
+// A model's records in order, through a buffer descriptor: 32-bit offsets,
+// and reads past the table's end give 0 (a side requests up to two records
+// past its model's last, which are never used).
+struct BufferStream {
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t next, end;   // offsets of the record to load, and of it when the model is done
+
+    __device__ BufferStream(const SweepArgs& g, int32_t first, int32_t q, int32_t k)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<SimRecord*>(g.sim), 0,
+                                                 (int)((uint32_t)g.n_kernels * 32u), 0x00027000)),
+          next(32u * (uint32_t)(first + k)), end(32u * (uint32_t)(first + q + 2))
+    {
+    }
+    __device__ void step() { next += 32u; }
+    __device__ bool done() const { return next == end; }   // after the step past the last kernel
+    __device__ Words lo() const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)next, 0, 0); }
+    __device__ Words hi() const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)next + 16, 0, 0);
+    }
 };
 
-__device__ inline void set_kernel(SimSide& s, const SimRecord& x)
-{
-    const uint64_t sh = x.shape;
-    s.beta = (uint32_t)sh & 0xffu;
-    s.wb = (uint32_t)(sh >> 8) & 0xffu;
-    s.rt = (uint32_t)(sh >> 16) & 0xffffffu;
-    s.m = (uint32_t)(sh >> 40);
-    s.fw = s.beta * s.wb;
-    s.fr = s.beta * s.rt;
-    s.fm = s.beta * s.m;
-    s.mag_wb = x.mag_wb;
-    s.mag_rt = x.mag_rt;
-    s.mag_m = x.mag_m;
-    s.sh_wb = x.shifts & 0xffu;
-    s.sh_rt = (x.shifts >> 8) & 0xffu;
-    s.sh_m = (x.shifts >> 16) & 0xffu;
-}
+// The same by pointers, for tables of any size; the last record is read
+// again instead of those past it.
+struct PointerStream {
+    const Words* base;
+    int32_t k, q;   // the record to load
 
-// The per-kernel constants above, after set_kernel.
-__device__ inline void kernel_constants(SimSide& s, const SweepArgs& g, const double* recip)
-{
-    const uint32_t cw = (uint32_t)g.cap_w, cr = (uint32_t)g.cap_r, cm = (uint32_t)g.cap_m,
-                   cb = (uint32_t)g.cap_b;
-    s.tbeta = (double)s.beta;
-    s.rbeta = recip[s.beta];
-    s.lw = cw - min(s.fw, cw / 2u);
-    s.lr = cr - min(s.fr, cr / 2u);
-    s.lm = cm - min(s.fm, cm / 2u);
-    s.lb = cb - min(s.beta, cb / 2u);
-}
-
-// Start model s at kernel k with `r` isolated work left on it.
-__device__ inline void sim_begin(SimSide& s, const SweepArgs& g, const double* recip,
-                                 const SimRecord* rec, int32_t q, int32_t k, double r)
-{
-    s.rec = rec;
-    s.q = q;
-    s.k = k;
-    s.delay = 0.0;
-    const int32_t kc = k < q ? k : q - 1;
-    const SimRecord cur = rec[kc];
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-        const int32_t kn = k + 1 + u < q ? k + 1 + u : q - 1;
-        s.next[u] = rec[kn];
+    __device__ PointerStream(const SweepArgs& g, int32_t first, int32_t q_, int32_t k_)
+        : base(reinterpret_cast<const Words*>(g.sim + first)), k(k_), q(q_)
+    {
     }
-    set_kernel(s, cur);
-    kernel_constants(s, g, recip);
-    s.r = r;
-}
+    __device__ void step() { ++k; }
+    __device__ bool done() const { return k == q + 2; }
+    __device__ const Words* at() const { return base + 2 * (int64_t)(k < q ? k : q - 1); }
+    __device__ Words lo() const { return at()[0]; }
+    __device__ Words hi() const { return at()[1]; }
+};
 
-// Move model s to its next kernel and request the record kAhead further on.
-__device__ inline void sim_advance(SimSide& s, const SweepArgs& g, const double* recip)
-{
-    ++s.k;
-    s.r = s.next[0].d;
-    set_kernel(s, s.next[0]);
-    kernel_constants(s, g, recip);
-#pragma unroll
-    for (int u = 0; u + 1 < kAhead; ++u) s.next[u] = s.next[u + 1];
-    const int32_t kn = s.k + kAhead < s.q ? s.k + kAhead : s.q - 1;
-    s.next[kAhead - 1] = s.rec[kn];
-}
+// The running kernel of one side in the usual form.
+struct ReadyKernel {
+    static constexpr bool kTable = true;          // reads the table of quotients
+    using Stream = BufferStream;
+    float inv_w, inv_r, inv_m;
+    uint32_t beta;                                // the float's bits
+    uint32_t left_w, left_r, left_m, left_b;      // floats' bits, for the partner
+    uint32_t row;                                 // LDS address of its row of quotients
+
+    __device__ void set(Words lo, Words hi, uint32_t row_bytes)
+    {
+        const uint32_t bytes = lo.z;   // (converted, so copied)
+        inv_w = float_of(taken(lo.w));
+        inv_r = float_of(taken(hi.x));
+        inv_m = float_of(taken(hi.y));
+        left_r = taken(hi.z);
+        left_m = taken(hi.w);
+        beta = bits_of((float)(bytes >> 24));
+        left_w = bits_of((float)((bytes >> 8) & 0xffu));
+        left_b = bits_of((float)((bytes >> 16) & 0xffu));
+        row = __umul24(bytes & 0xffu, row_bytes);
+    }
+
+    template <int POLICY>
+    __device__ Quotients quotients(const SweepArgs& g, int order) const
+    {
+        uint32_t lw = other(left_w), lr = other(left_r), lm = other(left_m), lb = other(left_b);
+        if (POLICY == RM_POLICY_FCFS && order == kTogether) {
+            // equal partitioning: at least the upper half of each capacity
+            lw = max(lw, bits_of((float)(2u * (g.cap_w - g.cap_w / 2u) + 1u)));
+            lr = max(lr, bits_of((float)(g.cap_r - g.cap_r / 2u) + 0.5f));
+            lm = max(lm, bits_of((float)(g.cap_m - g.cap_m / 2u) + 0.5f));
+            lb = max(lb, bits_of((float)(g.cap_b - g.cap_b / 2u)));
+        }
+        const uint32_t fit = min(min(bits_of(float_of(lw) * inv_w), bits_of(float_of(lr) * inv_r)),
+                                 bits_of(float_of(lm) * inv_m));
+        const uint32_t v = min(min(beta, lb), fit);
+        uint32_t b = (uint32_t)float_of(v);
+        // together: alternating when either keeps no block (the factor, any
+        // above the table's most blocks, makes the partner's count a limit
+        // only when it is 0)
+        const uint32_t limit = (uint32_t)__umul24(other(b), 100u);
+        const uint32_t both = min(b, limit);
+        if (POLICY == RM_POLICY_EQUAL) {
+            b = both;
+        } else {
+            const uint32_t alone = b ? b : ~0u;   // index -1
+            const uint32_t own = (uint32_t)float_of(beta);
+            b = order == kOtherFirst ? alone : order == kOwnFirst ? own : both;
+        }
+        return *(LdsQuotients)(size_t)(row + (b << 4) + 16u);
+    }
+};
 
 // floor(left / x) for left below 2^23 through x's division constant (exact,
 // see div_constant); `none` when x = 0.
@@ -141,168 +262,297 @@ __device__ inline uint32_t fit(uint32_t left, uint32_t x, uint32_t mag, uint32_t
     return x ? q : none;
 }
 
-// Blocks of kernel k that fit on the SM while kernel l keeps every block it
-// has (l has priority or was running first).  l's footprint fits the SM
-// alone, so every difference is non-negative.
-__device__ inline uint32_t blocks_beside_whole(const SweepArgs& g, const SimSide& k,
-                                               const SimSide& l)
-{
-    uint32_t b = min(k.beta, (uint32_t)g.cap_b - l.beta);
-    b = min(b, fit((uint32_t)g.cap_w - l.fw, k.wb, k.mag_wb, k.sh_wb, b));
-    b = min(b, fit((uint32_t)g.cap_r - l.fr, k.rt, k.mag_rt, k.sh_rt, b));
-    b = min(b, fit((uint32_t)g.cap_m - l.fm, k.m, k.mag_m, k.sh_m, b));
-    return b;
-}
+// The running kernel of one side in the general form.
+struct ShapeKernel {
+    static constexpr bool kTable = false;
+    using Stream = PointerStream;
+    uint32_t beta, wb, rt, m;
+    uint32_t fw, fr, fm;              // footprint: beta W_b warps, beta R T registers, beta M bytes
+    uint32_t mag_wb, mag_rt, mag_m;   // division constants of the three demands
+    uint32_t shifts;
 
-// Blocks of kernel k that fit on the SM when kernel l holds at most half of
-// every resource (Sec. 3.2 "Adjusted occupancy", equal partitioning).
-__device__ inline uint32_t blocks_beside(const SweepArgs& g, const SimSide& k, const SimSide& l)
-{
-    (void)g;
-    uint32_t b = min(k.beta, l.lb);
-    b = min(b, fit(l.lw, k.wb, k.mag_wb, k.sh_wb, b));
-    b = min(b, fit(l.lr, k.rt, k.mag_rt, k.sh_rt, b));
-    b = min(b, fit(l.lm, k.m, k.mag_m, k.sh_m, b));
-    return b;
-}
+    __device__ void set(Words lo, Words hi, uint32_t)
+    {
+        const uint64_t sh = ((uint64_t)taken(lo.w) << 32) | taken(lo.z);
+        beta = (uint32_t)sh & 0xffu;
+        wb = (uint32_t)(sh >> 8) & 0xffu;
+        rt = (uint32_t)(sh >> 16) & 0xffffffu;
+        m = (uint32_t)(sh >> 40);
+        fw = beta * wb;
+        fr = beta * rt;
+        fm = beta * m;
+        mag_wb = taken(hi.x);
+        mag_rt = taken(hi.y);
+        mag_m = taken(hi.z);
+        shifts = taken(hi.w);
+    }
 
-// Which of the two running kernels was running first (FCFS).
-constexpr int kTogether = 0, kAFirst = 1, kBFirst = 2;
-
-// Run the two models until either has no kernel left; adds to A.delay and
-// B.delay.  Under RM_POLICY_PRIORITY B's kernels keep their blocks; under
-// RM_POLICY_FCFS `started` says which running kernel came first.
-// Branch-free per event: the adjusted block counts and quotients are always
-// computed and selected.
-template <int POLICY>
-__device__ inline void simulate(const SweepArgs& g, const double* recip, SimSide& A, SimSide& B,
-                                int started)
-{
-    while (A.k < A.q && B.k < B.q) {
+    template <int POLICY>
+    __device__ Quotients quotients(const SweepArgs& g, int order) const
+    {
+        const uint32_t cw = (uint32_t)g.cap_w, cr = (uint32_t)g.cap_r, cm = (uint32_t)g.cap_m,
+                       cb = (uint32_t)g.cap_b;
+        uint32_t ow = other(fw), orr = other(fr), om = other(fm), ob = other(beta);
         // Eq. (2): the two kernels interfere when any resource overflows
-        const bool hit = ((uint32_t)(A.fw + B.fw > (uint32_t)g.cap_w) |
-                          (uint32_t)(A.fr + B.fr > (uint32_t)g.cap_r) |
-                          (uint32_t)(A.fm + B.fm > (uint32_t)g.cap_m) |
-                          (uint32_t)(A.beta + B.beta > (uint32_t)g.cap_b)) != 0u;
-        const double ta = A.tbeta, tb = B.tbeta;
-        double slowA, speedA, slowB, speedB;
-        const int first = POLICY == RM_POLICY_PRIORITY ? kBFirst
-                          : POLICY == RM_POLICY_FCFS   ? started
-                                                       : kTogether;
-        if (first == kTogether) {
-            const uint32_t ba = blocks_beside(g, A, B);
-            const uint32_t bb = blocks_beside(g, B, A);
-            const bool space = ba >= 1u && bb >= 1u;
-            const double fa = (double)ba, fb = (double)bb;
-            const double qa_slow = div_by_recip(ta, fa, recip[ba]);      // o/o~ = beta / b~
-            const double qa_speed = div_by_recip(fa, ta, A.rbeta);  // o~/o = b~ / beta
-            const double qb_slow = div_by_recip(tb, fb, recip[bb]);
-            const double qb_speed = div_by_recip(fb, tb, B.rbeta);
-            slowA = space ? qa_slow : 2.0;
-            speedA = space ? qa_speed : 0.5;
-            slowB = space ? qb_slow : 2.0;
-            speedB = space ? qb_speed : 0.5;
-        } else {
-            // the first kernel at its isolated speed, the other beside its
-            // whole footprint (no progress while not one block fits)
-            const bool aFirst = first == kAFirst;
-            const uint32_t bo = aFirst ? blocks_beside_whole(g, B, A) : blocks_beside_whole(g, A, B);
-            const double to = aFirst ? tb : ta, fo = (double)bo;
-            const double slow_o = bo ? div_by_recip(to, fo, recip[bo]) : __builtin_inf();
-            const double speed_o = bo ? div_by_recip(fo, to, aFirst ? B.rbeta : A.rbeta) : 0.0;
-            slowA = aFirst ? 1.0 : slow_o;
-            speedA = aFirst ? 1.0 : speed_o;
-            slowB = aFirst ? slow_o : 1.0;
-            speedB = aFirst ? speed_o : 1.0;
+        const bool hit = (fw + ow > cw) | (fr + orr > cr) | (fm + om > cm) | (beta + ob > cb);
+        const bool together = POLICY == RM_POLICY_EQUAL || order == kTogether;
+        if (together) {   // the partner holds at most half of every resource
+            ow = min(ow, cw / 2u);
+            orr = min(orr, cr / 2u);
+            om = min(om, cm / 2u);
+            ob = min(ob, cb / 2u);
         }
-        slowA = hit ? slowA : 1.0;
-        speedA = hit ? speedA : 1.0;
-        slowB = hit ? slowB : 1.0;
-        speedB = hit ? speedB : 1.0;
-        const double tA = A.r * slowA;   // wall time until A's kernel completes
-        const double tB = B.r * slowB;
-        // the stretch ends when the first kernel completes; fmin and !(a > b)
-        // treat the two models alike even for a NaN time (from a NaN
-        // duration), which completes both, so every iteration advances
-        const double e = fmin(tA, tB);
-        const bool doneA = !(tA > tB), doneB = !(tB > tA);
-        const double wA = e * speedA, wB = e * speedB;
-        A.delay = A.delay + (doneA ? e - A.r : e - wA);
-        B.delay = B.delay + (doneB ? e - B.r : e - wB);
-        A.r = A.r - wA;
-        B.r = B.r - wB;
-        if (POLICY == RM_POLICY_FCFS)   // the kernel that did not complete came first
-            started = (doneA && doneB) ? kTogether : (doneA ? kBFirst : kAFirst);
-        if (doneA) sim_advance(A, g, recip);
-        if (doneB) sim_advance(B, g, recip);
+        uint32_t b = min(beta, cb - ob);
+        b = min(b, fit(cw - ow, wb, mag_wb, shifts & 0xffu, b));
+        b = min(b, fit(cr - orr, rt, mag_rt, (shifts >> 8) & 0xffu, b));
+        b = min(b, fit(cm - om, m, mag_m, (shifts >> 16) & 0xffu, b));
+        const bool space = min(b, other(b)) >= 1u;
+        Quotients e;
+        e.x = (double)beta / (double)b;
+        e.y = (double)b / (double)beta;
+        if (together && !space) {
+            e.x = 2.0;
+            e.y = 0.5;
+        }
+        if (!together && b == 0u) {
+            e.x = __builtin_inf();
+            e.y = 0.0;
+        }
+        if (!hit || (!together && order == kOwnFirst)) e.x = e.y = 1.0;
+        return e;
+    }
+};
+
+// min(x, y) of two times in one instruction; a NaN loses against a number,
+// as with fmin (the library minimum first quiets signalling NaNs, which
+// products never are).
+__device__ inline double min_time(double x, double y)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+
+// One side of a run: its model's records from `first`, of which kernels
+// k .. q - 1 are still to run, kernel k with r isolated work left.  Both
+// lanes of a run call this together; they return their model's delay when
+// either model has run out of kernels.  `order` says which running kernel
+// came first (FCFS; fixed under PRIORITY).
+//
+// One event: whether this side's kernel completes; the work left and the
+// delay move on (a kernel that completes leaves r to its successor).
+template <int POLICY, typename KERNEL>
+__device__ inline bool event(const SweepArgs& g, const KERNEL& own, double& r, double& delay,
+                             int& order)
+{
+    const Quotients e = own.template quotients<POLICY>(g, order);
+    const double t = r * e.x;          // wall time until this side's kernel completes
+    const double to = other(t);
+    // the stretch ends when the first kernel completes; the minimum and
+    // !(a > b) treat the two models alike even for a NaN time (from a NaN
+    // duration), which completes both, so every event advances
+    const double len = min_time(t, to);
+    const bool done = !(t > to);
+    const double w = len * e.y;        // work this side completes
+    delay = delay + (len - (done ? r : w));
+    r = r - w;
+    if (POLICY == RM_POLICY_FCFS)   // the kernel that did not complete came first
+        order = done ? (!(to > t) ? kTogether : kOtherFirst) : kOwnFirst;
+    return done;
+}
+
+// Both lanes of every run of which one lane is in the mask.
+__device__ inline uint64_t whole_runs(uint64_t m)
+{
+    constexpr uint64_t kEven = 0x5555555555555555ull;
+    return m | ((m & kEven) << 1) | ((m >> 1) & kEven);
+}
+
+template <int POLICY, typename KERNEL>
+__device__ inline double simulate(const SweepArgs& g, int32_t first, int32_t q, int32_t k,
+                                  double r, int order)
+{
+    const uint32_t row_bytes = quotient_row_bytes((uint32_t)g.max_beta);
+    typename KERNEL::Stream stream(g, first, q, k);
+    KERNEL own;
+    own.set(stream.lo(), stream.hi(), row_bytes);
+    stream.step();
+    Words lo = stream.lo(), hi = stream.hi();   // the next kernel's record
+    stream.step();
+    double delay = 0.0;
+    for (;;) {
+        if (event<POLICY>(g, own, r, delay, order)) {
+            r = duration_of(lo);
+            own.set(lo, hi, row_bytes);
+            __builtin_amdgcn_sched_barrier(0);   // the record has been read: load over it
+            lo = stream.lo();
+            hi = stream.hi();
+            stream.step();
+        }
+        const uint64_t over = __ballot(stream.done());
+        if (over && __builtin_amdgcn_inverse_ballot_w64(whole_runs(over))) break;
+    }
+    return delay;
+}
+
+// The same for few runs, where nothing but the wave itself hides a load: the
+// records of a side are requested kAhead kernels ahead.  A request stays in
+// flight for kAhead events (the event loop is unrolled by kAhead, each event
+// with registers of its own for it) and is then written to the lane's ring
+// of kAhead records in LDS; the next kernel's record is read from the ring
+// into registers one event before it can be needed.  The request is issued
+// by every lane in every event, so that its place among the others in flight
+// is known: a lane whose kernel did not complete requests an offset past the
+// table, which reads no memory, and writes to a spare slot of its ring.  A
+// record requested when kernel k starts, k + 1 + kAhead, is in the ring from
+// the kAhead-th event on, and needed after kAhead of this side's kernels have
+// completed at the earliest; its slot is that of record k + 1, read before.
+constexpr int kAhead = 4;
+constexpr uint32_t kRingSlot = 64 * 16;                           // one vector per lane
+constexpr uint32_t kRingBytes = (kAhead + 1) * 2 * kRingSlot;     // of one wave; the last slot is spare
+typedef __attribute__((address_space(3))) Words* LdsWords;
+
+template <int POLICY>
+__device__ inline double simulate_ahead(const SweepArgs& g, int32_t first, int32_t q, int32_t k,
+                                        double r, int order)
+{
+    const uint32_t row_bytes = quotient_row_bytes((uint32_t)g.max_beta);
+    const uint32_t ring = quotient_bytes((uint32_t)g.max_beta) + 16u * (threadIdx.x & 63u);
+    const uint32_t spare = ring + kAhead * 2u * kRingSlot;
+    // slot of the record at table offset x (32 bytes a record)
+    const auto slot_of = [&](uint32_t x) {
+        static_assert(kAhead == 4 && kRingSlot == 1024, "shift");
+        return ring + ((x & (32u * (kAhead - 1))) << 6);
+    };
+    const auto put = [](uint32_t at, Words lo, Words hi) {
+        *(LdsWords)(size_t)at = lo;
+        *(LdsWords)(size_t)(at + kRingSlot) = hi;
+    };
+    BufferStream stream(g, first, q, k);
+    ReadyKernel own;
+    own.set(stream.lo(), stream.hi(), row_bytes);
+    stream.step();
+    Words lo = stream.lo(), hi = stream.hi();   // the next kernel's record
+    stream.step();
+#pragma unroll
+    for (int x = 0; x < kAhead; ++x) {   // records k + 2 .. k + 1 + kAhead
+        put(slot_of(stream.next), stream.lo(), stream.hi());
+        stream.step();
+    }
+    const uint32_t end = stream.end + 32u * kAhead;
+    Words flo[kAhead], fhi[kAhead];   // requests in flight
+    uint32_t to[kAhead];              // and their slots
+#pragma unroll
+    for (int x = 0; x < kAhead; ++x) {
+        flo[x] = fhi[x] = Words{0, 0, 0, 0};
+        to[x] = spare;
+    }
+    // the records read so far have landed (s_waitcnt vmcnt(0)): otherwise the
+    // compiler, which sees them join the loop's own, waits for requests in
+    // flight in every round
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    // The loop runs until every run of the wave is over, without leaving it
+    // in between, so that every path through it issues the same requests; a
+    // run that is over has its delay kept and goes on, on records that follow
+    // its models' or on none.
+    double delay = 0.0, result = 0.0;
+    uint64_t running = __ballot(true);
+    do {
+#pragma unroll
+        for (int x = 0; x < kAhead; ++x) {
+            const bool done = event<POLICY>(g, own, r, delay, order);
+            put(to[x], flo[x], fhi[x]);   // after the event's own, awaited LDS read
+            const uint32_t slot = slot_of(stream.next);
+            uint32_t from = 0xffffff00u;
+            to[x] = spare;
+            if (done) {
+                r = duration_of(lo);
+                own.set(lo, hi, row_bytes);
+                __builtin_amdgcn_sched_barrier(0);   // the record has been read: read over it
+                lo = *(LdsWords)(size_t)slot;
+                hi = *(LdsWords)(size_t)(slot + kRingSlot);
+                from = stream.next;
+                to[x] = slot;
+                stream.step();
+            }
+            flo[x] = __builtin_amdgcn_raw_buffer_load_b128(stream.rsrc, (int)from, 0, 0);
+            fhi[x] = __builtin_amdgcn_raw_buffer_load_b128(stream.rsrc, (int)from + 16, 0, 0);
+            uint64_t over = __ballot(stream.next == end) & running;
+            if (over) {
+                over = whole_runs(over);
+                if (__builtin_amdgcn_inverse_ballot_w64(over)) result = delay;
+                running &= ~over;
+            }
+        }
+    } while (running);
+    return result;
+}
+
+// A run's start on this lane's side, and the run.  PRIORITY: the odd lane's
+// kernels keep their blocks.  AHEAD: few runs (simulate_ahead).
+template <int POLICY, typename KERNEL, bool AHEAD = false>
+__device__ inline double run_side(const SweepArgs& g, const ModelInfo& own, int32_t k, double r,
+                                  int order)
+{
+    if (POLICY == RM_POLICY_PRIORITY) order = (threadIdx.x & 1) ? kOwnFirst : kOtherFirst;
+    if constexpr (AHEAD && KERNEL::kTable)
+        return simulate_ahead<POLICY>(g, own.first, own.q, k, r, order);
+    else
+        return simulate<POLICY, KERNEL>(g, own.first, own.q, k, r, order);
+}
+
+// Unordered pair x of the library under a symmetric policy (one run gives
+// both directions), ordered pair x under PRIORITY (the rule depends on the
+// roles: Delta_ij from the run in which model j's kernels keep their blocks).
+template <int POLICY>
+__device__ inline void run_pair(int32_t N, int64_t x, int32_t& i, int32_t& j)
+{
+    if (POLICY == RM_POLICY_PRIORITY) {
+        i = (int32_t)(x / N);
+        j = (int32_t)(x - (int64_t)i * N);
+    } else {
+        row_pair_at(N, x, i, j);
     }
 }
 
-// RN(1/n) for n = 0..255 (entry 0 unused).
-__device__ inline void build_recip_table(double* recip)
-{
-    for (int t = threadIdx.x; t < 256; t += blockDim.x) recip[t] = t ? 1.0 / (double)t : 0.0;
-    __syncthreads();
-}
-
 // ---------------------------------------------------------------------------
-// FIRST: one lane per unordered pair (i <= j), both directions from one run.
+// FIRST: one run per pair of run_pair.
 // ---------------------------------------------------------------------------
-template <int POLICY>
-__global__ __launch_bounds__(kSimBlock) void sim_first_kernel(SweepArgs g, int64_t n_pairs)
+template <int POLICY, typename KERNEL, bool AHEAD>
+__global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_first_kernel(SweepArgs g, int64_t n_runs)
 {
-    __shared__ double recip[256];
-    build_recip_table(recip);
-    const int64_t p = (int64_t)blockIdx.x * kSimBlock + threadIdx.x;
-    if (p >= n_pairs) return;
-    const int32_t N = g.n_models;
+    if (KERNEL::kTable) build_quotients(g.max_beta);
+    const int64_t x = (int64_t)blockIdx.x * (blockDim.x >> 1) + (threadIdx.x >> 1);
+    if (x >= n_runs) return;
+    const bool odd = threadIdx.x & 1;
     int32_t i, j;
-    row_pair_at(N, p, i, j);
-    const ModelInfo mi = g.info[i], mj = g.info[j];
-    double Di = 0.0, Dj = 0.0;
-    if (mi.q > 0 && mj.q > 0) {
-        SimSide A, B;
-        sim_begin(A, g, recip, g.sim + mi.first, mi.q, 0, g.sim[mi.first].d);
-        sim_begin(B, g, recip, g.sim + mj.first, mj.q, 0, g.sim[mj.first].d);
-        simulate<POLICY>(g, recip, A, B, kTogether);
-        Di = A.delay;
-        Dj = B.delay;
-        if (POLICY == RM_POLICY_PRIORITY && i != j) {
-            // the rule depends on the roles: Delta_ji from the run in which
-            // model i's kernels keep their blocks
-            sim_begin(A, g, recip, g.sim + mj.first, mj.q, 0, g.sim[mj.first].d);
-            sim_begin(B, g, recip, g.sim + mi.first, mi.q, 0, g.sim[mi.first].d);
-            simulate<POLICY>(g, recip, A, B, kTogether);
-            Dj = A.delay;
-        }
-    }
-    if (i == j) Dj = Di;   // (under priority the copy that keeps its blocks is B)
-    const int64_t ij = (int64_t)i * N + j, ji = (int64_t)j * N + i;
-    g.delay[ij] = Di;
-    g.delay[ji] = Dj;
-    if (g.slowdown) {
-        g.slowdown[ij] = slowdown_of(Di, mi.q, mj.q, mi.T);
-        g.slowdown[ji] = slowdown_of(Dj, mj.q, mi.q, mj.T);
-    }
-    if (g.per_alignment) {
-        g.per_alignment[ij] = Di;
-        g.per_alignment[ji] = Dj;
-    }
+    run_pair<POLICY>(g.n_models, x, i, j);
+    const int32_t a = odd ? j : i, b = odd ? i : j;   // this side's model, the partner's
+    const ModelInfo ma = g.info[a], mb = g.info[b];
+    double D = 0.0;
+    if (ma.q > 0 && mb.q > 0)
+        D = run_side<POLICY, KERNEL, AHEAD>(g, ma, 0, g.sim[ma.first].d, kTogether);
+    // a self pair's two sides agree; under PRIORITY the odd side kept its blocks
+    if (odd && (POLICY == RM_POLICY_PRIORITY || i == j)) return;
+    const int64_t ab = (int64_t)a * g.n_models + b;
+    g.delay[ab] = D;
+    if (g.slowdown) g.slowdown[ab] = slowdown_of(D, ma.q, mb.q, ma.T);
+    if (g.per_alignment) g.per_alignment[ab] = D;
 }
 
 // ---------------------------------------------------------------------------
-// OFFSETS: one lane per (ordered pair, offset r); model j joins
-// tau_r = T_i * r / K after model i.  Work item x = r * N^2 + pair, so the
-// lanes of a wave share r and have windows of similar length.  Model i runs
-// alone until tau: its kernel running at tau keeps P_i[k+1] - tau of work.
+// OFFSETS: one run per (ordered pair, offset r); model j joins
+// tau_r = T_i * r / K after model i.  Run x = r * N^2 + pair, so the runs of
+// a wave share r and have windows of similar length.  Model i runs alone
+// until tau: its kernel running at tau keeps P_i[k+1] - tau of work.
 // ---------------------------------------------------------------------------
-template <int POLICY>
-__global__ __launch_bounds__(kSimBlock) void sim_offsets_kernel(SweepArgs g, int64_t n_items)
+template <int POLICY, typename KERNEL, bool AHEAD>
+__global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_offsets_kernel(SweepArgs g, int64_t n_runs)
 {
-    __shared__ double recip[256];
-    build_recip_table(recip);
-    const int64_t x = (int64_t)blockIdx.x * kSimBlock + threadIdx.x;
-    if (x >= n_items) return;
+    if (KERNEL::kTable) build_quotients(g.max_beta);
+    const int64_t x = (int64_t)blockIdx.x * (blockDim.x >> 1) + (threadIdx.x >> 1);
+    if (x >= n_runs) return;
+    const bool odd = threadIdx.x & 1;
     const int64_t N = g.n_models;
     const int64_t NN = N * N;
     const int32_t K = g.num_offsets;
@@ -310,12 +560,12 @@ __global__ __launch_bounds__(kSimBlock) void sim_offsets_kernel(SweepArgs g, int
     const int64_t p = x - (int64_t)r * NN;
     const int32_t i = (int32_t)(p / N), j = (int32_t)(p - (int64_t)i * N);
     const ModelInfo mi = g.info[i], mj = g.info[j];
-    double Di = 0.0;
+    double D = 0.0;
     if (mi.q > 0 && mj.q > 0) {
         const double tau = mi.T * (double)r / (double)K;
         int32_t k = 0;
         double ri = g.sim[mi.first].d;
-        int started = kTogether;
+        bool i_first = false;
         if (tau > 0.0) {
             // kernels of i whose isolated interval ends by tau: P_i[k+1] <= tau
             const Record* Pi = g.rec + mi.first;   // Pi[k].end = P_i[k+1]
@@ -331,31 +581,38 @@ __global__ __launch_bounds__(kSimBlock) void sim_offsets_kernel(SweepArgs g, int
             ri = k < mi.q ? Pi[k].end - tau : 0.0;
             // kernel k started at P_i[k], before j's first kernel unless at tau
             const double start_k = k > 0 ? Pi[k - 1].end : 0.0;
-            if (k < mi.q && start_k < tau) started = kAFirst;
+            i_first = k < mi.q && start_k < tau;
         }
-        SimSide A, B;
-        sim_begin(A, g, recip, g.sim + mi.first, mi.q, k, ri);
-        sim_begin(B, g, recip, g.sim + mj.first, mj.q, 0, g.sim[mj.first].d);
-        simulate<POLICY>(g, recip, A, B, started);
-        Di = A.delay;
+        if (k < mi.q) {
+            const int order = !i_first ? kTogether : odd ? kOtherFirst : kOwnFirst;
+            const double rj = g.sim[mj.first].d;
+            D = run_side<POLICY, KERNEL, AHEAD>(g, odd ? mj : mi, odd ? 0 : k, odd ? rj : ri,
+                                         order);
+        }
     }
-    g.align_scratch[p * K + r] = Di;
-    if (g.per_alignment) g.per_alignment[p * K + r] = Di;
+    if (odd) return;
+    g.align_scratch[p * K + r] = D;
+    if (g.per_alignment) g.per_alignment[p * K + r] = D;
+}
+
+// Whether two kernels interfere (Eq. 2): their packed footprints, the device
+// bias added, reach a guard bit.
+__device__ inline bool interfere(const SweepArgs& g, int64_t u, int64_t v)
+{
+    return ((g.rec[u].fp + g.rec[v].fp + g.bias) & g.guard) != 0;
 }
 
 // ---------------------------------------------------------------------------
-// CONFLICT_STARTS: one workgroup per ordered pair; each lane runs start
-// pairs (s_i, s_j) whose kernels interfere and writes the per-alignment
+// CONFLICT_STARTS: one workgroup per ordered pair; its lane pairs run start
+// pairs (s_i, s_j) whose kernels interfere and write the per-alignment
 // scratch ([first_i + s_i][first_j + s_j], NaN outside C_ij) that the
 // reduction kernel of the temporal sweep reads.
 // ---------------------------------------------------------------------------
-constexpr int kSimStartsBlock = 256;
-
-template <int POLICY>
-__global__ __launch_bounds__(kSimStartsBlock) void sim_starts_kernel(SweepArgs g, int64_t n_pairs)
+template <int POLICY, typename KERNEL>
+__global__ __launch_bounds__(kSimBlock) void sim_starts_kernel(SweepArgs g, int64_t n_pairs)
 {
-    __shared__ double recip[256];
-    build_recip_table(recip);
+    if (KERNEL::kTable) build_quotients(g.max_beta);
+    const bool odd = threadIdx.x & 1;
     const int64_t N = g.n_models;
     const int64_t nk = g.n_kernels;
     for (int64_t p = blockIdx.x; p < n_pairs; p += gridDim.x) {
@@ -364,110 +621,164 @@ __global__ __launch_bounds__(kSimStartsBlock) void sim_starts_kernel(SweepArgs g
         const int64_t total = (int64_t)mi.q * mj.q;
         // the reduction flags and skips pairs beyond its capacity
         if ((int64_t)mi.q + mj.q > g.pair_cap || total > g.starts_cap) continue;
-        for (int64_t c = threadIdx.x; c < total; c += kSimStartsBlock) {
+        for (int64_t c = threadIdx.x >> 1; c < total; c += kSimBlock / 2) {
             const int32_t si = (int32_t)(c / mj.q), sj = (int32_t)(c - (int64_t)si * mj.q);
-            SimSide A, B;
-            sim_begin(A, g, recip, g.sim + mi.first, mi.q, si, g.sim[mi.first + si].d);
-            sim_begin(B, g, recip, g.sim + mj.first, mj.q, sj, g.sim[mj.first + sj].d);
-            const bool hit = (A.fw + B.fw > (uint32_t)g.cap_w) | (A.fr + B.fr > (uint32_t)g.cap_r) |
-                             (A.fm + B.fm > (uint32_t)g.cap_m) |
-                             (A.beta + B.beta > (uint32_t)g.cap_b);
             double v = __builtin_nan("");
-            if (hit) {
-                simulate<POLICY>(g, recip, A, B, kTogether);
-                v = A.delay;
+            if (interfere(g, (int64_t)mi.first + si, (int64_t)mj.first + sj)) {
+                const int32_t k = odd ? sj : si;
+                const ModelInfo own = odd ? mj : mi;
+                v = run_side<POLICY, KERNEL>(g, own, k, g.sim[own.first + k].d, kTogether);
             }
-            g.starts[((int64_t)mi.first + si) * nk + mj.first + sj] = v;
+            if (!odd) g.starts[((int64_t)mi.first + si) * nk + mj.first + sj] = v;
         }
     }
 }
 
 // ---------------------------------------------------------------------------
-// SAMPLED_STARTS: one lane per (unordered pair {i <= j}, draw r); draw x
-// starts model i at kernel floor(hi32(x) q_i / 2^32) and model j at
-// floor(lo32(x) q_j / 2^32).  The run is symmetric in the two models, so it
-// gives both directions; a draw whose start kernels do not interfere
-// (Eq. 2) is outside C_ij and yields NaN.  Item x = r * pairs + u, so the
-// lanes of a wave share r.  The per-draw delays go to align_scratch
-// ([ordered pair][r]) for the reduction kernel.
+// SAMPLED_STARTS: one run per (pair of run_pair, draw r); draw x of the
+// unordered pair {a <= b} starts model a at kernel floor(hi32(x) q_a / 2^32)
+// and model b at floor(lo32(x) q_b / 2^32).  A draw whose start kernels do
+// not interfere (Eq. 2) is outside C_ij and yields NaN.  Run x = r * pairs +
+// pair, so the runs of a wave share r.  The per-draw delays go to
+// align_scratch ([ordered pair][r]) for the reduction kernel.
 // ---------------------------------------------------------------------------
-template <int POLICY>
-__global__ __launch_bounds__(kSimBlock) void sim_sampled_kernel(SweepArgs g, int64_t n_items,
-                                                                int64_t n_upairs)
+template <int POLICY, typename KERNEL, bool AHEAD>
+__global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_sampled_kernel(SweepArgs g, int64_t n_runs,
+                                                                int64_t n_pairs)
 {
-    __shared__ double recip[256];
-    build_recip_table(recip);
-    const int64_t x = (int64_t)blockIdx.x * kSimBlock + threadIdx.x;
-    if (x >= n_items) return;
-    const int32_t N = g.n_models;
+    if (KERNEL::kTable) build_quotients(g.max_beta);
+    const int64_t x = (int64_t)blockIdx.x * (blockDim.x >> 1) + (threadIdx.x >> 1);
+    if (x >= n_runs) return;
+    const bool odd = threadIdx.x & 1;
+    const int64_t N = g.n_models;
     const int32_t K = g.num_offsets;
-    const int32_t r = (int32_t)(x / n_upairs);
-    const int64_t u = x - (int64_t)r * n_upairs;
+    const int32_t r = (int32_t)(x / n_pairs);
     int32_t i, j;
-    row_pair_at(N, u, i, j);
+    run_pair<POLICY>(g.n_models, x - (int64_t)r * n_pairs, i, j);
     const ModelInfo mi = g.info[i], mj = g.info[j];
-    double Di = __builtin_nan(""), Dj = __builtin_nan("");
+    double D = __builtin_nan("");
     if (mi.q > 0 && mj.q > 0) {
-        const uint64_t w = g.draws[u * K + r];
-        const int32_t si = sampled_start((uint32_t)(w >> 32), mi.q);
-        const int32_t sj = sampled_start((uint32_t)w, mj.q);
-        SimSide A, B;
-        sim_begin(A, g, recip, g.sim + mi.first, mi.q, si, g.sim[mi.first + si].d);
-        sim_begin(B, g, recip, g.sim + mj.first, mj.q, sj, g.sim[mj.first + sj].d);
-        const bool hit = (A.fw + B.fw > (uint32_t)g.cap_w) | (A.fr + B.fr > (uint32_t)g.cap_r) |
-                         (A.fm + B.fm > (uint32_t)g.cap_m) | (A.beta + B.beta > (uint32_t)g.cap_b);
-        if (hit) {
-            simulate<POLICY>(g, recip, A, B, kTogether);
-            Di = A.delay;
-            Dj = B.delay;
-            if (POLICY == RM_POLICY_PRIORITY && i != j) {
-                // Delta_ji from the run in which model i's kernels keep their blocks
-                sim_begin(A, g, recip, g.sim + mj.first, mj.q, sj, g.sim[mj.first + sj].d);
-                sim_begin(B, g, recip, g.sim + mi.first, mi.q, si, g.sim[mi.first + si].d);
-                simulate<POLICY>(g, recip, A, B, kTogether);
-                Dj = A.delay;
-            }
+        const int64_t lo = i < j ? i : j, hi = i < j ? j : i;
+        const uint64_t w = g.draws[(row_start(N, lo) + (hi - lo)) * K + r];
+        const uint32_t wi = i <= j ? (uint32_t)(w >> 32) : (uint32_t)w;
+        const uint32_t wj = i <= j ? (uint32_t)w : (uint32_t)(w >> 32);
+        const int32_t si = sampled_start(wi, mi.q), sj = sampled_start(wj, mj.q);
+        if (interfere(g, (int64_t)mi.first + si, (int64_t)mj.first + sj)) {
+            const int32_t k = odd ? sj : si;
+            const ModelInfo own = odd ? mj : mi;
+            D = run_side<POLICY, KERNEL, AHEAD>(g, own, k, g.sim[own.first + k].d, kTogether);
         }
     }
-    const int64_t N64 = N;
-    g.align_scratch[(i * N64 + j) * K + r] = Di;
-    if (i != j) g.align_scratch[(j * N64 + i) * K + r] = Dj;
+    if (odd && (POLICY == RM_POLICY_PRIORITY || i == j)) return;
+    const int64_t a = odd ? j : i, b = odd ? i : j;
+    g.align_scratch[(a * N + b) * K + r] = D;
 }
 
 // ---------------------------------------------------------------------------
-// launchers: one kernel per scheduler policy, so that a kernel holds one
-// policy's event loop (the three together in one kernel took about 60% more
-// registers and halved the waves a SIMD holds)
+// launchers: one kernel per scheduler policy, record form and way of reading
+// ahead, so that a kernel holds one event loop (the policies together in one
+// kernel took about 60% more registers and halved the waves a SIMD holds)
 // ---------------------------------------------------------------------------
-template <typename Kernel>
-Kernel pick_policy(const SweepArgs& a, Kernel equal, Kernel priority, Kernel fcfs)
+
+// Runs so few that all their waves are on the chip at once, five to a CU by
+// the LDS of a 32-block device: then what a run waits for bounds the launch,
+// records are requested further ahead and every wave is a workgroup of its
+// own, so that the waves spread evenly.  256 x 2000 FIRST, 1028 waves: 0.775
+// ms against 0.88 ms without reading ahead (1.08 ms in workgroups of four
+// waves).  With more runs other waves fill the waits, and four waves share
+// one table of quotients: edge OFFSETS(64), 32,768 waves, 2.61 ms against
+// 2.81 ms with a table per wave.
+constexpr int64_t kAheadWaves = 5 * 256;
+constexpr size_t kAheadLds = 32 * 1024;
+
+static size_t ahead_lds(const SweepArgs& a)
 {
-    return a.policy == RM_POLICY_PRIORITY ? priority : a.policy == RM_POLICY_FCFS ? fcfs : equal;
+    return (size_t)quotient_bytes((uint32_t)a.max_beta) + kRingBytes;
+}
+
+struct PlainRun {
+    using Kernel = ReadyKernel;
+    static constexpr bool kAhead = false;
+};
+struct AheadRun {
+    using Kernel = ReadyKernel;
+    static constexpr bool kAhead = true;
+};
+struct GeneralRun {
+    using Kernel = ShapeKernel;
+    static constexpr bool kAhead = false;
+};
+
+template <typename Launch>
+static hipError_t pick_policy(const SweepArgs& a, Launch launch)
+{
+    switch (a.policy) {
+    case RM_POLICY_PRIORITY: return launch(std::integral_constant<int, RM_POLICY_PRIORITY>{});
+    case RM_POLICY_FCFS: return launch(std::integral_constant<int, RM_POLICY_FCFS>{});
+    default: return launch(std::integral_constant<int, RM_POLICY_EQUAL>{});
+    }
+}
+
+// launch(policy, kind of run, workgroups, lanes of one, LDS bytes) for n_runs
+// runs of two lanes.
+template <typename Launch>
+static hipError_t launch_runs(const SweepArgs& a, int64_t n_runs, Launch launch)
+{
+    return pick_policy(a, [&](auto policy) {
+        const auto with = [&](auto kind, int block, size_t lds) {
+            const int64_t blocks = (2 * n_runs + block - 1) / block;
+            if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+            return launch(policy, kind, dim3((unsigned)blocks), dim3((unsigned)block), lds);
+        };
+        if (a.sim_general) return with(GeneralRun{}, kSimBlock, 0);
+        if (2 * n_runs <= kAheadWaves * 64 && ahead_lds(a) <= kAheadLds)
+            return with(AheadRun{}, 64, ahead_lds(a));
+        return with(PlainRun{}, kSimBlock, (size_t)quotient_bytes((uint32_t)a.max_beta));
+    });
+}
+
+// Pairs of run_pair.
+static int64_t n_run_pairs(const SweepArgs& a)
+{
+    const int64_t N = a.n_models;
+    return a.policy == RM_POLICY_PRIORITY ? N * N : N * (N + 1) / 2;
 }
 
 hipError_t launch_sim_first(const SweepArgs& a, hipStream_t s)
 {
-    const int64_t N = a.n_models;
-    const int64_t n_pairs = N * (N + 1) / 2;
-    const int64_t blocks = (n_pairs + kSimBlock - 1) / kSimBlock;
-    const auto kernel = pick_policy(a, sim_first_kernel<RM_POLICY_EQUAL>,
-                                    sim_first_kernel<RM_POLICY_PRIORITY>,
-                                    sim_first_kernel<RM_POLICY_FCFS>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kSimBlock), 0, s, a, n_pairs);
-    return hipGetLastError();
+    const int64_t n_runs = n_run_pairs(a);
+    return launch_runs(a, n_runs, [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds) {
+        using K = decltype(kind);
+        hipLaunchKernelGGL((sim_first_kernel<decltype(policy)::value, typename K::Kernel, K::kAhead>),
+                           blocks, block, lds, s, a, n_runs);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_sim_offsets(const SweepArgs& a, hipStream_t s)
 {
     const int64_t N = a.n_models;
-    const int64_t n_items = N * N * a.num_offsets;
-    const int64_t blocks = (n_items + kSimBlock - 1) / kSimBlock;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    const auto kernel = pick_policy(a, sim_offsets_kernel<RM_POLICY_EQUAL>,
-                                    sim_offsets_kernel<RM_POLICY_PRIORITY>,
-                                    sim_offsets_kernel<RM_POLICY_FCFS>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kSimBlock), 0, s, a, n_items);
-    return hipGetLastError();
+    const int64_t n_runs = N * N * a.num_offsets;
+    return launch_runs(a, n_runs, [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds) {
+        using K = decltype(kind);
+        hipLaunchKernelGGL(
+            (sim_offsets_kernel<decltype(policy)::value, typename K::Kernel, K::kAhead>), blocks,
+            block, lds, s, a, n_runs);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_sim_sampled(const SweepArgs& a, hipStream_t s)
+{
+    const int64_t n_pairs = n_run_pairs(a);
+    const int64_t n_runs = n_pairs * a.num_offsets;
+    return launch_runs(a, n_runs, [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds) {
+        using K = decltype(kind);
+        hipLaunchKernelGGL(
+            (sim_sampled_kernel<decltype(policy)::value, typename K::Kernel, K::kAhead>), blocks,
+            block, lds, s, a, n_runs, n_pairs);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_sim_starts(const SweepArgs& a, hipStream_t s)
@@ -476,25 +787,17 @@ hipError_t launch_sim_starts(const SweepArgs& a, hipStream_t s)
     const int64_t n_pairs = N * N;
     const int64_t cap = int64_t(1) << 20;
     const unsigned blocks = (unsigned)(n_pairs < cap ? n_pairs : cap);
-    const auto kernel = pick_policy(a, sim_starts_kernel<RM_POLICY_EQUAL>,
-                                    sim_starts_kernel<RM_POLICY_PRIORITY>,
-                                    sim_starts_kernel<RM_POLICY_FCFS>);
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kSimStartsBlock), 0, s, a, n_pairs);
-    return hipGetLastError();
-}
-
-hipError_t launch_sim_sampled(const SweepArgs& a, hipStream_t s)
-{
-    const int64_t N = a.n_models;
-    const int64_t n_upairs = N * (N + 1) / 2;
-    const int64_t n_items = n_upairs * a.num_offsets;
-    const int64_t blocks = (n_items + kSimBlock - 1) / kSimBlock;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    const auto kernel = pick_policy(a, sim_sampled_kernel<RM_POLICY_EQUAL>,
-                                    sim_sampled_kernel<RM_POLICY_PRIORITY>,
-                                    sim_sampled_kernel<RM_POLICY_FCFS>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kSimBlock), 0, s, a, n_items, n_upairs);
-    return hipGetLastError();
+    return pick_policy(a, [&](auto policy) {
+        constexpr int kPolicy = decltype(policy)::value;
+        if (a.sim_general)
+            hipLaunchKernelGGL((sim_starts_kernel<kPolicy, ShapeKernel>), dim3(blocks),
+                               dim3(kSimBlock), 0, s, a, n_pairs);
+        else
+            hipLaunchKernelGGL((sim_starts_kernel<kPolicy, ReadyKernel>), dim3(blocks),
+                               dim3(kSimBlock), quotient_bytes((uint32_t)a.max_beta), s, a,
+                               n_pairs);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace rm

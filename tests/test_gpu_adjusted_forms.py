@@ -1,0 +1,103 @@
+"""The adjusted-occupancy simulation's two record forms and two ways of
+reading ahead against the CPU oracle, bit for bit, under every policy: float
+block counts at their largest capacities, the general form just beyond them
+(capacity, blocks per SM), block demands on and beside divisors of what a
+kernel leaves, kernels that fit no SM or are invalid, and runs few and many
+enough for either event loop."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_common import gpu_pair
+from paper_2607_16784_amd import api
+from paper_2607_16784_amd import workloads as W
+from test_gpu_adjusted import same
+
+pytestmark = pytest.mark.gpu
+ADJ = api.SWEEP_ADJUSTED
+TOP = (1 << 22) - 2     # largest capacity of the float form
+
+DEVICES = {
+    # warps, slots, registers, shared memory
+    "float-top": dict(num_sm=2, max_threads_per_sm=1024, max_blocks_per_sm=15, regs_per_sm=TOP,
+                      smem_per_sm=8000, warp_size=32),
+    "float-top-smem": dict(num_sm=2, max_threads_per_sm=1024, max_blocks_per_sm=15,
+                           regs_per_sm=8000, smem_per_sm=TOP, warp_size=32),
+    "general-capacity": dict(num_sm=2, max_threads_per_sm=1024, max_blocks_per_sm=15,
+                             regs_per_sm=TOP + 1, smem_per_sm=8000, warp_size=32),
+    "float-blocks": dict(num_sm=1, max_threads_per_sm=127 * 32, max_blocks_per_sm=58,
+                         regs_per_sm=65535, smem_per_sm=65535, warp_size=32),
+    "general-blocks": dict(num_sm=1, max_threads_per_sm=127 * 32, max_blocks_per_sm=255,
+                           regs_per_sm=65535, smem_per_sm=65535, warp_size=32),
+    "one-block": dict(num_sm=4, max_threads_per_sm=1024, max_blocks_per_sm=1, regs_per_sm=65536,
+                      smem_per_sm=65536, warp_size=64),
+}
+
+
+def library(device, models, q, seed):
+    """Kernels whose register and shared-memory demands sit on and beside
+    divisors of the capacities, with invalid and infeasible ones among them."""
+    rng = np.random.default_rng(seed)
+    n = models * q
+    threads = rng.choice([1, 32, 33, 64, 96, 256, 512], n)
+    threads = np.minimum(threads, device["max_threads_per_sm"])
+    parts = rng.integers(1, 80, n)
+    regs = device["regs_per_sm"] // (parts * threads) + rng.integers(-1, 2, n)
+    smem = device["smem_per_sm"] // rng.integers(1, 80, n) + rng.integers(-1, 2, n)
+    regs = np.where(rng.random(n) < 0.15, 0, np.maximum(regs, 0))
+    smem = np.where(rng.random(n) < 0.15, 0, np.maximum(smem, 0))
+    grid = rng.integers(1, 200, n)
+    odd = rng.random(n)
+    grid[odd < 0.01] = 0                                        # invalid
+    threads[(odd > 0.01) & (odd < 0.02)] = 2 * device["max_threads_per_sm"]   # fits no SM
+    smem[(odd > 0.02) & (odd < 0.03)] = 2 * device["smem_per_sm"]
+    # repeated durations, so that kernels of two models end together
+    dur = rng.choice([1.0, 2.0, 3.0, 0.5], n) * rng.choice([1.0, 1.0, 1.25, 0.7], n)
+    i32 = lambda x: x.astype(np.int32)  # noqa: E731
+    return dict(offsets=np.arange(models + 1, dtype=np.int64) * q, grid=i32(grid),
+                threads=i32(threads), regs=i32(regs), smem=i32(smem), duration=dur)
+
+
+@pytest.mark.parametrize("name", sorted(DEVICES))
+@pytest.mark.parametrize("policy", ["equal", "priority", "fcfs"])
+def test_forms(name, policy):
+    device = DEVICES[name]
+    L = library(device, 7, 90, seed=len(name))
+    pol = api.POLICY_NAMES[policy]
+    draws = W.start_draws(7, 9, seed=3)
+    for align, K in (("first", 1), ("offsets", 5), ("sampled_starts", 9)):
+        print("forms", name, policy, align, flush=True)
+        am = api.ALIGN_NAMES[align]
+        kw = dict(start_draws=draws) if align == "sampled_starts" else {}
+        want = oracle.pair_matrix(device, L, align_mode=am, num_offsets=K, sweep_mode=ADJ,
+                                  policy=pol, **kw)
+        if kw:
+            import torch
+            kw = dict(start_draws=torch.as_tensor(draws.reshape(-1)).cuda())
+        got = gpu_pair(device, L, align_mode=am, num_offsets=K, sweep_mode=ADJ, policy=pol, **kw)
+        same(got["delay"], want["delay"], f"{align} delay")
+        same(got["slowdown"], want["slowdown"], f"{align} slowdown")
+        assert got["status"] == want["status"]
+
+
+@pytest.mark.parametrize("policy", ["equal", "priority", "fcfs"])
+@pytest.mark.parametrize("models", [1, 285, 286])
+def test_few_and_many_runs(models, policy):
+    # two lanes a run: the 40,755 unordered pairs of 285 models fit 1280 waves,
+    # the 41,041 of 286 do not; lengths so short that runs end within the
+    # events read ahead
+    device = W.A100
+    L = library(device, models, 6, seed=models)
+    rng = np.random.default_rng(1)
+    lens = rng.integers(1, 7, models)
+    take = np.concatenate([np.arange(n) + 6 * m for m, n in enumerate(lens)])
+    for k in ("grid", "threads", "regs", "smem", "duration"):
+        L[k] = L[k][take]
+    L["offsets"] = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    pol = api.POLICY_NAMES[policy]
+    print("runs", models, policy, flush=True)
+    want = oracle.pair_matrix(device, L, sweep_mode=ADJ, policy=pol)
+    got = gpu_pair(device, L, sweep_mode=ADJ, policy=pol, per_alignment=True)
+    same(got["delay"], want["delay"], "delay")
+    same(got["per_alignment"], want["delay"], "per alignment")
+    same(got["slowdown"], want["slowdown"], "slowdown")
