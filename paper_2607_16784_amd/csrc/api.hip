@@ -265,7 +265,7 @@ int pair_matrix(const rm_device_desc* dev, int32_t n_models, const int64_t* kern
     const rm::Desc d = to_desc(dev);
     rm::Packing pk;
     if (!rm::make_packing(d, &pk)) return RM_EUNSUPPORTED;
-    if (!adjusted && opts->align_mode != RM_ALIGN_CONFLICT_STARTS) {
+    if (!adjusted) {
         bool lds_ok = false;
         const hipError_t le = rm::sweep_lds_from_zero(&lds_ok);
         if (le != hipSuccess) return launch_failed(le);

@@ -205,8 +205,8 @@ struct SweepArgs {
     bool sim_general;        // form of the SimRecords
 };
 
-// *ok = the byte-addressed sweep kernels (FIRST, OFFSETS, sampled) declare
-// no static LDS, so their dynamic LDS starts at address 0.
+// *ok = the byte-addressed temporal sweep kernels declare no static LDS, so
+// their dynamic LDS starts at address 0.
 hipError_t sweep_lds_from_zero(bool* ok);
 
 hipError_t launch_sweep_first(const SweepArgs& a, hipStream_t s);
@@ -339,6 +339,7 @@ constexpr int kDppXor1 = 0xB1;   // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;   // quad_perm [2,3,0,1]
 constexpr int kDppRor4 = 0x124;  // row_ror:4
 constexpr int kDppRor8 = 0x128;  // row_ror:8
+constexpr int kDppHalfMirror = 0x141;   // row_half_mirror: lane u of 8 reads lane 7 - u
 
 // A DPP lane move of a double with no "old" operand, so no copy of the
 // value is made first; a lane whose source lies outside its row reads 0.

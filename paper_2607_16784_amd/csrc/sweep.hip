@@ -1594,68 +1594,12 @@ __global__ __launch_bounds__(kAlignBlock) void sweep_offsets_kernel(
     }
 }
 
-// ---------------------------------------------------------------------------
-// CONFLICT_STARTS: ordered pair (i, j); every start pair (s_i, s_j) whose two
-// kernels interfere.  Per-alignment delays go to a [n_kernels]^2 scratch
-// (NaN outside the set); a second kernel reduces each pair's block.
-// ---------------------------------------------------------------------------
-// Work item b = (ordered pair p, slice u) with p = b / slices: the item's
-// waves take the pair's start pairs u * 4 + wave, stepping by slices * 4,
-// so a pair's thousands of start pairs spread over many workgroups.
-__global__ __launch_bounds__(kAlignBlock) void sweep_starts_kernel(SweepArgs g, int64_t n_pairs,
-                                                                   int32_t slices)
-{
-    extern __shared__ Record lds[];
-    __shared__ double s_recip[256];
-    build_recip(s_recip);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t N = g.n_models;
-    const int64_t nk = g.n_kernels;
-    constexpr int32_t kWaves = kAlignBlock / 64;
-    for (int64_t b = blockIdx.x; b < n_pairs * slices; b += gridDim.x) {
-        const int64_t p = b / slices;
-        const int32_t slice = (int32_t)(b - p * slices);
-        const int32_t i = (int32_t)(p / N), j = (int32_t)(p % N);
-        const int32_t qa = g.q[i], qb = g.q[j];
-        const int64_t fa = g.first[i], fb = g.first[j];
-        if (!pair_fits(qa, qb, g.pair_cap) || (int64_t)qa * qb > g.starts_cap) continue;
-        const Slots A{lds};
-        const Slots B{lds + padded(qa + 3)};
-        stage(A, g.rec, fa, qa, g.bias, tid, kAlignBlock);
-        stage(B, g.rec, fb, qb, 0, tid, kAlignBlock);
-        __syncthreads();
-
-        const int32_t total = qa * qb;
-        for (int32_t c = slice * kWaves + wave; c < total; c += slices * kWaves) {
-            const int32_t si = c / qb, sj = c - si * qb;
-            double* out = g.starts + (fa + si) * nk + (fb + sj);
-            if (!((A[si + 1].fp + B[sj + 1].fp) & g.guard)) {
-                if (lane == 0) *out = __builtin_nan("");
-                continue;
-            }
-            Align al;
-            al.k0 = si;
-            al.l0 = sj;
-            al.sa = -A[si].end;
-            al.sb = -B[sj].end;
-            al.w0 = 0.0;
-            finish_align(A, qa, B, qb, al);
-            double acc = 0.0, unused = 0.0;
-            sweep_alignment<false>(A, B, PlainRecip{s_recip}, al, lane, 64, g.guard, acc, unused);
-            acc = wave_sum_dpp(acc);
-            if (lane == 0) *out = acc;
-        }
-        __syncthreads();   // staging is reused by the next pair
-    }
-}
-
 // Order key of a non-NaN double: unsigned comparison of keys orders the
 // values as numbers (non-negative values keep their bits with the sign bit
-// set, negative ones are inverted).  +0 and -0 get different keys; either
-// is a correct order statistic where they tie.
+// set, negative ones are inverted); -0 counts as +0.
 __device__ inline uint64_t order_key(double v)
 {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint64_t b = __builtin_bit_cast(uint64_t, v + 0.0);
     return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
 }
 
@@ -1664,140 +1608,170 @@ __device__ inline double from_order_key(uint64_t k)
     return __builtin_bit_cast(double, (k >> 63) ? (k & 0x7fffffffffffffffull) : ~k);
 }
 
-// LDS scratch of the exact selection below.
-struct SelectScratch {
-    int32_t hist[2][256];     // digit counts, double-buffered by pass
-    int32_t digit, rank;      // the chosen digit and the rank left within it
-    int32_t tie;              // candidates that share the chosen digit
-    uint64_t lo, hi;          // min and max key (then the next key up)
+// The reduction of one ordered pair's block keeps its start pairs in LDS as
+// order keys (kNoKey outside C_ij).  The chain of barriers and LDS round trips
+// of one workgroup bounds it -- and the fetch of instructions that run once,
+// so the loops stay rolled.  The maximum is taken with the members' range, and
+// the median by counting 8-bit digits from the highest bit in which two
+// members differ until at most 64 members share the digits so far (one or two
+// digits, mostly), which one wave ranks: a pair of 60-kernel models took 20 us
+// with the members compacted first and seven or eight byte-aligned digits, 13
+// us with the start pairs in registers of unrolled loops, 8.7 us now.
+constexpr int kReduceBlock = 1024, kReduceBatch = 4;
+constexpr uint64_t kNoKey = ~0ull;
+
+struct ReduceScratch {
+    int32_t hist[3][256];     // digit counts, by pass modulo 3
+    int32_t count;            // members
+    int32_t n_list;
+    uint64_t lo, hi;          // smallest and largest key
+    uint64_t above;           // smallest key above the chosen digits
+    uint64_t list[64];        // members that share the chosen digits
+    uint64_t kth, next;
 };
 
-// The k-th smallest (0-based) of the n values in LDS, exactly, by radix
-// selection over the order keys.  The leading bytes that the smallest and
-// the largest key share are fixed first; then one 8-bit digit per pass:
-// the candidates' digits are counted in a 256-entry histogram, wave 0 finds
-// the digit whose cumulative count spans rank k, and the candidates narrow
-// to it.  With `next`, also the (k+1)-th smallest (k + 1 < n): the same key
-// when more candidates share it than rank k uses up, else the smallest key
-// above it.
-__device__ inline double block_kth(const double* vals, int32_t n, int32_t k, SelectScratch* sc,
-                                   double* next)
+// Smallest and largest of the wave's values that are not NaN (NaN when all
+// are), uniform: v_min_f64 and v_max_f64 return the other operand of a NaN.
+template <bool MAX>
+__device__ inline double wave_extreme(double v)
 {
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int nthreads = blockDim.x;
-    // smallest and largest key; both histograms cleared
-    if (tid == 0) {
-        sc->lo = ~0ull;
-        sc->hi = 0;
-    }
-    for (int t = tid; t < 512; t += nthreads) (&sc->hist[0][0])[t] = 0;
-    __syncthreads();
-    uint64_t mn = ~0ull, mx = 0;
-    for (int32_t t = tid; t < n; t += nthreads) {
-        const uint64_t key = order_key(vals[t]);
-        mn = key < mn ? key : mn;
-        mx = key > mx ? key : mx;
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint64_t a = __shfl_xor(mn, o, 64), b = __shfl_xor(mx, o, 64);
-        mn = a < mn ? a : mn;
-        mx = b > mx ? b : mx;
-    }
-    if (lane == 0) {
-        atomicMin((unsigned long long*)&sc->lo, (unsigned long long)mn);
-        atomicMax((unsigned long long*)&sc->hi, (unsigned long long)mx);
-    }
-    __syncthreads();
-    mn = sc->lo;
-    mx = sc->hi;
-    const uint64_t diff = mn ^ mx;
-    if (diff == 0) {   // every candidate has the same key
-        __syncthreads();
-        if (next) *next = from_order_key(mn);
-        return from_order_key(mn);
-    }
-    // the bytes above the highest differing bit are common to every candidate
-    int shift = 56;
-    while (shift > 0 && (diff >> shift) == 0) shift -= 8;
-    uint64_t mask = shift == 56 ? 0 : ~0ull << (shift + 8);
-    uint64_t prefix = mn & mask;
-    int32_t last_count = 0;
-    for (int pass = 0; shift >= 0; shift -= 8, ++pass) {
-        int32_t* h = sc->hist[pass & 1];
-        int32_t* other = sc->hist[(pass + 1) & 1];
-        for (int32_t t = tid; t < n; t += nthreads) {
-            const uint64_t key = order_key(vals[t]);
-            if ((key & mask) == prefix) atomicAdd(&h[(key >> shift) & 0xff], 1);
-        }
-        // the other histogram was last read before the previous barrier
-        for (int t = tid; t < 256; t += nthreads) other[t] = 0;
-        __syncthreads();
-        if (tid < 64) {
-            const int32_t c0 = h[4 * lane], c1 = h[4 * lane + 1], c2 = h[4 * lane + 2],
-                          c3 = h[4 * lane + 3];
-            int32_t incl = c0 + c1 + c2 + c3;
-            for (int o = 1; o < 64; o <<= 1) {
-                const int32_t up = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += up;
-            }
-            int32_t before = incl - (c0 + c1 + c2 + c3);
-            const int32_t cs[4] = {c0, c1, c2, c3};
-            for (int u = 0; u < 4; ++u) {
-                if (k >= before && k < before + cs[u]) {
-                    sc->digit = 4 * lane + u;
-                    sc->rank = k - before;
-                    sc->tie = cs[u];
-                }
-                before += cs[u];
-            }
-        }
-        __syncthreads();
-        const uint64_t digit = (uint64_t)sc->digit;
-        k = sc->rank;
-        last_count = sc->tie;
-        prefix |= digit << shift;
-        mask |= 0xffull << shift;
-    }
-    const double v = from_order_key(prefix);
-    if (next) {
-        if (k + 1 < last_count) {
-            *next = v;   // the next rank holds the same key
-        } else {
-            // smallest key above the k-th
-            if (tid == 0) sc->hi = ~0ull;
-            __syncthreads();
-            uint64_t up = ~0ull;
-            for (int32_t t = tid; t < n; t += nthreads) {
-                const uint64_t key = order_key(vals[t]);
-                up = (key > prefix && key < up) ? key : up;
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                const uint64_t a = __shfl_xor(up, o, 64);
-                up = a < up ? a : up;
-            }
-            if (lane == 0) atomicMin((unsigned long long*)&sc->hi, (unsigned long long)up);
-            __syncthreads();
-            *next = from_order_key(sc->hi);
-        }
-    }
-    __syncthreads();   // sc is reused by the caller's next selection
+    const auto two = [](double x, double y) {
+        double r;
+        if (MAX)
+            asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+        else
+            asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+        return r;
+    };
+    v = two(v, dpp_take<kDppXor1>(v));
+    v = two(v, dpp_take<kDppXor2>(v));
+    v = two(v, dpp_take<kDppRor4>(v));
+    v = two(v, dpp_take<kDppRor8>(v));
+    double r = read_lane(v, 0);
+    for (int row = 1; row < 4; ++row) r = two(r, read_lane(v, 16 * row));
+    return r;
+}
+
+// Inclusive prefix sums over the wave: shifts inside 16-lane rows, then the
+// row sums carried across rows.
+__device__ inline int32_t wave_scan(int32_t v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31
     return v;
 }
 
-__global__ __launch_bounds__(kAlignBlock) void starts_reduce_kernel(SweepArgs g, int64_t n_pairs)
+// The k-th smallest (0-based) of the workgroup's keys below kNoKey, and with
+// `two` the (k+1)-th (k + 1 below their number) in `next`.  mn and mx are the
+// smallest and the largest of them; sc's first histogram is clear.  Every thread
+// gets the result.
+__device__ inline uint64_t block_kth_key(const uint64_t* key, int32_t total, int32_t k,
+                                         uint64_t mn, uint64_t mx, bool two, ReduceScratch& sc,
+                                         uint64_t& next)
 {
-    extern __shared__ double vals[];
-    __shared__ int32_t count;
-    __shared__ SelectScratch sc;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    next = mn;
+    if (mn == mx) return mn;
+    int shift = 64 - 8 - __builtin_clzll(mn ^ mx);
+    if (shift < 0) shift = 0;
+    // the bits above the first digit are common to every member
+    uint64_t mask = shift == 56 ? 0 : ~0ull << (shift + 8);
+    uint64_t prefix = mn & mask;
+    int32_t tie = 0;
+    for (int pass = 0;; ++pass) {
+        int32_t* h = sc.hist[pass % 3];
+#pragma unroll 1
+        for (int32_t c = tid; c < total; c += kReduceBlock) {
+            const uint64_t x = key[c];
+            if (x != kNoKey && (x & mask) == prefix) atomicAdd(&h[(x >> shift) & 0xff], 1);
+        }
+        // the next pass's histogram was last read two passes ago, before the
+        // previous pass's barrier
+        if (tid < 256) sc.hist[(pass + 1) % 3][tid] = 0;
+        __syncthreads();
+        // every wave finds the digit whose cumulative count spans rank k
+        const int32_t c0 = h[4 * lane], c1 = h[4 * lane + 1], c2 = h[4 * lane + 2],
+                      c3 = h[4 * lane + 3];
+        const int32_t incl = wave_scan(c0 + c1 + c2 + c3);
+        int32_t before = incl - (c0 + c1 + c2 + c3);
+        const int src = (int)__builtin_ctzll(__ballot(k < incl));
+        int32_t digit = 4 * lane, here = c0;
+        if (k >= before + here) { before += here; ++digit; here = c1; }
+        if (k >= before + here) { before += here; ++digit; here = c2; }
+        if (k >= before + here) { before += here; ++digit; here = c3; }
+        digit = __builtin_amdgcn_readlane(digit, src);
+        k -= __builtin_amdgcn_readlane(before, src);
+        tie = __builtin_amdgcn_readlane(here, src);
+        prefix |= (uint64_t)digit << shift;
+        mask |= 0xffull << shift;
+        if (tie <= 64 || shift == 0) break;
+        shift = shift > 8 ? shift - 8 : 0;
+    }
+    // the members that share the digits, unless more than 64 share them all
+    // (they are equal then)
+    const bool ranked = tie <= 64;
+    const bool beyond = two && k + 1 >= tie;   // the next rank lies above them
+    const uint64_t top = prefix | ~mask;
+    uint64_t up = kNoKey;
+#pragma unroll 1
+    for (int32_t c = tid; c < total; c += kReduceBlock) {
+        const uint64_t x = key[c];
+        if (x == kNoKey) continue;
+        if (ranked && (x & mask) == prefix) sc.list[atomicAdd(&sc.n_list, 1)] = x;
+        if (beyond && x > top && x < up) up = x;
+    }
+    if (beyond) {
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint64_t x = __shfl_xor(up, o, 64);
+            up = x < up ? x : up;
+        }
+        if (lane == 0) atomicMin((unsigned long long*)&sc.above, (unsigned long long)up);
+    }
+    __syncthreads();
+    if (!ranked) {
+        next = beyond ? sc.above : prefix;
+        return prefix;
+    }
+    if (tid < 64) {
+        const uint64_t mine = lane < tie ? sc.list[lane] : kNoKey;
+        int32_t rank = 0;
+        for (int32_t u = 0; u < tie; ++u) {
+            const uint64_t x = sc.list[u];
+            rank += (x < mine || (x == mine && u < lane)) ? 1 : 0;
+        }
+        if (lane < tie && rank == k) sc.kth = mine;
+        if (lane < tie && rank == k + 1) sc.next = mine;
+    }
+    __syncthreads();
+    next = beyond ? sc.above : sc.next;
+    return sc.kth;
+}
+
+// c / q for 0 <= c < RM_MAX_STARTS_PER_PAIR and q >= 1 with r the float
+// nearest 1 / q: the exact product is at least 1/(2q) from every integer and
+// the roundings shift it by less than 2^-23 (c + 1/2) / q.
+__device__ inline int32_t start_row(int32_t c, float r)
+{
+    return (int32_t)(((float)c + 0.5f) * r);
+}
+
+__global__ __launch_bounds__(kReduceBlock) void starts_reduce_kernel(SweepArgs g, int64_t n_pairs)
+{
+    extern __shared__ uint64_t key[];   // starts_cap of them
+    __shared__ ReduceScratch sc;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int64_t N = g.n_models;
     const int64_t nk = g.n_kernels;
     for (int64_t p = blockIdx.x; p < n_pairs; p += gridDim.x) {
         const int32_t i = (int32_t)(p / N), j = (int32_t)(p % N);
         const int32_t qa = g.q[i], qb = g.q[j];
         const int64_t fa = g.first[i], fb = g.first[j];
-        const int64_t total = (int64_t)qa * qb;
-        if (!pair_fits(qa, qb, g.pair_cap) || total > g.starts_cap) {
+        const int64_t total64 = (int64_t)qa * qb;
+        if (!pair_fits(qa, qb, g.pair_cap) || total64 > g.starts_cap) {
             const double nan = __builtin_nan("");
             if (tid == 0) {
                 if (g.status) atomicOr(g.status, RM_ST_PAIR_TOO_LONG);
@@ -1805,66 +1779,79 @@ __global__ __launch_bounds__(kAlignBlock) void starts_reduce_kernel(SweepArgs g,
                 if (g.slowdown) g.slowdown[p] = nan;
             }
             if (g.per_alignment)
-                for (int64_t c = tid; c < total; c += kAlignBlock)
+                for (int64_t c = tid; c < total64; c += kReduceBlock)
                     g.per_alignment[(fa + c / qb) * nk + fb + c % qb] = nan;
             continue;
         }
-        if (tid == 0) count = 0;
+        const int32_t total = (int32_t)total64;
+        if (tid < 256) sc.hist[0][tid] = 0;
+        if (tid == 0) {
+            sc.count = 0;
+            sc.n_list = 0;
+            sc.lo = kNoKey;
+            sc.hi = 0;
+            sc.above = kNoKey;
+        }
+        // start pair c sits at (fa + c / qb) nk + fb + c mod qb
+        const float rq = 1.0f / (float)(qb > 0 ? qb : 1);
+        const int64_t first = fa * nk + fb, row = nk - qb;
+        const auto place = [&](int32_t c) { return first + c + start_row(c, rq) * row; };
+        int32_t members = 0;
+        double small = __builtin_nan(""), large = small;
+#pragma unroll 1
+        for (int32_t c0 = tid; c0 < total; c0 += kReduceBatch * kReduceBlock) {
+            // a batch's loads in flight before any value is used
+            double v[kReduceBatch];
+#pragma unroll
+            for (int u = 0; u < kReduceBatch; ++u) {
+                const int32_t c = c0 + u * kReduceBlock;
+                v[u] = g.starts[place(c < total ? c : c0)];
+            }
+#pragma unroll
+            for (int u = 0; u < kReduceBatch; ++u) {
+                const int32_t c = c0 + u * kReduceBlock;
+                if (c >= total) continue;
+                if (g.per_alignment) g.per_alignment[place(c)] = v[u];
+                const bool member = v[u] == v[u];
+                key[c] = member ? order_key(v[u]) : kNoKey;
+                members += member ? 1 : 0;
+                small = fmin(small, v[u]);
+                large = fmax(large, v[u]);
+            }
+        }
+        members = __builtin_amdgcn_readlane(wave_scan(members), 63);
         __syncthreads();
-        // compact the members of C_ij (non-NaN) into LDS with one counter add
-        // per wave and 64 candidates; every lane of the wave takes part (the
-        // order is irrelevant to the selection).  Eight candidates per lane
-        // are loaded before any is used, so their latencies overlap.
-        constexpr int kBatch = 8;
-        for (int32_t c0 = wave * 64; c0 < (int32_t)total; c0 += kAlignBlock * kBatch) {
-            double v[kBatch];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int32_t c = c0 + u * kAlignBlock + lane;
-                v[u] = __builtin_nan("");
-                if (c < (int32_t)total) v[u] = g.starts[(fa + c / qb) * nk + fb + c % qb];
-            }
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int32_t c = c0 + u * kAlignBlock + lane;
-                if (g.per_alignment && c < (int32_t)total)
-                    g.per_alignment[(fa + c / qb) * nk + fb + c % qb] = v[u];
-                const uint64_t members = __ballot(v[u] == v[u]);
-                const int32_t pop = __popcll(members);
-                // lane 0 alone adds the wave's count (per-lane operands would
-                // make the compiler scan the lanes one by one), then every
-                // lane reads the old value from lane 0
-                int32_t old = 0;
-                if (lane == 0) old = atomicAdd(&count, pop);
-                const int32_t base = __builtin_amdgcn_readfirstlane(old);
-                const int32_t below = __popcll(members & ((1ull << lane) - 1ull));
-                if (v[u] == v[u]) vals[base + below] = v[u];
-            }
+        small = wave_extreme<false>(small);
+        large = wave_extreme<true>(large);
+        if (lane == 0 && members > 0) {
+            atomicAdd(&sc.count, members);
+            atomicMin((unsigned long long*)&sc.lo, (unsigned long long)order_key(small));
+            atomicMax((unsigned long long*)&sc.hi, (unsigned long long)order_key(large));
         }
         __syncthreads();
         // median (mean of the two middle values for an even count) or
         // maximum of the members; 0 for an empty set
-        const int32_t n = count;
+        const int32_t n = sc.count;
         double D = 0.0;
         if (n > 0) {
+            const uint64_t mn = sc.lo, mx = sc.hi;
             if (g.reduce_mode == RM_REDUCE_MAX) {
                 // the oracle's maximum starts from 0 (delays are never
                 // negative unless a duration is)
-                const double m = block_kth(vals, n, n - 1, &sc, nullptr);
+                const double m = from_order_key(mx);
                 D = m > 0.0 ? m : 0.0;
-            } else if (n & 1) {
-                D = block_kth(vals, n, n / 2, &sc, nullptr);
             } else {
-                double hi = 0.0;
-                const double lo = block_kth(vals, n, n / 2 - 1, &sc, &hi);
-                D = (lo + hi) / 2.0;
+                uint64_t next;
+                const uint64_t mid = block_kth_key(key, total, (n - 1) / 2, mn, mx, (n & 1) == 0, sc, next);
+                D = from_order_key(mid);
+                if ((n & 1) == 0) D = (D + from_order_key(next)) / 2.0;
             }
         }
         if (tid == 0) {
             g.delay[p] = D;
             if (g.slowdown) g.slowdown[p] = slowdown_of(D, qa, qb, g.iso[i]);
         }
-        __syncthreads();   // count and vals are reused by the next pair
+        __syncthreads();   // sc is reused by the next pair
     }
 }
 
@@ -1995,21 +1982,19 @@ __device__ inline void walk_sampled(uint32_t pa, uint32_t sum, double sha, doubl
     acc_j = __builtin_fma(tt, al_p, acc_j);
 }
 
-// Start kernels of a draw and whether they interfere; for a draw in C_ij
-// also the boundaries of each model inside the draw's window (it ends when
-// the first of the two shifted timelines ends).  The staged models' slot 0
-// sit at byte addresses offA and offB (A's footprints biased), qa, qb > 0.
-__device__ inline bool draw_setup(uint32_t offA, uint32_t offB, int32_t qa, int32_t qb,
-                                  uint64_t x, uint64_t guard, int32_t& sa, int32_t& sb,
-                                  int32_t& nA, int32_t& nB)
+// Whether start kernels sa and sb interfere; if so also the boundaries of
+// each model inside the start pair's window (it ends when the first of the two
+// timelines, shifted so that both kernels start at 0, ends).  The staged
+// models' slot 0 sit at byte addresses offA and offB (A's footprints biased),
+// qa, qb > 0.
+__device__ inline bool start_window(uint32_t offA, uint32_t offB, int32_t qa, int32_t qb,
+                                    int32_t sa, int32_t sb, uint64_t guard, int32_t& nA,
+                                    int32_t& nB)
 {
-    sa = sampled_start((uint32_t)(x >> 32), qa);
-    sb = sampled_start((uint32_t)x, qb);
     nA = nB = 0;
     if (!((lds_rec(offA + 16u * (uint32_t)(sa + 1)).fp +
            lds_rec(offB + 16u * (uint32_t)(sb + 1)).fp) & guard))
         return false;
-    // timelines shifted so that kernels sa and sb start at 0
     const double sha = -lds_end(offA + 16u * (uint32_t)sa);
     const double shb = -lds_end(offB + 16u * (uint32_t)sb);
     const double endA = lds_end(offA + 16u * (uint32_t)qa) + sha;
@@ -2025,19 +2010,29 @@ __device__ inline bool draw_setup(uint32_t offA, uint32_t offB, int32_t qa, int3
     return true;
 }
 
-// Delays of one draw in C_ij for both directions, swept by one wave from its
-// start kernels (sa, sb) and window counts (nA, nB).  The results are
-// wave-uniform.
-__device__ inline void sweep_draw(uint32_t offA, uint32_t offB, int32_t sa, int32_t sb,
-                                  int32_t nA, int32_t nB, uint64_t guard, int lane, double& Di,
-                                  double& Dj)
+// Start kernels of a draw, and start_window of them.
+__device__ inline bool draw_setup(uint32_t offA, uint32_t offB, int32_t qa, int32_t qb,
+                                  uint64_t x, uint64_t guard, int32_t& sa, int32_t& sb,
+                                  int32_t& nA, int32_t& nB)
+{
+    sa = sampled_start((uint32_t)(x >> 32), qa);
+    sb = sampled_start((uint32_t)x, qb);
+    return start_window(offA, offB, qa, qb, sa, sb, guard, nA, nB);
+}
+
+// This lane's part (lane t of L) of both directions' delays of a start pair in
+// C_ij with window counts (nA, nB).
+template <int L>
+__device__ inline void walk_start_pair(uint32_t offA, uint32_t offB, int32_t sa, int32_t sb,
+                                       int32_t nA, int32_t nB, uint64_t guard, int t, double& Di,
+                                       double& Dj)
 {
     const double sha = -lds_end(offA + 16u * (uint32_t)sa);
     const double shb = -lds_end(offB + 16u * (uint32_t)sb);
     const int32_t n = nA + nB;
-    const int32_t S = (n + 63) / 64;
-    const int32_t d = (lane * n) / 64;
-    const int32_t steps = ((lane + 1) * n) / 64 - d;
+    const int32_t S = (n + L - 1) / L;
+    const int32_t d = (t * n) / L;
+    const int32_t steps = ((t + 1) * n) / L - d;
     // merge-path over A' = A[sa+1 .. sa+nA] and B' = B[sb+1 .. sb+nB]
     // (shifted, A first on ties): the largest a in [lo, hi] that is lo or
     // has A[sa + a] + sha <= B[sb + d + 1 - a] + shb, by FIRST's
@@ -2050,20 +2045,30 @@ __device__ inline void sweep_draw(uint32_t offA, uint32_t offB, int32_t sa, int3
     const uint32_t hiA = offA + 16u * (uint32_t)(sa + hi);
     const uint32_t sumAB = offA + offB + 16u * (uint32_t)(sa + sb + d + 1);
     for (int32_t step = step0; step > 0; step >>= 1) {
-        const uint32_t t = pa + 16u * (uint32_t)step;
-        const uint32_t pr = t < hiA ? t : hiA;
+        const uint32_t x = pa + 16u * (uint32_t)step;
+        const uint32_t pr = x < hiA ? x : hiA;
         const bool le = lds_end(pr) + sha <= lds_end(sumAB - pr) + shb;
-        pa = (le & (t <= hiA)) ? pr : pa;
+        pa = (le & (x <= hiA)) ? pr : pa;
     }
     // current kernels k = sa + a and l = sb + d - a: pa is A's slot k, B's
     // slot l sits at sumAB - 16 - pa
     const uint32_t pb = sumAB - 16u - pa;
     const double xa = lds_end(pa) + sha, yb = lds_end(pb) + shb;
-    double acc_i = 0.0, acc_j = 0.0;
+    Di = Dj = 0.0;
     __builtin_amdgcn_s_setprio(0);   // the walk yields to other waves' searches
-    walk_sampled(pa + 16u, pa + pb + 32u, sha, shb, xa > yb ? xa : yb, S, steps, guard, acc_i,
-                 acc_j);
+    walk_sampled(pa + 16u, pa + pb + 32u, sha, shb, xa > yb ? xa : yb, S, steps, guard, Di, Dj);
     __builtin_amdgcn_s_setprio(2);
+}
+
+// Delays of one draw in C_ij for both directions, swept by one wave from its
+// start kernels (sa, sb) and window counts (nA, nB).  The results are
+// wave-uniform.
+__device__ inline void sweep_draw(uint32_t offA, uint32_t offB, int32_t sa, int32_t sb,
+                                  int32_t nA, int32_t nB, uint64_t guard, int lane, double& Di,
+                                  double& Dj)
+{
+    double acc_i, acc_j;
+    walk_start_pair<64>(offA, offB, sa, sb, nA, nB, guard, lane, acc_i, acc_j);
     Di = read_lane(wave_sum_lane0(acc_i), 0);
     Dj = read_lane(wave_sum_lane0(acc_j), 0);
 }
@@ -2338,10 +2343,125 @@ __global__ __launch_bounds__(kAlignBlock) void sampled_reduce_kernel(SweepArgs g
 }
 
 // ---------------------------------------------------------------------------
+// CONFLICT_STARTS: unordered pair {i <= j}; every start pair (s_i, s_j) whose
+// two kernels interfere.  C_ji holds the same start pairs with the roles
+// swapped and the window of a start pair is the same for both directions, so
+// one walk yields Delta^c_ij and Delta^c_ji.  The per-alignment delays go to a
+// [n_kernels]^2 scratch (NaN outside the set); a second kernel reduces each
+// ordered pair's block.
+//
+// Work item b = (pair p, slice u) with p = b / slices; the item's waves take
+// chunks of `chunk` start pairs, stepping by slices * 4 chunks.  Each lane
+// sets up one start pair of a chunk (interference test, window counts); the
+// members go to a list of the wave, from which groups of L lanes take one
+// each: its merged boundaries split by merge-path over the L lanes and walked
+// as in the sampled sweep, whose layout and walk this kernel shares.  The
+// models are short here (q_i q_j <= RM_MAX_STARTS_PER_PAIR), so a start pair
+// has some ten boundaries per lane of a small group; with one wave each, a
+// start pair of two 50-kernel models was searches and a 64-lane sum around a
+// walk of one or two boundaries, for each direction on its own: ten models of
+// 50 kernels 165 us, 21 us now.
+// ---------------------------------------------------------------------------
+constexpr int kStartsWaves = kAlignBlock / 64;
+struct StartMember {
+    int32_t c, nA, nB;   // start pair s_i q_j + s_j, boundaries in its window
+};
+constexpr uint32_t kStartsListBase = 320 * sizeof(double);
+constexpr uint32_t kStartsRecBase = kStartsListBase + kStartsWaves * 64 * sizeof(StartMember);
+static_assert(kStartsRecBase % 16 == 0, "record slots");
+
+__host__ __device__ inline size_t starts_lds_bytes(int32_t pair_cap)
+{
+    return kStartsRecBase + (size_t)first_slots(pair_cap) * sizeof(Record);
+}
+
+// Sum over aligned groups of L lanes, on every lane of the group.
+template <int L>
+__device__ inline double group_sum(double v)
+{
+    static_assert(L == 8 || L == 16 || L == 64, "group");
+    v = v + dpp_take<kDppXor1>(v);
+    v = v + dpp_take<kDppXor2>(v);
+    if (L == 8) return v + dpp_take<kDppHalfMirror>(v);
+    v = v + dpp_take<kDppRor4>(v);
+    v = v + dpp_take<kDppRor8>(v);
+    if (L == 16) return v;
+    return ((read_lane(v, 0) + read_lane(v, 16)) + read_lane(v, 32)) + read_lane(v, 48);
+}
+
+template <int L>
+__global__ __launch_bounds__(kAlignBlock) void sweep_starts_kernel(SweepArgs g, int64_t n_pairs,
+                                                                   int32_t slices, int32_t chunk)
+{
+    extern __shared__ Record lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // 1/D at slot D + D/4; slots 0 and 255 hold 0, as in FIRST's sweep
+    *(LdsDouble)(size_t)(8u * (uint32_t)(tid + (tid >> 2))) =
+        (tid == 0 || tid == 255) ? 0.0 : 1.0 / (double)tid;
+    char* base = reinterpret_cast<char*>(lds);
+    StartMember* list = reinterpret_cast<StartMember*>(base + kStartsListBase) + 64 * wave;
+    const int64_t nk = g.n_kernels;
+    for (int64_t b = blockIdx.x; b < n_pairs * slices; b += gridDim.x) {
+        const int64_t p = b / slices;
+        const int32_t slice = (int32_t)(b - p * slices);
+        int32_t i, j;
+        row_pair_at(g.n_models, p, i, j);
+        const int32_t qa = g.q[i], qb = g.q[j];
+        const int64_t fa = g.first[i], fb = g.first[j];
+        if (!pair_fits(qa, qb, g.pair_cap) || (int64_t)qa * qb > g.starts_cap) continue;
+        const uint32_t offA = kStartsRecBase;
+        const uint32_t offB = kStartsRecBase + 16u * (uint32_t)(qa + 1 + kSentinels);
+        stage_model(reinterpret_cast<Record*>(base + offA), g.rec + fa, qa, kSentinels, g.bias, tid,
+                    kAlignBlock);
+        stage_model(reinterpret_cast<Record*>(base + offB), g.rec + fb, qb, kSentinels, 0, tid,
+                    kAlignBlock);
+        __syncthreads();
+
+        const int32_t total = qa * qb;
+        for (int32_t c0 = (slice * kStartsWaves + wave) * chunk; c0 < total;
+             c0 += slices * kStartsWaves * chunk) {
+            const int32_t c = c0 + lane;
+            const bool valid = lane < chunk && c < total;
+            const int32_t si = valid ? c / qb : 0, sj = valid ? c - si * qb : 0;
+            int32_t nA = 0, nB = 0;
+            const bool member = valid && start_window(offA, offB, qa, qb, si, sj, g.guard, nA, nB);
+            if (valid && !member) {
+                g.starts[(fa + si) * nk + (fb + sj)] = __builtin_nan("");
+                if (i != j) g.starts[(fb + sj) * nk + (fa + si)] = __builtin_nan("");
+            }
+            const uint64_t members = __ballot(member);
+            if (member) {
+                StartMember& m = list[__popcll(members & ((1ull << lane) - 1ull))];
+                m.c = c;
+                m.nA = nA;
+                m.nB = nB;
+            }
+            __builtin_amdgcn_wave_barrier();
+            const int32_t n_members = __popcll(members);
+            for (int32_t u = lane / L; u < n_members; u += 64 / L) {
+                const StartMember m = list[u];
+                const int32_t ti = m.c / qb, tj = m.c - ti * qb;
+                double Di, Dj;
+                walk_start_pair<L>(offA, offB, ti, tj, m.nA, m.nB, g.guard, lane & (L - 1), Di, Dj);
+                Di = group_sum<L>(Di);
+                Dj = group_sum<L>(Dj);
+                if ((lane & (L - 1)) == 0) {
+                    g.starts[(fa + ti) * nk + (fb + tj)] = Di;
+                    // (a self pair's other direction is a start pair of its own)
+                    if (i != j) g.starts[(fb + tj) * nk + (fa + ti)] = Dj;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();   // the list is rewritten by the next chunk
+        }
+        __syncthreads();   // staging is reused by the next item
+    }
+}
+
+// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 
-// The FIRST, OFFSETS and sampled sweep kernels address LDS by plain byte
+// The temporal sweep kernels address LDS by plain byte
 // addresses counted from 0.  That holds when they declare no static LDS: the
 // dynamic allocation then starts at address 0.  Checked once per process
 // from the kernels' attributes (a property of the code object).
@@ -2356,6 +2476,9 @@ hipError_t sweep_lds_from_zero(bool* ok)
                                  reinterpret_cast<const void*>(sweep_first_kernel<2, 2, 4>),
                                  reinterpret_cast<const void*>(sweep_first_kernel<2, 1, 8>),
                                  reinterpret_cast<const void*>(sweep_first_kernel<1, 1, 16>),
+                                 reinterpret_cast<const void*>(sweep_starts_kernel<8>),
+                                 reinterpret_cast<const void*>(sweep_starts_kernel<16>),
+                                 reinterpret_cast<const void*>(sweep_starts_kernel<64>),
                                  reinterpret_cast<const void*>(sweep_offsets_kernel),
                                  reinterpret_cast<const void*>(sweep_sampled_kernel)};
         v = 1;
@@ -2448,35 +2571,49 @@ hipError_t launch_sweep_offsets(const SweepArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_sweep_starts(const SweepArgs& a, hipStream_t s)
+template <int L>
+static hipError_t launch_starts_group(const SweepArgs& a, hipStream_t s)
 {
     const int64_t N = a.n_models;
-    const int64_t n_pairs = N * N;
-    const size_t lds = (size_t)pair_records(a.pair_cap) * sizeof(Record);
-    hipError_t e = allow_lds(sweep_starts_kernel, lds);
+    const int64_t n_pairs = N * (N + 1) / 2;
+    const size_t lds = starts_lds_bytes(a.pair_cap);
+    const hipError_t e = allow_lds(sweep_starts_kernel<L>, lds);
     if (e != hipSuccess) return e;
-    // enough slices per pair for about 1024 workgroups in all, but at least
-    // a few start pairs per wave (at most starts_cap of them per pair)
-    const int64_t per_wave = 4 * (kAlignBlock / 64);
+    // chunks of start pairs so small that a few thousand waves share them
+    // (down to one per group of lanes), for about 1024 workgroups
+    int32_t chunk = 64 / L;
+    while (chunk < 64 && n_pairs * a.starts_cap > (int64_t)4096 * chunk) chunk *= 2;
+    const int64_t per_item = (int64_t)kStartsWaves * chunk;
     int64_t slices = (1024 + n_pairs - 1) / n_pairs;
-    const int64_t most = (a.starts_cap + per_wave - 1) / per_wave;
+    const int64_t most = (a.starts_cap + per_item - 1) / per_item;
     if (slices > most) slices = most;
     if (slices < 1) slices = 1;
     const int64_t items = n_pairs * slices;
     constexpr int64_t kMax = int64_t(1) << 22;
-    hipLaunchKernelGGL(sweep_starts_kernel, dim3((unsigned)(items < kMax ? items : kMax)),
-                       dim3(kAlignBlock), lds, s, a, n_pairs, (int32_t)slices);
+    hipLaunchKernelGGL(sweep_starts_kernel<L>, dim3((unsigned)(items < kMax ? items : kMax)),
+                       dim3(kAlignBlock), lds, s, a, n_pairs, (int32_t)slices, chunk);
     return hipGetLastError();
+}
+
+// Lanes per start pair: about five boundaries each, a window holding about a
+// third of the pair's q_i + q_j boundaries on average (ten models of 50
+// kernels: 8 lanes 34.8 us a call, 16 lanes 41.3 us); a whole wave from some
+// hundred boundaries up.
+hipError_t launch_sweep_starts(const SweepArgs& a, hipStream_t s)
+{
+    if (a.pair_cap <= 256) return launch_starts_group<8>(a, s);
+    if (a.pair_cap <= 640) return launch_starts_group<16>(a, s);
+    return launch_starts_group<64>(a, s);
 }
 
 hipError_t launch_starts_reduce(const SweepArgs& a, hipStream_t s)
 {
     const int64_t N = a.n_models;
     const int64_t n_pairs = N * N;
-    const size_t lds = (size_t)a.starts_cap * sizeof(double);
-    hipError_t e = allow_lds(starts_reduce_kernel, lds);
+    const size_t lds = (size_t)a.starts_cap * sizeof(uint64_t);
+    const hipError_t e = allow_lds(starts_reduce_kernel, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(starts_reduce_kernel, dim3(pair_grid(n_pairs)), dim3(kAlignBlock), lds, s,
+    hipLaunchKernelGGL(starts_reduce_kernel, dim3(pair_grid(n_pairs)), dim3(kReduceBlock), lds, s,
                        a, n_pairs);
     return hipGetLastError();
 }
