@@ -5,63 +5,95 @@
 // the 16-byte records the sweep stages.
 //
 // The sum is taken strictly in sequence so every boundary is the same fp64
-// value the CPU oracle produces and boundary ties resolve identically.  One
-// 256-lane workgroup per model: wave 0 stages a chunk of durations into LDS
-// with coalesced loads and one of its lanes runs the dependent add chain
-// out of LDS, keeping only the running sum at the start of every block of
-// 16 values (the reads of the next block are issued before the adds of the
-// current one, so the chain is one add per value); meanwhile waves 1-3
-// compute the chunk's footprints on the other SIMDs.  Then 128 lanes each
-// redo one block's 16 adds from its starting sum -- the same additions in
-// the same order, so the same values -- and the chunk's boundaries are
-// written as 16-byte records.
+// value the CPU oracle produces and boundary ties resolve identically: a
+// chain of dependent adds, at least 2 ns each, which bounds this kernel.  One workgroup
+// of six waves per model; a chunk's durations are staged into LDS by all of
+// them, then its sub-chunks go through a pipeline with one barrier a step:
+//  * wave 0 runs the chain over sub-chunk s.  The 16 lanes of a row hold a
+//    block of 16 consecutive durations in one register, and v_fmac_f64 with
+//    a row_newbcast operand adds lane k's duration (times 1, so the sum rounds
+//    once, as an addition does) with no read or move between two adds; the
+//    blocks ahead are in flight.  Only the running sum at the start of every
+//    span of two blocks is kept.
+//  * waves 2-5 compute the footprints of sub-chunk s.
+//  * wave 1 finishes sub-chunk s - 1: 16 lanes redo one span's 32 adds each
+//    from its starting sum -- the same additions in the same order, so the
+//    same values -- and the wave writes whole 16-byte records.
+// 256 models of 2000 kernels: 21.4 us with one lane reading the durations out
+// of LDS value by value and the redo after the whole chain, 16.4 us now (1.9 us
+// until the durations are staged, 2 us a sub-chunk, 5 us of launch).
 #include "rm_common.h"
 
 namespace rm {
 
-constexpr int kPrepareChunk = 2048;
-constexpr int kPrepareThreads = 256;        // wave 0: sums; waves 1-3: footprints
+constexpr int kPrepareThreads = 384;
 constexpr int kBlk = 16;                    // values per block of the add chain
-constexpr int kBlocks = kPrepareChunk / kBlk;
-constexpr int kPerLane = kPrepareChunk / 64;
+constexpr int kSubBlks = 32;                // blocks per sub-chunk
+constexpr int kSub = kSubBlks * kBlk;
+constexpr int kSpanBlks = 2;                // blocks per redo span
+constexpr int kSpan = kSpanBlks * kBlk;
+constexpr int kSubSpans = kSubBlks / kSpanBlks;
+constexpr int kPrepareChunk = 2048;
+constexpr int kStageRegs = (kPrepareChunk + kPrepareThreads - 1) / kPrepareThreads;
+constexpr int kFootLanes = kPrepareThreads - 128;   // waves 2-5
+constexpr int kFootRegs = kSub / kFootLanes;
+static_assert(kPrepareChunk % kSub == 0 && kSub % kFootLanes == 0, "whole sub-chunks");
 
 // LDS slot of value t of a chunk: one spare slot after every 16 values, so
-// the lanes that redo consecutive blocks read different banks.
+// the lanes that redo consecutive spans read different banks.
 __device__ inline int slot_of(int t)
 {
     return t + (t >> 4);
 }
-constexpr int kBufSlots = kPrepareChunk + kBlocks;
+constexpr int kBufSlots = kPrepareChunk + kPrepareChunk / kBlk;
 
-// The add chain over the chunk's values in buf (zero padded to whole
-// blocks), from `run`; start[b] receives the running sum before block b.
-// The next block's values are read before the current block's adds, into
-// the other of two register blocks, so no values are copied between blocks.
-// A scheduling barrier after the reads keeps the scheduler from sinking them
-// to just before their own adds, where every other block would wait a full
-// LDS round trip.
-__device__ inline void load_block(const double* buf, int b, double (&v)[kBlk])
+// sum + x[0] + ... + x[15], one after the other, x[k] held by lane k of each
+// 16-lane row.  (The wait states cover x written by an instruction just
+// before: a DPP operand is read past the forwarding paths.)
+__device__ inline double add_block(double sum, double x)
 {
-#pragma unroll
-    for (int u = 0; u < kBlk; ++u) v[u] = buf[slot_of(b * kBlk + u)];
-    __builtin_amdgcn_sched_barrier(0);
+    const double one = 1.0;
+#define RM_ADD(K)                                                                          \
+    "v_fmac_f64_dpp %0, %1, %2 row_newbcast:" #K " row_mask:0xf bank_mask:0xf\n\t"
+    asm("s_nop 1\n\t" RM_ADD(0) RM_ADD(1) RM_ADD(2) RM_ADD(3) RM_ADD(4) RM_ADD(5) RM_ADD(6)
+            RM_ADD(7) RM_ADD(8) RM_ADD(9) RM_ADD(10) RM_ADD(11) RM_ADD(12) RM_ADD(13) RM_ADD(14)
+                RM_ADD(15)
+        : "+v"(sum)
+        : "v"(x), "v"(one));
+#undef RM_ADD
+    return sum;
 }
 
-__device__ inline double add_chain(const double* buf, double* start, int len, double run)
+// The chain over a sub-chunk's values in buf (zero past the end), from `run`;
+// start[kStartLane l + e] receives the running sum before redo span e, once
+// per lane l, so that no lane is masked off for it (lane 0's are used).  Blocks
+// go through eight at a time, the next eight read meanwhile: 2.6 ns an add
+// without the stores, 3.05 ns with one per block, 3.65 ns with one per block
+// by a single lane (one wave alone).
+constexpr int kStartLane = kSubSpans + 1;
+__device__ inline double add_chain(const double* buf, double* start, int len, int lane, double run)
 {
-    const int nb = (len + kBlk - 1) / kBlk;
-    double x[kBlk], y[kBlk];
-    load_block(buf, 0, x);
-    for (int b = 0; b < nb; b += 2) {
-        load_block(buf, b + 1 < nb ? b + 1 : b, y);
-        start[b] = run;
+    constexpr int kGroup = 8;
+    static_assert(kSubBlks % kGroup == 0, "whole groups");
+    const int nb = (len + kBlk - 1) / kBlk, l = lane & (kBlk - 1);
+    start += kStartLane * lane;
+    double x[kGroup];
 #pragma unroll
-        for (int u = 0; u < kBlk; ++u) run = run + x[u];
-        if (b + 1 >= nb) break;
-        load_block(buf, b + 2 < nb ? b + 2 : b + 1, x);
-        start[b + 1] = run;
+    for (int u = 0; u < kGroup; ++u) x[u] = buf[(kBlk + 1) * u + l];
+#pragma unroll 1
+    for (int b = 0; b < nb; b += kGroup) {
+        double y[kGroup];
+        const int ahead = b + kGroup < kSubBlks ? b + kGroup : b;
 #pragma unroll
-        for (int u = 0; u < kBlk; ++u) run = run + y[u];
+        for (int u = 0; u < kGroup; ++u) y[u] = buf[(kBlk + 1) * (ahead + u) + l];
+        __builtin_amdgcn_sched_barrier(0);   // these reads go out before the adds
+#pragma unroll
+        for (int u = 0; u < kGroup; ++u) {   // blocks past the end add zeros
+            if (u % kSpanBlks == 0) start[(b + u) / kSpanBlks] = run;
+            run = add_block(run, x[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kGroup; ++u) x[u] = y[u];
     }
     return run;
 }
@@ -115,8 +147,10 @@ __global__ __launch_bounds__(kPrepareThreads) void prepare_kernel(
     double* __restrict__ iso_time, ModelInfo* __restrict__ info, int32_t* status)
 {
     __shared__ double buf[kBufSlots];
-    __shared__ double start[kBlocks];
+    __shared__ uint64_t fps[kPrepareChunk];
+    __shared__ double start[2][kStartLane * 64];   // by sub-chunk parity
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (wave == 0) __builtin_amdgcn_s_setprio(3);   // the chain shares its SIMD
     for (int32_t m = blockIdx.x; m < n_models; m += gridDim.x) {
         int64_t first = offsets[m], last = offsets[m + 1];
         int32_t st = 0;
@@ -126,76 +160,99 @@ __global__ __launch_bounds__(kPrepareThreads) void prepare_kernel(
         }
         const int64_t q = last - first;
         if (q == 0 && tid == 0) st |= RM_ST_EMPTY_MODEL;
-        double run = 0.0;   // meaningful in lane 0 of wave 0 only
-        for (int64_t c = 0; c < q; c += kPrepareChunk) {
-            const int len = (int)((q - c) < kPrepareChunk ? (q - c) : kPrepareChunk);
-            if (wave == 0) {
-                // every load of the chunk in flight before any is used; the
-                // reads past len re-read the last duration and are zeroed
-                double v[kPerLane];
+        const auto length = [&](int64_t c) {
+            return (int)((q - c) < kPrepareChunk ? (q - c) : kPrepareChunk);
+        };
+        // a chunk's durations, every load in flight; past the end the last one
+        double next[kStageRegs];
+        const auto request = [&](int64_t c) {
+            const int len = length(c);
 #pragma unroll
-                for (int u = 0; u < kPerLane; ++u) {
-                    const int t = lane + 64 * u;
-                    v[u] = dur[first + c + (t < len ? t : len - 1)];
-                }
-#pragma unroll
-                for (int u = 0; u < kPerLane; ++u) {
-                    const int t = lane + 64 * u;
-                    if (t < len && (!(v[u] > 0.0) || !isfinite(v[u]))) st |= RM_ST_BAD_DURATION;
-                    buf[slot_of(t)] = t < len ? v[u] : 0.0;
-                }
+            for (int u = 0; u < kStageRegs; ++u) {
+                const int t = tid + kPrepareThreads * u;
+                next[u] = dur[first + c + (t < len ? t : len - 1)];
             }
+        };
+        double run = 0.0;   // meaningful in wave 0 only
+        if (q > 0) request(0);
+        for (int64_t c = 0; c < q; c += kPrepareChunk) {
+            const int len = length(c);
+#pragma unroll
+            for (int u = 0; u < kStageRegs; ++u) {
+                const int t = tid + kPrepareThreads * u;
+                if (t < len && (!(next[u] > 0.0) || !isfinite(next[u]))) st |= RM_ST_BAD_DURATION;
+                if (t < kPrepareChunk) buf[slot_of(t)] = t < len ? next[u] : 0.0;
+            }
+            if (c + kPrepareChunk < q) request(c + kPrepareChunk);
+            // launch shapes of waves 2-5's kernels of a sub-chunk
+            int32_t G[kFootRegs], T[kFootRegs], R[kFootRegs], M[kFootRegs];
+            const auto shapes = [&](int t0) {
+#pragma unroll
+                for (int u = 0; u < kFootRegs; ++u) {
+                    const int t = t0 + (tid - 128) + kFootLanes * u;
+                    const int64_t x = first + c + (t < len ? t : len - 1);
+                    G[u] = grid[x];
+                    T[u] = threads[x];
+                    R[u] = regs[x];
+                    M[u] = smem[x];
+                }
+            };
+            if (wave >= 2) shapes(0);
             __syncthreads();
-            if (wave == 0) {
-                if (lane == 0) run = add_chain(buf, start, len, run);
-            } else {
-                // footprints of the chunk, split over waves 1-3
-                const int w = wave - 1;
-                for (int t0 = 64 * 4 * w; t0 < len; t0 += 64 * 4 * 3) {
-                    int32_t G[4], T[4], R[4], M[4];
+            // steps of the pipeline: sub-chunks [0, len) and one step more
+#pragma unroll 1
+            for (int t0 = 0, par = 0; t0 < len + kSub; t0 += kSub, par ^= 1) {
+                if (wave == 0) {
+                    if (t0 < len)
+                        run = add_chain(buf + slot_of(t0), start[par],
+                                        len - t0 < kSub ? len - t0 : kSub, lane, run);
+                } else if (wave == 1) {
+                    const int f0 = t0 - kSub;   // the sub-chunk to finish
+                    if (f0 >= 0 && f0 < len) {
+                        if (lane < kSubSpans) {
+                            double r = start[par ^ 1][lane];
+                            double* v = buf + slot_of(f0 + lane * kSpan);
+#pragma unroll 1
+                            for (int w = 0; w < kSpanBlks; ++w, v += kBlk + 1) {
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int t = t0 + lane + 64 * u;
-                        const int64_t x = first + c + (t < len ? t : len - 1);
-                        G[u] = grid[x];
-                        T[u] = threads[x];
-                        R[u] = regs[x];
-                        M[u] = smem[x];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int t = t0 + lane + 64 * u;
-                        if (t < len) {
-                            const KernelOcc o = kernel_occupancy(d, pk, G[u], T[u], R[u], M[u]);
-                            st |= o.status;
-                            records[first + c + t].fp = o.fp;
-                            if (sim) {
-                                const int64_t x = first + c + t;
-                                const uint32_t wb = ((uint32_t)(T[u] > 0 ? T[u] : 1) +
-                                                     (uint32_t)d.warp - 1u) / (uint32_t)d.warp;
-                                const uint64_t rt = (uint64_t)(R[u] > 0 ? R[u] : 0) *
-                                                    (uint64_t)(T[u] > 0 ? T[u] : 0);
-                                const uint64_t mm = (uint64_t)(M[u] > 0 ? M[u] : 0);
-                                sim[x] = sim_record(d, form, dur[x], o.beta, wb, rt, mm);
+                                for (int u = 0; u < kBlk; ++u) {
+                                    r = r + v[u];
+                                    v[u] = r;
+                                }
                             }
                         }
-                    }
-                }
-            }
-            __syncthreads();
-            // each block's boundaries again from its starting sum, in place
-            if (tid < kBlocks && tid * kBlk < len) {
-                double r = start[tid];
+                        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int u = 0; u < kBlk; ++u) {
-                    r = r + buf[slot_of(tid * kBlk + u)];
-                    buf[slot_of(tid * kBlk + u)] = r;
+                        for (int u = 0; u < kSub / 64; ++u) {
+                            const int t = f0 + lane + 64 * u;
+                            Record r;
+                            r.end = buf[slot_of(t)];
+                            r.fp = fps[t];
+                            if (t < len) records[first + c + t] = r;
+                        }
+                    }
+                } else if (t0 < len) {
+                    KernelOcc o[kFootRegs];
+#pragma unroll
+                    for (int u = 0; u < kFootRegs; ++u) {
+                        const int t = t0 + (tid - 128) + kFootLanes * u;
+                        o[u] = kernel_occupancy(d, pk, G[u], T[u], R[u], M[u]);
+                        if (t < len) st |= o[u].status;
+                        fps[t] = o[u].fp;
+                        if (sim && t < len) {
+                            const uint32_t wb = ((uint32_t)(T[u] > 0 ? T[u] : 1) +
+                                                 (uint32_t)d.warp - 1u) / (uint32_t)d.warp;
+                            const uint64_t rt = (uint64_t)(R[u] > 0 ? R[u] : 0) *
+                                                (uint64_t)(T[u] > 0 ? T[u] : 0);
+                            const uint64_t mm = (uint64_t)(M[u] > 0 ? M[u] : 0);
+                            const int64_t x = first + c + t;
+                            sim[x] = sim_record(d, form, dur[x], o[u].beta, wb, rt, mm);
+                        }
+                    }
+                    if (t0 + kSub < len) shapes(t0 + kSub);
                 }
+                __syncthreads();
             }
-            __syncthreads();
-            for (int t = tid; t < len; t += kPrepareThreads)
-                records[first + c + t].end = buf[slot_of(t)];
-            __syncthreads();
         }
         if (tid == 0) {
             model_first[m] = first;
