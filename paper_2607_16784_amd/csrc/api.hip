@@ -298,6 +298,7 @@ int pair_matrix(const rm_device_desc* dev, int32_t n_models, const int64_t* kern
     a.bias = pk.bias;
     a.guard = pk.guard;
     const int64_t hint = opts->max_kernels_per_model;
+    a.max_kernels = hint;
     a.pair_cap = RM_MAX_PAIR_KERNELS;
     if (hint > 0 && 2 * hint < RM_MAX_PAIR_KERNELS) a.pair_cap = (int32_t)(2 * hint);
     a.starts_cap = RM_MAX_STARTS_PER_PAIR;

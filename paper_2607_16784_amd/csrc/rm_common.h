@@ -185,6 +185,7 @@ struct SweepArgs {
     int32_t n_models;
     int64_t n_kernels;
     uint64_t bias, guard;
+    int64_t max_kernels;     // the caller's bound on a model's kernels (0: none)
     int32_t pair_cap;        // max q_i + q_j a pair may have to be staged
     int32_t starts_cap;      // max q_i * q_j for CONFLICT_STARTS
     int32_t num_offsets;     // K (OFFSETS, SAMPLED_STARTS)

@@ -2534,11 +2534,34 @@ static hipError_t launch_first_shape(const SweepArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// The tile shape for models of at most half the pair cap, whose rows and
+// columns then all fit the LDS.  The cap stops at 2048 kernels a model; with
+// longer ones some columns of a 2 x 2 item do not fit beside its rows and
+// their pairs are swept from memory, several times slower.  Whether that is
+// the common case follows from a typical long model, halfway between the mean
+// and the longest: one pair per item at a time then stages every model (48
+// models of 1000-4000 kernels 102.6 -> 56.7 us a call, 128 432 -> 233 us), or
+// three models per item where three of the longest fit (48 of 2600 129 -> 43
+// us, 48 of 100-3000 61 -> 43 us).  With a few long models among short ones
+// the 2 x 2 item is the better one (200 models, a tenth of them 4000 kernels
+// long, the others 200-1000: 199 us against 406 us).
+static TileShape first_shape(const SweepArgs& a)
+{
+    const TileShape usual = tile_shape((a.pair_cap + 1) / 2);
+    if (a.pair_cap < RM_MAX_PAIR_KERNELS) return usual;
+    const int64_t mean = a.n_kernels / a.n_models;
+    const int64_t longest = a.max_kernels;          // 0: unknown
+    const int64_t typical = longest > mean ? (longest + mean) / 2 : mean;
+    const int64_t fits3 = kTileSlots / 3 - (tile_model_slots(0));
+    const int64_t fits4 = kTileSlots / 4 - (tile_model_slots(0));
+    if (longest > fits4 && longest <= fits3 && typical > 2100) return tile_shape((int32_t)fits3);
+    if (typical > fits4) return tile_shape(kTileSlots / 2);
+    return usual;
+}
+
 hipError_t launch_sweep_first(const SweepArgs& a, hipStream_t s)
 {
-    // the tile shape for models of at most half the pair cap (longer ones
-    // are swept from memory)
-    const TileShape sh = tile_shape((a.pair_cap + 1) / 2);
+    const TileShape sh = first_shape(a);
     if (sh.R == 4 && sh.C == 4) return launch_first_shape<4, 4, 1>(a, s);
     if (sh.R == 4 && sh.C == 2) return launch_first_shape<4, 2, 2>(a, s);
     if (sh.R == 3 && sh.C == 2) return launch_first_shape<3, 2, 2>(a, s);
