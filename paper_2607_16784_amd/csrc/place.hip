@@ -410,10 +410,12 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
 // ---------------------------------------------------------------------------
 // placement, one lane per resident slot
 //
-// For up to 64 resident slots (n_devices * capacity <= 64, capacity a power
-// of two) one wave runs the whole event loop with lane g*C + p holding slot
-// p of device g: its model, the arrival that placed it, and its aggregated
-// time over the device's residents, all in registers.  An arrival is one
+// For up to 64 resident slots (n_devices * C <= 64, C the power of two from the
+// capacity up) one wave runs the whole event loop with lane g*C + p holding
+// slot p of device g: its model, the arrival that placed it, and its aggregated
+// time over the device's residents, all in registers; slots from the capacity
+// on stay empty and add +0 to every sum.  (15 arrivals onto 10 devices of 3:
+// 33 us in the workgroup's rounds below, 11 us so.)  An arrival is one
 // round without barriers: every slot lane multiplies in its two delay
 // entries, the ordered sums over each device's slots come from DPP quad
 // broadcasts (C <= 4) or C-1 DPP shifts inside 16-lane rows (a device's C
@@ -478,8 +480,8 @@ __device__ inline int32_t wave_argmin_lane(double key, double& kmin)
 template <int C, bool ISO>
 __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
     int32_t N, const double* __restrict__ delay, const double* __restrict__ iso_g,
-    const int32_t* __restrict__ q_g, int32_t G, int32_t* resident, int32_t* resident_count,
-    int32_t E, const int32_t* __restrict__ events_g, double lambda, int32_t drop_mode,
+    const int32_t* __restrict__ q_g, int32_t G, int32_t cap, int32_t* resident,
+    int32_t* resident_count, int32_t E, const int32_t* __restrict__ events_g, double lambda, int32_t drop_mode,
     int32_t* __restrict__ placed_device, double* __restrict__ placed_mu, int32_t* status)
 {
     // per-model times, their reciprocals, reciprocals of the kernel counts,
@@ -541,9 +543,10 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
 
     // ---- initial state
     int32_t cnt = slot ? resident_count[g] : 0;
-    bool bad = slot && (cnt < 0 || cnt > C);
-    cnt = (cnt < 0 || cnt > C) ? 0 : cnt;
-    int32_t r = slot ? resident[g * C + p] : -1;
+    bool bad = slot && (cnt < 0 || cnt > cap);
+    cnt = (cnt < 0 || cnt > cap) ? 0 : cnt;
+    int32_t r = slot && p < cap ? resident[g * cap + p] : -1;
+    const int32_t most = G * cap;   // slots in all
     bad = bad || (slot && p < cnt && (r < 0 || r >= N));
     if (__ballot(bad)) {
         if (lane == 0 && status) atomicOr(status, RM_ST_BAD_MODEL_ID);
@@ -556,7 +559,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
     int32_t rev = -1, rq = 0;
     double rTi = 0.0, rrT = 0.0, rrq = 0.0, racc = 0.0;
     // residents over all devices (uniform): some device has a free slot
-    // while it is below G * C
+    // while it is below `most`
     int32_t n_res = (slot && p == 0) ? cnt : 0;
     for (int o = 32; o > 0; o >>= 1) n_res += __shfl_xor(n_res, o, 64);
     n_res = __builtin_amdgcn_readfirstlane(n_res);
@@ -639,7 +642,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
         // without branches on per-lane data.  The round reads the next
         // event, and the rare events below leave this loop, so the state
         // carried from round to round is not merged with theirs.
-        while (v >= 0 && v < N && n_res < G * C) {
+        while (v >= 0 && v < N && n_res < most) {
             int32_t v_next;
             const bool occ = slot && p < cnt;
             int32_t qv;
@@ -731,7 +734,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
             }
             // the device's mean drop with the arrival, on its last slot lane
             const double mbar = div_by_recip(z + drop(x, Tv, yTv), (double)(cnt + 1), rcnt);
-            const double key = (slot && p == C - 1 && cnt < C && mbar < inf) ? mbar : inf;
+            const double key = (slot && p == C - 1 && cnt < cap && mbar < inf) ? mbar : inf;
             // before the decision, so that it fills the argmin's latency: the
             // arrival's aggregated time on every lane of its device (from the
             // device's last slot lane) and the overlap scales of the entries
@@ -852,7 +855,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
     flush();
 
     if (slot) {
-        resident[g * C + p] = p < cnt ? r : -1;
+        if (p < cap) resident[g * cap + p] = p < cnt ? r : -1;
         if (p == 0) resident_count[g] = cnt;
     }
 }
@@ -868,7 +871,9 @@ hipError_t launch_place(int32_t n_models, const double* delay, const double* iso
     if (n_models <= kLdsModels) lds += (size_t)n_models * (2 * sizeof(double) + sizeof(int32_t));
     if (n_events <= kLdsEvents) lds += (size_t)n_events * sizeof(int32_t);
     lds = (lds + 15) / 16 * 16;
-    if (n_devices * capacity <= 64 && n_models <= kLdsModels && n_events <= kLdsEvents) {
+    int32_t slots = 1;   // a device's lanes
+    while (slots < capacity) slots <<= 1;
+    if (n_devices * slots <= 64 && n_models <= kLdsModels && n_events <= kLdsEvents) {
         // the wave kernel also keeps 1 / q per model
         const size_t wave_lds = lds + (size_t)n_models * sizeof(double);
         auto go = [&](auto kernel) {
@@ -879,12 +884,12 @@ hipError_t launch_place(int32_t n_models, const double* delay, const double* iso
                 if (e != hipSuccess) return e;
             }
             hipLaunchKernelGGL(kernel, dim3(1), dim3(kPlaceThreads), wave_lds, s, n_models, delay, iso,
-                               q, n_devices, resident, resident_count, n_events, events, lambda,
-                               drop_mode, placed_device, placed_mu_mean, status);
+                               q, n_devices, capacity, resident, resident_count, n_events, events,
+                               lambda, drop_mode, placed_device, placed_mu_mean, status);
             return hipGetLastError();
         };
         const bool iso = drop_mode == RM_DROP_ISO;
-        switch (capacity) {
+        switch (slots) {
         case 1: return iso ? go(place_wave_kernel<1, true>) : go(place_wave_kernel<1, false>);
         case 2: return iso ? go(place_wave_kernel<2, true>) : go(place_wave_kernel<2, false>);
         case 4: return iso ? go(place_wave_kernel<4, true>) : go(place_wave_kernel<4, false>);
