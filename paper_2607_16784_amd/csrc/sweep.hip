@@ -1265,9 +1265,9 @@ __device__ inline double block_reduce_values(double* buf, int32_t n, int32_t red
 // footprint that ends at tau.  The merged boundary list is then A's ends
 // P_i[1..q_i] and B's shifted ends tau + P_j[0..q_j]; stretches before tau
 // (B not started) and after the first model ends (a sentinel) conflict with
-// nothing, so the window of Alg. 1 needs no bounds.  Each wave takes one
-// alignment at a time: a uniform search finds the A boundaries <= tau, the
-// lanes split the rest with merge-path and walk it branch-free.  Persistent
+// nothing, so the window of Alg. 1 needs no bounds.  Each group of L lanes
+// takes one alignment at a time: its lanes split the boundaries past tau with
+// merge-path and walk them branch-free.  Persistent
 // workgroups take contiguous runs of ordered pairs, so model i (row-major)
 // stays staged while j changes.
 // ---------------------------------------------------------------------------
@@ -1369,6 +1369,20 @@ __device__ inline void walk_offset(uint32_t pa, uint32_t sum, double tau, double
     if (t < S) offset_step<16>(pa, sum, guard, tau, lo, ra, rb, na, nb, acc);
 }
 
+// Sum over aligned groups of L lanes, on every lane of the group.
+template <int L>
+__device__ inline double group_sum(double v)
+{
+    static_assert(L == 8 || L == 16 || L == 64, "group");
+    v = v + dpp_take<kDppXor1>(v);
+    v = v + dpp_take<kDppXor2>(v);
+    if (L == 8) return v + dpp_take<kDppHalfMirror>(v);
+    v = v + dpp_take<kDppRor4>(v);
+    v = v + dpp_take<kDppRor8>(v);
+    if (L == 16) return v;
+    return ((read_lane(v, 0) + read_lane(v, 16)) + read_lane(v, 32)) + read_lane(v, 48);
+}
+
 // Largest of n >= 1 values in LDS (finite or NaN-free), by wave 0; the
 // result is returned to every thread through LDS.
 __device__ inline double block_max_values(const double* vals, int32_t n, double* slot)
@@ -1395,6 +1409,7 @@ __device__ inline double block_max_values(const double* vals, int32_t n, double*
     return *slot;
 }
 
+template <int L>
 __global__ __launch_bounds__(kAlignBlock) void sweep_offsets_kernel(
     SweepArgs g, int64_t n_pairs, const ModelInfo* __restrict__ info, int32_t n_sent)
 {
@@ -1521,13 +1536,21 @@ __global__ __launch_bounds__(kAlignBlock) void sweep_offsets_kernel(
         // the lane's split of the wave's previous offset of this pair
         int32_t aPrev = 0, a0Prev = 0;
         bool havePrev = false;
-        for (int32_t r = wave; r < K; r += kAlignBlock / 64) {
+        constexpr int kGroups = kAlignBlock / L;
+        const int t = lane & (L - 1);
+        for (int32_t r0 = 0; r0 < K; r0 += kGroups) {
+            // (a group past the last offset walks nothing)
+            const int32_t r1 = r0 + tid / L, r = r1 < K ? r1 : K - 1;
+            if (L == 64 && r1 >= K) break;
             const double tau = Ti * (double)r / (double)K;
-            const int32_t a0 = __builtin_amdgcn_readfirstlane(s_a0[r]);
-            const int32_t d_end = __builtin_amdgcn_readfirstlane(s_dend[r]);
-            const int32_t rem = d_end - a0;
-            const int32_t S = (rem + 63) / 64;
-            const int32_t d = a0 + (lane * S < rem ? lane * S : rem);
+            int32_t a0 = s_a0[r], d_end = s_dend[r];
+            if (L == 64) {
+                a0 = __builtin_amdgcn_readfirstlane(a0);
+                d_end = __builtin_amdgcn_readfirstlane(d_end);
+            }
+            const int32_t rem = r1 < K ? d_end - a0 : 0;
+            const int32_t S = (rem + L - 1) / L;
+            const int32_t d = a0 + (t * S < rem ? t * S : rem);
             // merge-path over A' = A[1..qa] and B' = B[0..qb] + tau (A first on
             // ties): the largest a in [lo, hi] that is lo or has
             // A[a] <= B[d - a] + tau, by power-of-two probes from lo (the same
@@ -1539,18 +1562,20 @@ __global__ __launch_bounds__(kAlignBlock) void sweep_offsets_kernel(
                 uint32_t p_ = offA + 16u * (uint32_t)los;
                 const uint32_t hiA = offA + 16u * (uint32_t)his;
                 for (int32_t step = st; step > 0; step >>= 1) {
-                    const uint32_t t = p_ + 16u * (uint32_t)step;
-                    const uint32_t pr = t < hiA ? t : hiA;
+                    const uint32_t x = p_ + 16u * (uint32_t)step;
+                    const uint32_t pr = x < hiA ? x : hiA;
                     const bool le = lds_end(pr) <= lds_end(sumAB - pr) + tau;
-                    p_ = (le & (t <= hiA)) ? pr : p_;
+                    p_ = (le & (x <= hiA)) ? pr : p_;
                 }
                 return p_;
             };
-            // As in FIRST's split: a window of 2 kSplitWindow slots around
-            // the lane's split of the wave's previous offset, moved by the
-            // change of a0, searched first; two probes issued with its first
-            // check that the answer lies inside, else the whole range is
-            // searched.  The same answer either way.
+            // As in FIRST's split, for whole waves: a window of 2 kSplitWindow
+            // slots around the lane's split of the wave's previous offset,
+            // moved by the change of a0, searched first; two probes issued with
+            // its first check that the answer lies inside, else the whole
+            // range is searched.  The same answer either way.  (A smaller
+            // group's offsets lie further apart and its split serves more
+            // boundaries: searching the whole range at once is 1% faster.)
             uint32_t pa = 0;
             bool inWindow = false;
             if (havePrev) {
@@ -1567,7 +1592,7 @@ __global__ __launch_bounds__(kAlignBlock) void sweep_offsets_kernel(
             if (!inWindow) pa = search(lo, hi, step0);
             aPrev = (int32_t)((pa - offA) >> 4);
             a0Prev = a0;
-            havePrev = true;
+            havePrev = L == 64;
             const int32_t a = (int32_t)((pa - offA) >> 4), b = d - a;
             // start of the stretch after the d-th merged boundary
             const double xa = lds_end(pa);
@@ -1575,10 +1600,18 @@ __global__ __launch_bounds__(kAlignBlock) void sweep_offsets_kernel(
             double acc = 0.0;
             const uint32_t pb = offB + 16u * (uint32_t)b;   // B's current record, B[b]
             __builtin_amdgcn_s_setprio(0);
-            walk_offset(pa + 16u, pa + 16u + pb, tau, xa > yb ? xa : yb, S, g.guard, acc);
+            // (whole waves walk S steps past the end onto sentinels; a smaller
+            // group's lanes stop at the end)
+            const int32_t left = rem - t * S;
+            const int32_t steps = L == 64 ? S : left < 0 ? 0 : left < S ? left : S;
+            walk_offset(pa + 16u, pa + 16u + pb, tau, xa > yb ? xa : yb, steps, g.guard, acc);
             __builtin_amdgcn_s_setprio(2);
-            acc = wave_sum_lane0(acc);
-            if (lane == 0) {
+            if (L == 64) {
+                acc = wave_sum_lane0(acc);
+            } else {
+                acc = group_sum<L>(acc);
+            }
+            if (t == 0 && r1 < K) {
                 vals[r] = acc;
                 if (g.per_alignment) g.per_alignment[p * K + r] = acc;
             }
@@ -2375,20 +2408,6 @@ __host__ __device__ inline size_t starts_lds_bytes(int32_t pair_cap)
     return kStartsRecBase + (size_t)first_slots(pair_cap) * sizeof(Record);
 }
 
-// Sum over aligned groups of L lanes, on every lane of the group.
-template <int L>
-__device__ inline double group_sum(double v)
-{
-    static_assert(L == 8 || L == 16 || L == 64, "group");
-    v = v + dpp_take<kDppXor1>(v);
-    v = v + dpp_take<kDppXor2>(v);
-    if (L == 8) return v + dpp_take<kDppHalfMirror>(v);
-    v = v + dpp_take<kDppRor4>(v);
-    v = v + dpp_take<kDppRor8>(v);
-    if (L == 16) return v;
-    return ((read_lane(v, 0) + read_lane(v, 16)) + read_lane(v, 32)) + read_lane(v, 48);
-}
-
 template <int L>
 __global__ __launch_bounds__(kAlignBlock) void sweep_starts_kernel(SweepArgs g, int64_t n_pairs,
                                                                    int32_t slices, int32_t chunk)
@@ -2479,7 +2498,9 @@ hipError_t sweep_lds_from_zero(bool* ok)
                                  reinterpret_cast<const void*>(sweep_starts_kernel<8>),
                                  reinterpret_cast<const void*>(sweep_starts_kernel<16>),
                                  reinterpret_cast<const void*>(sweep_starts_kernel<64>),
-                                 reinterpret_cast<const void*>(sweep_offsets_kernel),
+                                 reinterpret_cast<const void*>(sweep_offsets_kernel<8>),
+                                 reinterpret_cast<const void*>(sweep_offsets_kernel<16>),
+                                 reinterpret_cast<const void*>(sweep_offsets_kernel<64>),
                                  reinterpret_cast<const void*>(sweep_sampled_kernel)};
         v = 1;
         for (const void* k : kernels) {
@@ -2570,28 +2591,40 @@ hipError_t launch_sweep_first(const SweepArgs& a, hipStream_t s)
     return launch_first_shape<1, 1, 16>(a, s);
 }
 
-hipError_t launch_sweep_offsets(const SweepArgs& a, hipStream_t s)
+template <int L>
+static hipError_t launch_offsets_group(const SweepArgs& a, hipStream_t s)
 {
     const int64_t N = a.n_models;
     const int64_t n_pairs = N * N;
     const int32_t n_sent = offsets_sentinels(a.pair_cap);
     const size_t lds = offsets_lds_bytes(a.pair_cap, n_sent,
                                          (int32_t)next_pow2((unsigned)a.num_offsets));
-    hipError_t e = allow_lds(sweep_offsets_kernel, lds);
+    hipError_t e = allow_lds(sweep_offsets_kernel<L>, lds);
     if (e != hipSuccess) return e;
     int dev = 0, cus = 0, per_cu = 0;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
         return e;
-    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sweep_offsets_kernel,
+    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sweep_offsets_kernel<L>,
                                                           kAlignBlock, lds)) != hipSuccess)
         return e;
     if (per_cu < 1) per_cu = 1;
     int64_t wgs = (int64_t)cus * per_cu;
     if (wgs > n_pairs) wgs = n_pairs;
-    hipLaunchKernelGGL(sweep_offsets_kernel, dim3((unsigned)wgs), dim3(kAlignBlock), lds, s, a,
+    hipLaunchKernelGGL(sweep_offsets_kernel<L>, dim3((unsigned)wgs), dim3(kAlignBlock), lds, s, a,
                        n_pairs, a.info, n_sent);
     return hipGetLastError();
+}
+
+// Lanes per offset: as few as leave every group of the workgroup an offset.
+// A wave's split and sum then serve several offsets of nearly equal windows at
+// once: edge OFFSETS(64) 1.23 ms with 64 lanes an offset, 1.00 ms with 16,
+// 0.966 ms with 8, 1.02 ms with 4 (whose lanes wait longer for the longest).
+hipError_t launch_sweep_offsets(const SweepArgs& a, hipStream_t s)
+{
+    if (a.num_offsets >= 32) return launch_offsets_group<8>(a, s);
+    if (a.num_offsets >= 16) return launch_offsets_group<16>(a, s);
+    return launch_offsets_group<64>(a, s);
 }
 
 template <int L>
