@@ -462,19 +462,173 @@ __device__ inline double min_key(double x, double y)
 }
 
 template <int C>
-__device__ inline int32_t wave_argmin_lane(double key, double& kmin)
+__device__ inline double row_min(double m)
 {
-    double m = key;
     if (C < 2) m = min_key(m, dpp_take<kDppXor1>(m));
     if (C < 4) m = min_key(m, dpp_take<kDppXor2>(m));
     if (C < 8) m = min_key(m, dpp_take<kDppRor4>(m));
-    m = min_key(m, dpp_take<kDppRor8>(m));
+    return min_key(m, dpp_take<kDppRor8>(m));
+}
+
+template <int C>
+__device__ inline int32_t wave_argmin_lane(double key, double& kmin)
+{
+    double m = row_min<C>(key);
     m = min_key(m, dpp_take<kDppRowBcast15>(m));
     m = min_key(m, dpp_take<kDppRowBcast31>(m));
     const double k = read_lane(m, 63);
     kmin = k;
     const unsigned long long hit = __ballot(key == k && k < __builtin_inf());
     return hit ? __ffsll((long long)hit) - 1 : -1;
+}
+
+// Ordered sums over each device's slots, needed on its last slot lane:
+// x = T_v + d2_0 + d2_1 + ..., z = drop_0 + drop_1 + ... (empty slots add +0).
+// With C <= 4 a device's slots form one DPP quad (or half of one), so its last
+// lane adds its slots' values in slot order from quad broadcasts; with C = 8
+// the sums run as C-1 row shifts.
+template <int C>
+__device__ inline void slot_sums(int32_t p, double& x, double& z)
+{
+    if (C == 4) {
+        x = ((dpp_take<kDppQuad0>(x) + dpp_take<kDppQuad1>(x)) + dpp_take<kDppQuad2>(x)) + x;
+        z = ((dpp_take<kDppQuad0>(z) + dpp_take<kDppQuad1>(z)) + dpp_take<kDppQuad2>(z)) + z;
+    } else if (C == 2) {
+        x = dpp_take<kDppPair0>(x) + x;
+        z = dpp_take<kDppPair0>(z) + z;
+    } else {
+#pragma unroll
+        for (int s2 = 1; s2 < C; ++s2) {
+            const double xs = dpp_take<kDppShr1>(x);   // lane p - 1 (p >= 1 reads it)
+            const double zs = dpp_take<kDppShr1>(z);
+            x = (p == s2) ? xs + x : x;
+            z = (p == s2) ? zs + z : z;
+        }
+    }
+}
+
+// Eq. (5) through the model's reciprocal (computed, then selected, so no lane
+// branches), or the drop step of Alg. 1.
+template <bool ISO>
+__device__ inline double slot_drop(double T_agg, double T, double yT)
+{
+    if (ISO) {
+        const double r = div_by_recip(T_agg - T, T, yT);
+        return T > 0.0 ? r : 0.0;
+    }
+    return drop_of(T_agg, T, RM_DROP_ADJUSTED);
+}
+
+// A run of arrivals that lambda defers leaves the state as it is, so the
+// arrivals after it can be looked at side by side: after kScanAfter deferrals
+// in a row wave 0 puts the slots into LDS and all sixteen waves evaluate the
+// next events, 64 to 256 at a time, up to the first that is placed or is no
+// arrival.  1000 arrivals of which lambda defers most took 0.56 ms one round
+// each; now 16 devices of 3 take 78 us and 4 devices of 3 take 31 us (place_kernel:
+// 87 and 39 us).  Instruction issue of the sixteen waves bounds it, about 3.5 us
+// for 64 events on 64 lanes.  A run that ends early costs one such batch, so
+// after a scan that found fewer than kScanAfter deferrals the next one waits
+// for twice as many (departures stream of 1000 arrivals: 1.105 ms without
+// scans, 1.115 ms with).
+constexpr int kScanAfter = 16;
+constexpr int kScanMost = 256;
+
+struct ScanState {
+    double acc[64], T[64], yT[64], yq[64];
+    int32_t r[64], cnt[64], q[64];
+    double mu[2][256];  // smallest mean of an event, by chunk modulo 2
+    int32_t stop[3];    // first event that ends the run, by chunk modulo 3
+    int32_t e;          // first event; -1: no more scans
+};
+
+// By every wave of the workgroup (the slots in sc): the first event from sc.e
+// on that is not an arrival deferred by lambda; the events before it get their
+// outputs.
+template <int C, bool ISO>
+__device__ inline int32_t scan_deferred(ScanState& sc, int32_t N, const double* __restrict__ delay,
+                                        const double* iso, const double* rT, const double* rQ,
+                                        const int32_t* q, const double* s_rn, int32_t G,
+                                        int32_t cap, int32_t E, const int32_t* events,
+                                        double lambda, int32_t* __restrict__ placed_device,
+                                        double* __restrict__ placed_mu)
+{
+    constexpr int kPer = 4;
+    // a lane's events that are evaluated side by side; with C = 8 the row
+    // shifts of more than one would not fit the registers beside the slots
+    constexpr int kSide = C == 8 ? 1 : kPer;
+    // the slots of up to 32 or 16 lanes are held twice or four times, each
+    // copy for an event of its own
+    const int32_t bits = G * C <= 16 ? 4 : (G * C <= 32 ? 5 : 6), width = 1 << bits;
+    const int32_t lane = threadIdx.x & 63, sl = lane & (width - 1);
+    const int32_t chunk = (kPer * kPlaceThreads) >> bits;   // 64, 128 or 256 events
+    const int32_t g = sl / C, p = sl % C;
+    const bool slot = g < G;
+    const int32_t cnt = sc.cnt[sl], rq = sc.q[sl];
+    const bool occ = slot && p < cnt;
+    const uint32_t rr = occ ? (uint32_t)sc.r[sl] : 0u;
+    const double racc = sc.acc[sl], rTi = sc.T[sl], rrT = sc.yT[sl], rrq = sc.yq[sl];
+    const double rcnt = s_rn[cnt + 1];
+    const double inf = __builtin_inf();
+    int32_t stop = E;
+    int32_t k = 0;
+    for (int32_t b = __builtin_amdgcn_readfirstlane(sc.e);; b += chunk, ++k) {
+        for (int h = 0; h < kPer; h += kSide) {
+            // this wave's events, their entries all in flight before any is used
+            double d1[kSide], d2[kSide], least[kSide];
+            int32_t x[kSide], v[kSide];
+            bool arrival[kSide];
+#pragma unroll
+            for (int u = 0; u < kSide; ++u) {
+                x[u] = ((h + u) * kPlaceThreads + (int32_t)threadIdx.x) >> bits;   // in the chunk
+                const int32_t ev = b + x[u] < E ? events[b + x[u]] : -1;
+                arrival[u] = ev >= 0 && ev < N;
+                v[u] = arrival[u] ? ev : 0;
+                d1[u] = delay[__umul24(rr, (uint32_t)N) + (uint32_t)v[u]];
+                d2[u] = delay[__umul24((uint32_t)v[u], (uint32_t)N) + rr];
+            }
+#pragma unroll
+            for (int u = 0; u < kSide; ++u) {
+                // the round of the event loop, without its commit; of the two
+                // overlap scales the one of the longer model is not 1
+                const double Tv = iso[v[u]], yTv = rT[v[u]], yqv = rQ[v[u]];
+                const int32_t qv = q[v[u]];
+                const bool longer = rq > qv;
+                const double ratio = overlap_scale_r(longer ? rq : qv, longer ? qv : rq,
+                                                     longer ? yqv : rrq);
+                const double e1 = occ ? (longer ? ratio : 1.0) * d1[u] : 0.0;
+                const double e2 = occ ? (longer ? 1.0 : ratio) * d2[u] : 0.0;
+                double y = (p == 0) ? Tv + e2 : e2;
+                double z = occ ? slot_drop<ISO>(racc + e1, rTi, rrT) : 0.0;
+                slot_sums<C>(p, y, z);
+                const double mbar = div_by_recip(z + slot_drop<ISO>(y, Tv, yTv), (double)(cnt + 1), rcnt);
+                least[u] = (slot && p == C - 1 && cnt < cap && mbar < inf) ? mbar : inf;
+                // the minimum of the event's lanes on the last of them
+                least[u] = row_min<C>(least[u]);
+                if (width > 16) least[u] = min_key(least[u], dpp_take<kDppRowBcast15>(least[u]));
+                if (width > 32) least[u] = min_key(least[u], dpp_take<kDppRowBcast31>(least[u]));
+            }
+            if (sl == width - 1) {
+#pragma unroll
+                for (int u = kSide - 1; u >= 0; --u) {
+                    sc.mu[k & 1][x[u]] = least[u];
+                    if (!arrival[u] || (least[u] < inf && least[u] < lambda))
+                        atomicMin(&sc.stop[k % 3], b + x[u]);
+                }
+            }
+        }
+        if (threadIdx.x == 0) sc.stop[(k + 1) % 3] = 0x7fffffff;   // last read two chunks ago
+        __syncthreads();
+        stop = __builtin_amdgcn_readfirstlane(sc.stop[k % 3]);
+        const bool last = stop < b + chunk;
+        const int32_t n = last ? stop - b : chunk;
+        if ((int32_t)threadIdx.x < n) {
+            placed_device[b + threadIdx.x] = -1;
+            placed_mu[b + threadIdx.x] = sc.mu[k & 1][threadIdx.x];
+        }
+        if (last) break;
+    }
+    __syncthreads();   // sc is written again by the next scan
+    return stop;
 }
 
 template <int C, bool ISO>
@@ -494,6 +648,8 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
     int32_t* q = reinterpret_cast<int32_t*>(rQ + N);
     int32_t* events = q + N;
     __shared__ double s_rn[kCapMax + 2];   // RN(1/k), k = 0..capacity+1
+    __shared__ ScanState sc;
+    const bool scans = E > kScanAfter;
     if (threadIdx.x < kCapMax + 2) s_rn[threadIdx.x] = 1.0 / (double)threadIdx.x;
     for (int32_t m = threadIdx.x; m < N; m += kPlaceThreads) {
         const double T = iso_g[m];
@@ -533,8 +689,20 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
         if (__ballot(bad != 0) && (threadIdx.x & 63) == 0 && status)
             atomicOr(status, RM_ST_BAD_DELAY);
         check_delay(delay, N, status, 64, kPlaceThreads - 64);
+        while (scans) {
+            __syncthreads();   // wave 0 has set the next scan up, or is done
+            if (__builtin_amdgcn_readfirstlane(sc.e) < 0) break;
+            scan_deferred<C, ISO>(sc, N, delay, iso, rT, rQ, q, s_rn, G, cap, E, events, lambda,
+                                  placed_device, placed_mu);
+        }
         return;
     }
+    // lets the other waves go
+    auto dismiss = [&]() {
+        if (!scans) return;
+        if (threadIdx.x == 0) sc.e = -1;
+        __syncthreads();
+    };
 
     const int32_t lane = threadIdx.x, g = lane / C, p = lane % C;
     const bool slot = g < G;
@@ -554,6 +722,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
             placed_device[e] = -1;
             placed_mu[e] = nan;
         }
+        dismiss();
         return;
     }
     int32_t rev = -1, rq = 0;
@@ -584,16 +753,6 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
         rrq = rQ[r];
     }
     rebuild(-1);
-
-    // Eq. (5) through the model's reciprocal (computed, then selected, so
-    // no lane branches), or the drop step of Alg. 1
-    auto drop = [&](double T_agg, double T, double yT) {
-        if (ISO) {
-            const double r = div_by_recip(T_agg - T, T, yT);
-            return T > 0.0 ? r : 0.0;
-        }
-        return drop_of(T_agg, T, RM_DROP_ADJUSTED);
-    };
 
     // events [wbase, wbase + 64) in registers, one per lane
     int32_t wbase = 0;
@@ -636,223 +795,237 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
     double pf_d1 = 0.0, pf_d2 = 0.0, pf_g1 = 1.0, pf_g2 = 1.0;
 
     int32_t e = 0;
-    while (e < E) {
-        int32_t v = event_at(e);
-        // ---- arrivals while some device has a free slot: one round each,
-        // without branches on per-lane data.  The round reads the next
-        // event, and the rare events below leave this loop, so the state
-        // carried from round to round is not merged with theirs.
-        while (v >= 0 && v < N && n_res < most) {
-            int32_t v_next;
-            const bool occ = slot && p < cnt;
-            int32_t qv;
-            double Tv, yTv, yqv;
-            if (nx_v == v) {
-                qv = nx_q;
-                Tv = nx_T;
-                yTv = nx_y;
-                yqv = nx_yq;
-            } else {
-                qv = q[v];
-                Tv = iso[v];
-                yTv = rT[v];
-                yqv = rQ[v];
-            }
-            // a prefetch for this arrival covers every occupied slot: slots keep
-            // their model between rounds, and the one a round fills was fetched
-            // for the arrival it received
-            double d1, d2;
-            if (pf_v == v) {
-                d1 = pf_g1 * pf_d1;
-                d2 = pf_g2 * pf_d2;
-            } else {
-                const int32_t rr = occ ? r : 0;
-                d1 = overlap_scale_r(rq, qv, yqv) *
-                     delay[(uint32_t)rr * (uint32_t)N + (uint32_t)v];
-                d2 = overlap_scale_r(qv, rq, rrq) *
-                     delay[(uint32_t)v * (uint32_t)N + (uint32_t)rr];
-            }
-            d1 = occ ? d1 : 0.0;
-            d2 = occ ? d2 : 0.0;
-            // issue the next arrival's reads for the slot's resident after this
-            // round (the arrival itself where this slot would receive it).  The
-            // reads are unconditional (clamped to entry 0 when there is nothing
-            // to fetch) so that no branch joins on their results.
-            {
-                const int32_t vn0 = e + 1 < E ? event_at(e + 1) : -1;
-                v_next = vn0;
-                // the reads serve the next arrival: past up to two departures
-                // (their slot moves carry the reads along), as far as the
-                // events in registers reach
-                int32_t vt = vn0;
-                if (vt < 0 && e + 2 < E && e + 2 - wbase < 64) {
-                    vt = __builtin_amdgcn_readlane(ev_w, e + 2 - wbase);
-                    if (vt < 0 && e + 3 < E && e + 3 - wbase < 64)
-                        vt = __builtin_amdgcn_readlane(ev_w, e + 3 - wbase);
+    // arrivals deferred by lambda since the state last changed, and how many
+    // of them start a scan
+    int32_t deferred = 0, scan_after = kScanAfter;
+    for (;;) {
+        while (e < E) {
+            int32_t v = event_at(e);
+            // ---- arrivals while some device has a free slot: one round each,
+            // without branches on per-lane data.  The round reads the next
+            // event, and the rare events below leave this loop, so the state
+            // carried from round to round is not merged with theirs.
+            while (v >= 0 && v < N && n_res < most && deferred < scan_after) {
+                int32_t v_next;
+                const bool occ = slot && p < cnt;
+                int32_t qv;
+                double Tv, yTv, yqv;
+                if (nx_v == v) {
+                    qv = nx_q;
+                    Tv = nx_T;
+                    yTv = nx_y;
+                    yqv = nx_yq;
+                } else {
+                    qv = q[v];
+                    Tv = iso[v];
+                    yTv = rT[v];
+                    yqv = rQ[v];
                 }
-                const bool vn_ok = vt >= 0 && vt < N;
-                const int32_t vn = vn_ok ? vt : 0;
-                const int32_t rn0 = !slot ? -1 : (p < cnt ? r : (p == cnt ? v : -1));
-                const int32_t rn = rn0 >= 0 ? rn0 : 0;
-                nx_v = vn_ok ? vn : -1;
-                pf_v = nx_v;
-                nx_q = q[vn];
-                nx_T = iso[vn];
-                nx_y = rT[vn];
-                nx_yq = rQ[vn];
-                // N <= kLdsModels, so the entry index fits 24 bits
-                pf_d1 = delay[__umul24((uint32_t)rn, (uint32_t)N) + (uint32_t)vn];
-                pf_d2 = delay[__umul24((uint32_t)vn, (uint32_t)N) + (uint32_t)rn];
-                pf_qr = (p < cnt) ? rq : qv;
-                pf_yqr = (p < cnt) ? rrq : yqv;
-            }
-            // 1 / (residents + 1) of this lane's device, read after the next
-            // event so that reading that event waits for no LDS read
-            const double rcnt = s_rn[cnt + 1];
-            const double cand = racc + d1;
-            // ordered sums over each device's slots, needed on its last slot lane:
-            // x = T_v + d2_0 + d2_1 + ..., z = drop_0 + drop_1 + ... (empty slots
-            // add +0).  With C <= 4 a device's slots form one DPP quad (or half
-            // of one), so its last lane adds its slots' values in slot order from
-            // quad broadcasts; with C = 8 the sums run as C-1 row shifts.
-            double x = (p == 0) ? Tv + d2 : d2;
-            double z = occ ? drop(cand, rTi, rrT) : 0.0;
-            if (C == 4) {
-                x = ((dpp_take<kDppQuad0>(x) + dpp_take<kDppQuad1>(x)) + dpp_take<kDppQuad2>(x)) + x;
-                z = ((dpp_take<kDppQuad0>(z) + dpp_take<kDppQuad1>(z)) + dpp_take<kDppQuad2>(z)) + z;
-            } else if (C == 2) {
-                x = dpp_take<kDppPair0>(x) + x;
-                z = dpp_take<kDppPair0>(z) + z;
-            } else {
-    #pragma unroll
-                for (int s2 = 1; s2 < C; ++s2) {
-                    const double xs = dpp_take<kDppShr1>(x);   // lane p - 1 (p >= 1 reads it)
-                    const double zs = dpp_take<kDppShr1>(z);
-                    x = (p == s2) ? xs + x : x;
-                    z = (p == s2) ? zs + z : z;
+                // a prefetch for this arrival covers every occupied slot: slots keep
+                // their model between rounds, and the one a round fills was fetched
+                // for the arrival it received
+                double d1, d2;
+                if (pf_v == v) {
+                    d1 = pf_g1 * pf_d1;
+                    d2 = pf_g2 * pf_d2;
+                } else {
+                    const int32_t rr = occ ? r : 0;
+                    d1 = overlap_scale_r(rq, qv, yqv) *
+                         delay[(uint32_t)rr * (uint32_t)N + (uint32_t)v];
+                    d2 = overlap_scale_r(qv, rq, rrq) *
+                         delay[(uint32_t)v * (uint32_t)N + (uint32_t)rr];
                 }
+                d1 = occ ? d1 : 0.0;
+                d2 = occ ? d2 : 0.0;
+                // issue the next arrival's reads for the slot's resident after this
+                // round (the arrival itself where this slot would receive it).  The
+                // reads are unconditional (clamped to entry 0 when there is nothing
+                // to fetch) so that no branch joins on their results.
+                {
+                    const int32_t vn0 = e + 1 < E ? event_at(e + 1) : -1;
+                    v_next = vn0;
+                    // the reads serve the next arrival: past up to two departures
+                    // (their slot moves carry the reads along), as far as the
+                    // events in registers reach
+                    int32_t vt = vn0;
+                    if (vt < 0 && e + 2 < E && e + 2 - wbase < 64) {
+                        vt = __builtin_amdgcn_readlane(ev_w, e + 2 - wbase);
+                        if (vt < 0 && e + 3 < E && e + 3 - wbase < 64)
+                            vt = __builtin_amdgcn_readlane(ev_w, e + 3 - wbase);
+                    }
+                    const bool vn_ok = vt >= 0 && vt < N;
+                    const int32_t vn = vn_ok ? vt : 0;
+                    const int32_t rn0 = !slot ? -1 : (p < cnt ? r : (p == cnt ? v : -1));
+                    const int32_t rn = rn0 >= 0 ? rn0 : 0;
+                    nx_v = vn_ok ? vn : -1;
+                    pf_v = nx_v;
+                    nx_q = q[vn];
+                    nx_T = iso[vn];
+                    nx_y = rT[vn];
+                    nx_yq = rQ[vn];
+                    // N <= kLdsModels, so the entry index fits 24 bits
+                    pf_d1 = delay[__umul24((uint32_t)rn, (uint32_t)N) + (uint32_t)vn];
+                    pf_d2 = delay[__umul24((uint32_t)vn, (uint32_t)N) + (uint32_t)rn];
+                    pf_qr = (p < cnt) ? rq : qv;
+                    pf_yqr = (p < cnt) ? rrq : yqv;
+                }
+                // 1 / (residents + 1) of this lane's device, read after the next
+                // event so that reading that event waits for no LDS read
+                const double rcnt = s_rn[cnt + 1];
+                const double cand = racc + d1;
+                double x = (p == 0) ? Tv + d2 : d2;
+                double z = occ ? slot_drop<ISO>(cand, rTi, rrT) : 0.0;
+                slot_sums<C>(p, x, z);
+                // the device's mean drop with the arrival, on its last slot lane
+                const double mbar = div_by_recip(z + slot_drop<ISO>(x, Tv, yTv), (double)(cnt + 1), rcnt);
+                const double key = (slot && p == C - 1 && cnt < cap && mbar < inf) ? mbar : inf;
+                // before the decision, so that it fills the argmin's latency: the
+                // arrival's aggregated time on every lane of its device (from the
+                // device's last slot lane) and the overlap scales of the entries
+                // requested above (they need only q)
+                double t_new = x;
+                if (C == 4) t_new = dpp_take<kDppQuad3>(x);
+                else if (C == 2) t_new = dpp_take<kDppPair1>(x);
+                const double g1n = overlap_scale_r(pf_qr, nx_q, nx_yq);
+                const double g2n = overlap_scale_r(nx_q, pf_qr, pf_yqr);
+                // argmin over devices, lowest device on ties; the winning key is
+                // the wave minimum
+                double kwin;
+                const int32_t win = wave_argmin_lane<C>(key, kwin);
+                const int32_t idx = win >= 0 ? win / C : 0x7fffffff;
+                const bool placed = win >= 0 && kwin < lambda;
+                out(e, placed ? idx : -1, kwin);
+                // commit to the chosen device
+                if (C == 8) t_new = read_lane(x, placed ? win : 0);
+                const bool mine = placed && g == idx;
+                const bool take_new = mine && p == cnt;
+                racc = (mine && p < cnt) ? cand : (take_new ? t_new : racc);
+                r = take_new ? v : r;
+                rev = take_new ? e : rev;
+                rq = take_new ? qv : rq;
+                rTi = take_new ? Tv : rTi;
+                rrT = take_new ? yTv : rrT;
+                rrq = take_new ? yqv : rrq;
+                cnt = mine ? cnt + 1 : cnt;
+                n_res += placed ? 1 : 0;
+                deferred = placed ? 0 : deferred + 1;
+                pf_g1 = g1n;
+                pf_g2 = g2n;
+                ++e;
+                if (e >= E) break;
+                v = v_next;
             }
-            // the device's mean drop with the arrival, on its last slot lane
-            const double mbar = div_by_recip(z + drop(x, Tv, yTv), (double)(cnt + 1), rcnt);
-            const double key = (slot && p == C - 1 && cnt < cap && mbar < inf) ? mbar : inf;
-            // before the decision, so that it fills the argmin's latency: the
-            // arrival's aggregated time on every lane of its device (from the
-            // device's last slot lane) and the overlap scales of the entries
-            // requested above (they need only q)
-            double t_new = x;
-            if (C == 4) t_new = dpp_take<kDppQuad3>(x);
-            else if (C == 2) t_new = dpp_take<kDppPair1>(x);
-            const double g1n = overlap_scale_r(pf_qr, nx_q, nx_yq);
-            const double g2n = overlap_scale_r(nx_q, pf_qr, pf_yqr);
-            // argmin over devices, lowest device on ties; the winning key is
-            // the wave minimum
-            double kwin;
-            const int32_t win = wave_argmin_lane<C>(key, kwin);
-            const int32_t idx = win >= 0 ? win / C : 0x7fffffff;
-            const bool placed = win >= 0 && kwin < lambda;
-            out(e, placed ? idx : -1, kwin);
-            // commit to the chosen device
-            if (C == 8) t_new = read_lane(x, placed ? win : 0);
-            const bool mine = placed && g == idx;
-            const bool take_new = mine && p == cnt;
-            racc = (mine && p < cnt) ? cand : (take_new ? t_new : racc);
-            r = take_new ? v : r;
-            rev = take_new ? e : rev;
-            rq = take_new ? qv : rq;
-            rTi = take_new ? Tv : rTi;
-            rrT = take_new ? yTv : rrT;
-            rrq = take_new ? yqv : rrq;
-            cnt = mine ? cnt + 1 : cnt;
-            n_res += placed ? 1 : 0;
-            pf_g1 = g1n;
-            pf_g2 = g2n;
-            ++e;
             if (e >= E) break;
-            v = v_next;
+            if (v < 0) {
+                // ---- departure of the model placed by arrival event `target`
+                // (the next arrival's reads stay valid: they follow their slots)
+                const int64_t target = -1 - (int64_t)v;
+                if (target >= e || events[target] < 0) {
+                    if (lane == 0 && status) atomicOr(status, RM_ST_BAD_EVENT);
+                    out(e, -1, nan);
+                    ++e;
+                    continue;
+                }
+                const unsigned long long hit = __ballot(slot && p < cnt && rev == (int32_t)target);
+                if (!hit) {       // the arrival was deferred: nothing to remove
+                    out(e, -1, nan);
+                    ++e;
+                    continue;
+                }
+                const int32_t L = __ffsll((long long)hit) - 1, hg = L / C, hp = L % C;
+                out(e, hg, nan);
+                // slots after the departing one move down by one
+                const int32_t r_up = __builtin_amdgcn_update_dpp(r, r, kDppShl1, 0xF, 0xF, false);
+                const int32_t ev_up = __builtin_amdgcn_update_dpp(rev, rev, kDppShl1, 0xF, 0xF, false);
+                const int32_t q_up = __builtin_amdgcn_update_dpp(rq, rq, kDppShl1, 0xF, 0xF, false);
+                const double T_up = dpp_move<kDppShl1>(rTi);
+                const double y_up = dpp_move<kDppShl1>(rrT);
+                const double yq_up = dpp_move<kDppShl1>(rrq);
+                const int32_t pq_up = __builtin_amdgcn_update_dpp(pf_qr, pf_qr, kDppShl1, 0xF, 0xF, false);
+                const double pyq_up = dpp_move<kDppShl1>(pf_yqr);
+                const double pd1_up = dpp_move<kDppShl1>(pf_d1);
+                const double pd2_up = dpp_move<kDppShl1>(pf_d2);
+                const double pg1_up = dpp_move<kDppShl1>(pf_g1);
+                const double pg2_up = dpp_move<kDppShl1>(pf_g2);
+                if (g == hg) {
+                    if (p >= hp) {
+                        r = r_up;
+                        rev = ev_up;
+                        rq = q_up;
+                        rTi = T_up;
+                        rrT = y_up;
+                        rrq = yq_up;
+                        pf_qr = pq_up;
+                        pf_yqr = pyq_up;
+                        pf_d1 = pd1_up;
+                        pf_d2 = pd2_up;
+                        pf_g1 = pg1_up;
+                        pf_g2 = pg2_up;
+                    }
+                    cnt -= 1;
+                }
+                n_res -= 1;
+                deferred = 0;
+                rebuild(hg);
+                ++e;
+                continue;
+            }
+            if (v >= N) {
+                if (lane == 0 && status) atomicOr(status, RM_ST_BAD_MODEL_ID);
+                out(e, -1, nan);
+                ++e;
+                continue;
+            }
+            if (n_res < most) break;   // a run of deferrals
+            // ---- every device full (the only case left): arrivals up to the
+            // next departure are deferred with an infinite mean (no device can
+            // take them)
+            int32_t e1 = e;
+            while (e1 < E) {
+                const int32_t x = e1 + lane;
+                const int32_t ev = x < E ? events[x] : 0;
+                const unsigned long long dep = __ballot(x < E && ev < 0);
+                const int32_t n = dep ? __ffsll((long long)dep) - 1 : (E - e1 < 64 ? E - e1 : 64);
+                if (lane < n) {
+                    placed_device[x] = -1;
+                    placed_mu[x] = ev >= N ? nan : inf;
+                }
+                if (__ballot(lane < n && ev >= N) && lane == 0 && status)
+                    atomicOr(status, RM_ST_BAD_MODEL_ID);
+                e1 += n;
+                if (dep) break;
+            }
+            pf_v = -1;
+            nx_v = -1;
+            e = e1;
         }
         if (e >= E) break;
-        if (v < 0) {
-            // ---- departure of the model placed by arrival event `target`
-            // (the next arrival's reads stay valid: they follow their slots)
-            const int64_t target = -1 - (int64_t)v;
-            if (target >= e || events[target] < 0) {
-                if (lane == 0 && status) atomicOr(status, RM_ST_BAD_EVENT);
-                out(e, -1, nan);
-                ++e;
-                continue;
-            }
-            const unsigned long long hit = __ballot(slot && p < cnt && rev == (int32_t)target);
-            if (!hit) {       // the arrival was deferred: nothing to remove
-                out(e, -1, nan);
-                ++e;
-                continue;
-            }
-            const int32_t L = __ffsll((long long)hit) - 1, hg = L / C, hp = L % C;
-            out(e, hg, nan);
-            // slots after the departing one move down by one
-            const int32_t r_up = __builtin_amdgcn_update_dpp(r, r, kDppShl1, 0xF, 0xF, false);
-            const int32_t ev_up = __builtin_amdgcn_update_dpp(rev, rev, kDppShl1, 0xF, 0xF, false);
-            const int32_t q_up = __builtin_amdgcn_update_dpp(rq, rq, kDppShl1, 0xF, 0xF, false);
-            const double T_up = dpp_move<kDppShl1>(rTi);
-            const double y_up = dpp_move<kDppShl1>(rrT);
-            const double yq_up = dpp_move<kDppShl1>(rrq);
-            const int32_t pq_up = __builtin_amdgcn_update_dpp(pf_qr, pf_qr, kDppShl1, 0xF, 0xF, false);
-            const double pyq_up = dpp_move<kDppShl1>(pf_yqr);
-            const double pd1_up = dpp_move<kDppShl1>(pf_d1);
-            const double pd2_up = dpp_move<kDppShl1>(pf_d2);
-            const double pg1_up = dpp_move<kDppShl1>(pf_g1);
-            const double pg2_up = dpp_move<kDppShl1>(pf_g2);
-            if (g == hg) {
-                if (p >= hp) {
-                    r = r_up;
-                    rev = ev_up;
-                    rq = q_up;
-                    rTi = T_up;
-                    rrT = y_up;
-                    rrq = yq_up;
-                    pf_qr = pq_up;
-                    pf_yqr = pyq_up;
-                    pf_d1 = pd1_up;
-                    pf_d2 = pd2_up;
-                    pf_g1 = pg1_up;
-                    pf_g2 = pg2_up;
-                }
-                cnt -= 1;
-            }
-            n_res -= 1;
-            rebuild(hg);
-            ++e;
-            continue;
+        // ---- a run of deferrals: the events after it, by all waves
+        flush();
+        sc.acc[lane] = racc;
+        sc.T[lane] = rTi;
+        sc.yT[lane] = rrT;
+        sc.yq[lane] = rrq;
+        sc.r[lane] = r;
+        sc.cnt[lane] = cnt;
+        sc.q[lane] = rq;
+        if (lane == 0) {
+            sc.stop[0] = 0x7fffffff;
+            sc.e = e;
         }
-        if (v >= N) {
-            if (lane == 0 && status) atomicOr(status, RM_ST_BAD_MODEL_ID);
-            out(e, -1, nan);
-            ++e;
-            continue;
-        }
-        // ---- every device full (the only case left): arrivals up to the
-        // next departure are deferred with an infinite mean (no device can
-        // take them)
-        int32_t e1 = e;
-        while (e1 < E) {
-            const int32_t x = e1 + lane;
-            const int32_t ev = x < E ? events[x] : 0;
-            const unsigned long long dep = __ballot(x < E && ev < 0);
-            const int32_t n = dep ? __ffsll((long long)dep) - 1 : (E - e1 < 64 ? E - e1 : 64);
-            if (lane < n) {
-                placed_device[x] = -1;
-                placed_mu[x] = ev >= N ? nan : inf;
-            }
-            if (__ballot(lane < n && ev >= N) && lane == 0 && status)
-                atomicOr(status, RM_ST_BAD_MODEL_ID);
-            e1 += n;
-            if (dep) break;
-        }
+        __syncthreads();
+        const int32_t from = e;
+        e = scan_deferred<C, ISO>(sc, N, delay, iso, rT, rQ, q, s_rn, G, cap, E, events, lambda,
+                                  placed_device, placed_mu);
+        scan_after = e - from >= kScanAfter ? kScanAfter
+                                            : (2 * scan_after < kScanMost ? 2 * scan_after
+                                                                          : kScanMost);
+        deferred = 0;
         pf_v = -1;
         nx_v = -1;
-        e = e1;
     }
     flush();
+    dismiss();
 
     if (slot) {
         if (p < cap) resident[g * cap + p] = p < cnt ? r : -1;
@@ -877,7 +1050,7 @@ hipError_t launch_place(int32_t n_models, const double* delay, const double* iso
         // the wave kernel also keeps 1 / q per model
         const size_t wave_lds = lds + (size_t)n_models * sizeof(double);
         auto go = [&](auto kernel) {
-            if (wave_lds > 65536) {
+            if (wave_lds > 49152) {   // beside the slots of a scan
                 const hipError_t e = hipFuncSetAttribute(
                     reinterpret_cast<const void*>(kernel),
                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)wave_lds);
