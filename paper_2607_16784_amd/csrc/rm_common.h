@@ -298,12 +298,6 @@ __device__ inline KernelOcc kernel_occupancy(const Desc& d, const Packing& pk, i
     return o;
 }
 
-__device__ inline double wave_sum(double v)
-{
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 __device__ inline int32_t wave_or(int32_t v)
 {
     for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, 64);
@@ -359,15 +353,6 @@ __device__ inline double read_lane(double v, int lane)
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-__device__ inline double wave_sum_dpp(double v)
-{
-    v = v + dpp_double<kDppXor1>(v);
-    v = v + dpp_double<kDppXor2>(v);
-    v = v + dpp_double<kDppRor4>(v);
-    v = v + dpp_double<kDppRor8>(v);
-    return ((read_lane(v, 0) + read_lane(v, 16)) + read_lane(v, 32)) + read_lane(v, 48);
 }
 
 // Exactly rounded a / b from y = RN(1/b): one correction step after the

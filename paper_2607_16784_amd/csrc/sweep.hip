@@ -4,11 +4,12 @@
 // gamma_ij * Delta_ij / T_i (Sec. 3.3, Eq. 5).
 //
 // Design (gfx950):
-//  * One workgroup per model pair at a time.  Both models' 16-byte records
-//    {P[k+1], packed footprint of kernel k} are staged into LDS with
-//    coalesced loads, behind a slot {P[0] = 0} and followed by sentinel
-//    slots with an empty footprint.  The victim's footprints are pre-biased
-//    so the Eq. (2) test of a kernel pair is one 64-bit add and one AND.
+//  * A workgroup works on one model pair at a time (FIRST: on a tile of
+//    several).  The models' 16-byte records {P[k+1], packed footprint of
+//    kernel k} are staged into LDS with coalesced loads, behind a slot
+//    {P[0] = 0} and followed by sentinel slots with an empty footprint.  One
+//    model's footprints are pre-biased so the Eq. (2) test of a kernel pair
+//    is one 64-bit add and one AND.
 //  * An alignment is a window [w0, w1) over the two (shifted) timelines.  The
 //    interval boundaries inside it form two sorted lists A' and B'; walking
 //    their merge in order visits every stretch during which one pair (k, l)
@@ -17,51 +18,30 @@
 //    every lane walks the same number of boundaries; per-lane sums are
 //    combined with DPP reductions.
 //  * FIRST: one alignment per pair; the window is symmetric, so one sweep of
-//    the unordered pair yields both Delta_ij and Delta_ji, and the whole
-//    512-lane workgroup splits it (persistent workgroups, pipelined loads).
-//    OFFSETS / CONFLICT_STARTS: one ordered pair per workgroup at a time,
-//    each wave sweeps its own alignments with 64 lanes.
-//  * Every stretch contributes (e - lo) * a_k / (a_k + a_l).  OFFSETS and
-//    CONFLICT_STARTS form the share as the correctly rounded quotient
-//    (tabulated reciprocal plus one correction step); FIRST multiplies the
-//    length by the tabulated reciprocal and adds a_k times that with a fused
-//    multiply-add, and takes the other direction as the conflicting time
-//    minus that (a stretch's two shares add up to its length).  Only the
-//    rounding of each term (a few ulp) and the order of the final sums
-//    differ from a sequential evaluation.
+//    the unordered pair yields both Delta_ij and Delta_ji; one or two waves
+//    split it (persistent workgroups, pipelined loads).  So does one walk of
+//    a start pair (CONFLICT_STARTS, SAMPLED_STARTS).  OFFSETS sweeps ordered
+//    pairs.  Short windows are split over 8 or 16 lanes, so that a wave
+//    carries several alignments, long or few ones over the whole wave.
+//  * Every stretch contributes (e - lo) * a_k / (a_k + a_l): the length times
+//    the tabulated reciprocal, then a_k times that added with a fused
+//    multiply-add; where both directions come from one walk the other one is
+//    the conflicting time minus that (a stretch's two shares add up to its
+//    length).  Pairs too long to stage form the share as the correctly
+//    rounded quotient.  Only the rounding of each term (a few ulp) and the
+//    order of the final sums differ from a sequential evaluation.
 #include <atomic>
 
 #include "rm_common.h"
 
 namespace rm {
 
-// A model's staged records in LDS, slot s at physical index s + s/8: one
-// 16-byte hole after every eight records.  Merge-path lanes sit about eight
-// records apart, so without the hole every lane of a 16-byte LDS read would
-// start in the same bank; with it consecutive lanes start 36 banks apart.
-struct Slots {
-    Record* p;
-    __device__ Record& operator[](int32_t s) const { return p[s + (s >> 3)]; }
-};
-
-// Physical records taken by n slots.
-__host__ __device__ inline int32_t padded(int32_t n)
-{
-    return n + (n + 7) / 8;
-}
-
-// LDS records reserved per pair when q_i + q_j <= K (both models' q + 3 slots).
-__host__ __device__ inline int32_t pair_records(int32_t K)
-{
-    return K + 6 + (K + 6 + 7) / 8 + 2;
-}
-
 // The generic alignment sweep below reads a model's records through an
 // accessor: slot 0 holds {P[0] = 0, empty footprint}, slot k+1 the record of
-// kernel k, slots past q a sentinel that conflicts with nothing.  Slots (LDS,
-// staged) and GlobalSlots (the record table in memory, for pairs too long to
-// stage) provide it; reciprocals 1/D come from a plain table (PlainRecip) or
-// the spread LDS table of the byte-addressed kernels (SpreadRecip).
+// kernel k, slots past q a sentinel that conflicts with nothing.  GlobalSlots
+// provides it for pairs too long to stage (the record table in memory);
+// reciprocals 1/D come from the spread LDS table of the byte-addressed
+// kernels (SpreadRecip).
 
 // Number of slots t in [lo, hi] with s[t].end + sig <= v (s non-decreasing).
 template <typename SL>
@@ -127,22 +107,11 @@ __device__ inline double share_of(double a, double den, double y)
     return __builtin_fma(r, y, q0);
 }
 
-// 1/D for D = 0..255, built once per workgroup (needs >= 256 threads).
-__device__ inline void build_recip(double* recip)
-{
-    if (threadIdx.x < 256) recip[threadIdx.x] = 1.0 / (double)threadIdx.x;
-}
-
-struct PlainRecip {
-    const double* t;
-    __device__ double operator()(uint32_t d) const { return t[d]; }
-};
-
 // Walk `steps` merged boundaries starting at kernels (k, l).  The record
 // after the current one of each model is loaded one step ahead (both are
 // reloaded every step, so there is no branch), so each LDS load has a whole
 // step to land before it is consumed.
-template <bool BOTH, bool SHIFT, typename SL, typename RC>
+template <bool BOTH, typename SL, typename RC>
 __device__ inline void walk(SL A, SL B, RC recip, int32_t k, int32_t l, double sa, double sb,
                             double lo, int32_t steps, uint64_t guard, double& acc_i,
                             double& acc_j)
@@ -154,8 +123,8 @@ __device__ inline void walk(SL A, SL B, RC recip, int32_t k, int32_t l, double s
     double nea = A[k + 2].end, neb = B[l + 2].end;
     uint64_t nfa = A[k + 2].fp, nfb = B[l + 2].fp;
     for (int32_t t = 0; t < steps; ++t) {
-        const double xa = SHIFT ? ea + sa : ea;
-        const double xb = SHIFT ? eb + sb : eb;
+        const double xa = ea + sa;
+        const double xb = eb + sb;
         const bool takeA = xa <= xb;
         const double e = takeA ? xa : xb;
         const double len = e - lo;
@@ -200,31 +169,7 @@ __device__ inline void sweep_alignment(SL A, SL B, RC recip, const Align& al, in
     const double xa = A[k].end + al.sa, yb = B[l].end + al.sb;
     double lo = xa > yb ? xa : yb;
     if (al.w0 > lo) lo = al.w0;
-    walk<BOTH, true>(A, B, recip, k, l, al.sa, al.sb, lo, steps, guard, acc_i, acc_j);
-}
-
-// Stage model m's records into slots [0, q+2] of `dst` (q + 3 slots).
-__device__ inline void stage(Slots dst, const Record* __restrict__ rec, int64_t first, int32_t q,
-                             uint64_t bias, int tid, int nthreads)
-{
-    for (int32_t t = tid; t < q; t += nthreads) {
-        Record r = rec[first + t];
-        r.fp += bias;
-        dst[t + 1] = r;
-    }
-    if (tid < 3) {
-        dst[tid == 0 ? 0 : q + tid].end = tid == 0 ? 0.0 : __builtin_inf();
-        dst[tid == 0 ? 0 : q + tid].fp = bias;
-    }
-}
-
-// Spread consecutive workgroups over the 8 XCDs in contiguous chunks, so the
-// pairs resident on one XCD share models and hit in that XCD's L2.
-__device__ inline int64_t xcd_remap(int64_t b, int64_t nblocks)
-{
-    const int64_t per = nblocks / 8;
-    if (b >= per * 8) return b;
-    return (b % 8) * per + b / 8;
+    walk<BOTH>(A, B, recip, k, l, al.sa, al.sb, lo, steps, guard, acc_i, acc_j);
 }
 
 // The pair's kernels fit the staging buffer (sized for q_i + q_j <= K).
