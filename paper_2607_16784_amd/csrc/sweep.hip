@@ -2157,7 +2157,7 @@ __global__ __launch_bounds__(kFirstBlock, 2) void sweep_sampled_kernel(
     double* sortbuf = vals_j + K;
     int32_t* s_nA = reinterpret_cast<int32_t*>(sortbuf + (K > 64 ? next_pow2((unsigned)K) : 0));
     int32_t* s_nB = s_nA + K;
-    int32_t* s_mem = s_nB + K;     // the pair's draws in C_ij
+    int32_t* s_mem = s_nB + K;     // the pair's draws in C_ij, in no set order
     int32_t* s_nmem = s_next + 2;  // how many
 
     const int64_t G = gridDim.x;
@@ -2231,28 +2231,6 @@ __global__ __launch_bounds__(kFirstBlock, 2) void sweep_sampled_kernel(
             }
             __syncthreads();
             const int32_t nmem = *s_nmem;
-            // Longest windows first, so that the last draws of a pair, which
-            // the other waves wait for, are its shortest: 256 x 2000 kernels,
-            // 64 draws, 1.359 -> 1.342 ms.  (Smaller lane groups, as in the
-            // OFFSETS sweep, leave too few draws a pair to share out: 32 lanes
-            // a draw 1.39 ms, 16 lanes 1.88.  Twice the waves, 1024 lanes a
-            // workgroup without the next pair's records in registers: 1.33.)
-            // More members than this fill the waves without it, and their
-            // ranks would cost the square of their number.
-            if (nmem <= kFirstBlock / 4) {
-                int32_t r = 0, rank = 0;
-                if (tid < nmem) {
-                    r = s_mem[tid];
-                    const int32_t n = s_nA[r] + s_nB[r];
-                    for (int32_t u = 0; u < nmem; ++u) {
-                        const int32_t x = s_mem[u], nx = s_nA[x] + s_nB[x];
-                        rank += (nx > n || (nx == n && u < tid)) ? 1 : 0;
-                    }
-                }
-                __syncthreads();
-                if (tid < nmem) s_mem[rank] = r;
-                __syncthreads();
-            }
             // The loop body has no lane-dependent branch: a branch on the
             // lane index before the cross-lane operations of a draw lets the
             // compiler run the wave's lanes through the loop separately.
