@@ -433,6 +433,7 @@ constexpr int kDppQuad2 = 0xAA;   // quad_perm [2,2,2,2]
 constexpr int kDppQuad3 = 0xFF;   // quad_perm [3,3,3,3]: slot 3 of the quad
 constexpr int kDppPair1 = 0xF5;   // quad_perm [1,1,3,3]: slot 1 of each lane pair
 constexpr int kDppPair0 = 0xA0;   // quad_perm [0,0,2,2]: slot 0 of each lane pair
+constexpr int kDppMirror = 0x140; // row_mirror: lane u of 16 reads lane 15 - u
 
 template <int CTRL>
 __device__ inline double dpp_move(double v)
@@ -521,114 +522,127 @@ __device__ inline double slot_drop(double T_agg, double T, double yT)
 
 // A run of arrivals that lambda defers leaves the state as it is, so the
 // arrivals after it can be looked at side by side: after kScanAfter deferrals
-// in a row wave 0 puts the slots into LDS and all sixteen waves evaluate the
-// next events, 64 to 256 at a time, up to the first that is placed or is no
-// arrival.  1000 arrivals of which lambda defers most took 0.56 ms one round
-// each; now 16 devices of 3 take 78 us and 4 devices of 3 take 31 us (place_kernel:
-// 87 and 39 us).  Instruction issue of the sixteen waves bounds it, about 3.5 us
-// for 64 events on 64 lanes.  A run that ends early costs one such batch, so
-// after a scan that found fewer than kScanAfter deferrals the next one waits
-// for twice as many (departures stream of 1000 arrivals: 1.105 ms without
-// scans, 1.115 ms with).
-constexpr int kScanAfter = 16;
+// in a row wave 0 puts the slots into LDS and the other fifteen waves evaluate the
+// next events, each on a lane per device as place_kernel does, up to the first
+// that is placed or is no arrival; wave 0 waits.  (The evaluation stays out of
+// wave 0's code: inlined beside the event loop it slowed that loop by up to
+// 16%.)  A chunk of a scan is a chain of LDS and L2 reads, some 3 us for the
+// 15 (64 devices) to 256 events of 960 lanes, against 0.56 us for each round.
+// After a scan that found at least kScanAfter deferrals the next one starts
+// four times sooner, after any other twice as late, up to kScanMost events.  A
+// call of 1000 arrivals of which lambda 0.02 defers most: 16 devices of 3 105 us
+// (place_kernel 149 us, one round each 560 us), 10 of 3 70 us (97 us), 8 of 5 59
+// us (77 us).
+constexpr int kScanAfter = 8;
 constexpr int kScanMost = 256;
+constexpr int kScanLanes = kPlaceThreads - 64;
 
 struct ScanState {
-    double acc[64], T[64], yT[64], yq[64];
-    int32_t r[64], cnt[64], q[64];
-    double mu[2][256];  // smallest mean of an event, by chunk modulo 2
-    int32_t stop[3];    // first event that ends the run, by chunk modulo 3
-    int32_t e;          // first event; -1: no more scans
+    double acc[64];
+    int32_t r[64], cnt[64];
+    double mu[2][kScanMost];   // smallest mean of an event, by chunk modulo 2
+    int32_t stop[3];           // first event that ends the run, by chunk modulo 3
+    int32_t e;                 // first event; -1: no more scans
+    int32_t ready;             // waves that have checked their part of the delays
 };
 
-// By every wave of the workgroup (the slots in sc): the first event from sc.e
-// on that is not an arrival deferred by lambda; the events before it get their
-// outputs.
-template <int C, bool ISO>
-__device__ inline int32_t scan_deferred(ScanState& sc, int32_t N, const double* __restrict__ delay,
-                                        const double* iso, const double* rT, const double* rQ,
-                                        const int32_t* q, const double* s_rn, int32_t G,
-                                        int32_t cap, int32_t E, const int32_t* events,
-                                        double lambda, int32_t* __restrict__ placed_device,
-                                        double* __restrict__ placed_mu)
+// Events of one chunk of a scan, for G devices: a group of Gp lanes each.
+__device__ inline int32_t scan_chunk(int32_t Gp)
 {
-    constexpr int kPer = 4;
-    // a lane's events that are evaluated side by side; with C = 8 the row
-    // shifts of more than one would not fit the registers beside the slots
-    constexpr int kSide = C == 8 ? 1 : kPer;
-    // the slots of up to 32 or 16 lanes are held twice or four times, each
-    // copy for an event of its own
-    const int32_t bits = G * C <= 16 ? 4 : (G * C <= 32 ? 5 : 6), width = 1 << bits;
-    const int32_t lane = threadIdx.x & 63, sl = lane & (width - 1);
-    const int32_t chunk = (kPer * kPlaceThreads) >> bits;   // 64, 128 or 256 events
-    const int32_t g = sl / C, p = sl % C;
-    const bool slot = g < G;
-    const int32_t cnt = sc.cnt[sl], rq = sc.q[sl];
-    const bool occ = slot && p < cnt;
-    const uint32_t rr = occ ? (uint32_t)sc.r[sl] : 0u;
-    const double racc = sc.acc[sl], rTi = sc.T[sl], rrT = sc.yT[sl], rrq = sc.yq[sl];
-    const double rcnt = s_rn[cnt + 1];
-    const double inf = __builtin_inf();
-    int32_t stop = E;
-    int32_t k = 0;
-    for (int32_t b = __builtin_amdgcn_readfirstlane(sc.e);; b += chunk, ++k) {
-        for (int h = 0; h < kPer; h += kSide) {
-            // this wave's events, their entries all in flight before any is used
-            double d1[kSide], d2[kSide], least[kSide];
-            int32_t x[kSide], v[kSide];
-            bool arrival[kSide];
-#pragma unroll
-            for (int u = 0; u < kSide; ++u) {
-                x[u] = ((h + u) * kPlaceThreads + (int32_t)threadIdx.x) >> bits;   // in the chunk
-                const int32_t ev = b + x[u] < E ? events[b + x[u]] : -1;
-                arrival[u] = ev >= 0 && ev < N;
-                v[u] = arrival[u] ? ev : 0;
-                d1[u] = delay[__umul24(rr, (uint32_t)N) + (uint32_t)v[u]];
-                d2[u] = delay[__umul24((uint32_t)v[u], (uint32_t)N) + rr];
-            }
-#pragma unroll
-            for (int u = 0; u < kSide; ++u) {
-                // the round of the event loop, without its commit; of the two
-                // overlap scales the one of the longer model is not 1
-                const double Tv = iso[v[u]], yTv = rT[v[u]], yqv = rQ[v[u]];
-                const int32_t qv = q[v[u]];
-                const bool longer = rq > qv;
-                const double ratio = overlap_scale_r(longer ? rq : qv, longer ? qv : rq,
-                                                     longer ? yqv : rrq);
-                const double e1 = occ ? (longer ? ratio : 1.0) * d1[u] : 0.0;
-                const double e2 = occ ? (longer ? 1.0 : ratio) * d2[u] : 0.0;
-                double y = (p == 0) ? Tv + e2 : e2;
-                double z = occ ? slot_drop<ISO>(racc + e1, rTi, rrT) : 0.0;
-                slot_sums<C>(p, y, z);
-                const double mbar = div_by_recip(z + slot_drop<ISO>(y, Tv, yTv), (double)(cnt + 1), rcnt);
-                least[u] = (slot && p == C - 1 && cnt < cap && mbar < inf) ? mbar : inf;
-                // the minimum of the event's lanes on the last of them
-                least[u] = row_min<C>(least[u]);
-                if (width > 16) least[u] = min_key(least[u], dpp_take<kDppRowBcast15>(least[u]));
-                if (width > 32) least[u] = min_key(least[u], dpp_take<kDppRowBcast31>(least[u]));
-            }
-            if (sl == width - 1) {
-#pragma unroll
-                for (int u = kSide - 1; u >= 0; --u) {
-                    sc.mu[k & 1][x[u]] = least[u];
-                    if (!arrival[u] || (least[u] < inf && least[u] < lambda))
-                        atomicMin(&sc.stop[k % 3], b + x[u]);
-                }
-            }
-        }
-        if (threadIdx.x == 0) sc.stop[(k + 1) % 3] = 0x7fffffff;   // last read two chunks ago
+    const int32_t groups = kScanLanes / Gp;
+    return groups < kScanMost ? groups : kScanMost;
+}
+
+// Wave 0's side of a scan from event b: the first event that ends the run.
+__device__ inline int32_t await_scan(const ScanState& sc, int32_t b, int32_t chunk)
+{
+    int32_t stop;
+    for (int32_t k = 0;; b += chunk, ++k) {
         __syncthreads();
         stop = __builtin_amdgcn_readfirstlane(sc.stop[k % 3]);
+        if (stop < b + chunk) break;
+    }
+    __syncthreads();   // sc is written again by the next scan
+    return stop;
+}
+
+// Minimum over aligned groups of Gp lanes (a power of two) of keys that are
+// never NaN, on every lane of the group.
+__device__ inline double group_min(double m, int32_t Gp)
+{
+    if (Gp >= 2) m = min_key(m, dpp_take<kDppXor1>(m));
+    if (Gp >= 4) m = min_key(m, dpp_take<kDppXor2>(m));
+    if (Gp >= 8) m = min_key(m, dpp_take<kDppHalfMirror>(m));
+    if (Gp >= 16) m = min_key(m, dpp_take<kDppMirror>(m));
+    for (int o = 16; o < Gp; o <<= 1) m = min_key(m, __shfl_xor(m, o, 64));
+    return m;
+}
+
+// By the other waves: finds the first event from sc.e on that is not an arrival
+// deferred by lambda; the events before it get their outputs.  A lane takes
+// one device of one event: the sums of the event loop over the device's
+// residents in order.
+template <int C, bool ISO>
+__device__ inline void scan_deferred(ScanState& sc, int32_t N, const double* __restrict__ delay,
+                                     const double* iso, const double* rT, const double* rQ,
+                                     const int32_t* q, const double* s_rn, int32_t G, int32_t Gp,
+                                     int32_t cap, int32_t E, const int32_t* events, double lambda,
+                                     int32_t* __restrict__ placed_device,
+                                     double* __restrict__ placed_mu)
+{
+    const int32_t t = (int32_t)threadIdx.x - 64, chunk = scan_chunk(Gp);
+    const int32_t x = t / Gp, g = t & (Gp - 1);   // event of the chunk, device
+    const int32_t cnt = x < chunk && g < G ? sc.cnt[g * C] : 0;
+    const bool room = x < chunk && g < G && cnt < cap;
+    const double rcnt = s_rn[cnt + 1];
+    const double inf = __builtin_inf();
+    for (int32_t b = __builtin_amdgcn_readfirstlane(sc.e), k = 0;; b += chunk, ++k) {
+        const int32_t ev = x < chunk && b + x < E ? events[b + x] : -1;
+        const bool arrival = ev >= 0 && ev < N;
+        double least = inf;
+        if (arrival && room) {
+            double d1[C], d2[C];
+#pragma unroll
+            for (int p = 0; p < C; ++p) {   // every entry in flight before any is used
+                const int32_t m = p < cnt ? sc.r[g * C + p] : 0;
+                d1[p] = delay[__umul24((uint32_t)m, (uint32_t)N) + (uint32_t)ev];
+                d2[p] = delay[__umul24((uint32_t)ev, (uint32_t)N) + (uint32_t)m];
+            }
+            const double Tv = iso[ev], yTv = rT[ev], yqv = rQ[ev];
+            const int32_t qv = q[ev];
+            double sum = 0.0, T_agg = Tv;
+#pragma unroll
+            for (int p = 0; p < C; ++p) {
+                if (p >= cnt) continue;
+                const int32_t m = sc.r[g * C + p], qm = q[m];
+                // of the two overlap scales the one of the longer model is not 1
+                const bool longer = qm > qv;
+                const double ratio = overlap_scale_r(longer ? qm : qv, longer ? qv : qm,
+                                                     longer ? yqv : rQ[m]);
+                const double cand = sc.acc[g * C + p] + (longer ? ratio : 1.0) * d1[p];
+                sum = sum + slot_drop<ISO>(cand, iso[m], rT[m]);
+                T_agg = T_agg + (longer ? 1.0 : ratio) * d2[p];
+            }
+            const double mbar = div_by_recip(sum + slot_drop<ISO>(T_agg, Tv, yTv),
+                                             (double)(cnt + 1), rcnt);
+            least = mbar < inf ? mbar : inf;
+        }
+        least = group_min(least, Gp);
+        if (g == 0 && x < chunk) {
+            sc.mu[k & 1][x] = least;
+            if (!arrival || (least < inf && least < lambda)) atomicMin(&sc.stop[k % 3], b + x);
+        }
+        if (t == 0) sc.stop[(k + 1) % 3] = 0x7fffffff;   // last read two chunks ago
+        __syncthreads();
+        const int32_t stop = __builtin_amdgcn_readfirstlane(sc.stop[k % 3]);
         const bool last = stop < b + chunk;
-        const int32_t n = last ? stop - b : chunk;
-        if ((int32_t)threadIdx.x < n) {
-            placed_device[b + threadIdx.x] = -1;
-            placed_mu[b + threadIdx.x] = sc.mu[k & 1][threadIdx.x];
+        if (t < (last ? stop - b : chunk)) {
+            placed_device[b + t] = -1;
+            placed_mu[b + t] = sc.mu[k & 1][t];
         }
         if (last) break;
     }
     __syncthreads();   // sc is written again by the next scan
-    return stop;
 }
 
 template <int C, bool ISO>
@@ -650,7 +664,10 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
     __shared__ double s_rn[kCapMax + 2];   // RN(1/k), k = 0..capacity+1
     __shared__ ScanState sc;
     const bool scans = E > kScanAfter;
+    int32_t Gp = 1;   // lanes of an event in a scan
+    while (Gp < G) Gp <<= 1;
     if (threadIdx.x < kCapMax + 2) s_rn[threadIdx.x] = 1.0 / (double)threadIdx.x;
+    if (threadIdx.x == 0) sc.ready = 0;
     for (int32_t m = threadIdx.x; m < N; m += kPlaceThreads) {
         const double T = iso_g[m];
         iso[m] = T;
@@ -689,10 +706,11 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
         if (__ballot(bad != 0) && (threadIdx.x & 63) == 0 && status)
             atomicOr(status, RM_ST_BAD_DELAY);
         check_delay(delay, N, status, 64, kPlaceThreads - 64);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&sc.ready, 1);
         while (scans) {
             __syncthreads();   // wave 0 has set the next scan up, or is done
             if (__builtin_amdgcn_readfirstlane(sc.e) < 0) break;
-            scan_deferred<C, ISO>(sc, N, delay, iso, rT, rQ, q, s_rn, G, cap, E, events, lambda,
+            scan_deferred<C, ISO>(sc, N, delay, iso, rT, rQ, q, s_rn, G, Gp, cap, E, events, lambda,
                                   placed_device, placed_mu);
         }
         return;
@@ -742,7 +760,8 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
 #pragma unroll
         for (int32_t u = 0; u < C; ++u) {
             const int32_t m = __shfl(r, g * C + u, 64);
-            if (mine && u < cnt && u != p) t = t + scaled_delay(delay, q, N, r, m);
+            if (mine && u < cnt && u != p)
+                t = t + overlap_scale_r(rq, q[m], rQ[m]) * delay[(int64_t)r * N + m];
         }
         if (mine) racc = t;
     };
@@ -789,15 +808,16 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
 
     // the next arrival's model data and delay entries, fetched one round
     // ahead: raw entries for arrival pf_v and the overlap scales with them
-    int32_t nx_v = -1, nx_q = 0, pf_qr = 0;
+    int32_t nx_q = 0, pf_qr = 0;
     double nx_T = 0.0, nx_y = 0.0, nx_yq = 0.0, pf_yqr = 0.0;
     int32_t pf_v = -1;
     double pf_d1 = 0.0, pf_d2 = 0.0, pf_g1 = 1.0, pf_g2 = 1.0;
 
     int32_t e = 0;
-    // arrivals deferred by lambda since the state last changed, and how many
-    // of them start a scan
-    int32_t deferred = 0, scan_after = kScanAfter;
+    // a scan starts at event `scan_at` unless the state changes before it:
+    // `scan_after` events after the last change
+    int32_t scan_after = kScanAfter, scan_at = scan_after < E ? scan_after : E;
+    auto changed = [&](int32_t next) { scan_at = E - next < scan_after ? E : next + scan_after; };
     for (;;) {
         while (e < E) {
             int32_t v = event_at(e);
@@ -805,30 +825,26 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
             // without branches on per-lane data.  The round reads the next
             // event, and the rare events below leave this loop, so the state
             // carried from round to round is not merged with theirs.
-            while (v >= 0 && v < N && n_res < most && deferred < scan_after) {
+            while (v >= 0 && v < N && n_res < most) {
                 int32_t v_next;
                 const bool occ = slot && p < cnt;
+                // a prefetch for this arrival covers every occupied slot: slots keep
+                // their model between rounds, and the one a round fills was fetched
+                // for the arrival it received
                 int32_t qv;
-                double Tv, yTv, yqv;
-                if (nx_v == v) {
+                double Tv, yTv, yqv, d1, d2;
+                if (pf_v == v) {
                     qv = nx_q;
                     Tv = nx_T;
                     yTv = nx_y;
                     yqv = nx_yq;
+                    d1 = pf_g1 * pf_d1;
+                    d2 = pf_g2 * pf_d2;
                 } else {
                     qv = q[v];
                     Tv = iso[v];
                     yTv = rT[v];
                     yqv = rQ[v];
-                }
-                // a prefetch for this arrival covers every occupied slot: slots keep
-                // their model between rounds, and the one a round fills was fetched
-                // for the arrival it received
-                double d1, d2;
-                if (pf_v == v) {
-                    d1 = pf_g1 * pf_d1;
-                    d2 = pf_g2 * pf_d2;
-                } else {
                     const int32_t rr = occ ? r : 0;
                     d1 = overlap_scale_r(rq, qv, yqv) *
                          delay[(uint32_t)rr * (uint32_t)N + (uint32_t)v];
@@ -857,8 +873,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
                     const int32_t vn = vn_ok ? vt : 0;
                     const int32_t rn0 = !slot ? -1 : (p < cnt ? r : (p == cnt ? v : -1));
                     const int32_t rn = rn0 >= 0 ? rn0 : 0;
-                    nx_v = vn_ok ? vn : -1;
-                    pf_v = nx_v;
+                    pf_v = vn_ok ? vn : -1;
                     nx_q = q[vn];
                     nx_T = iso[vn];
                     nx_y = rT[vn];
@@ -908,12 +923,12 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
                 rrq = take_new ? yqv : rrq;
                 cnt = mine ? cnt + 1 : cnt;
                 n_res += placed ? 1 : 0;
-                deferred = placed ? 0 : deferred + 1;
                 pf_g1 = g1n;
                 pf_g2 = g2n;
                 ++e;
-                if (e >= E) break;
+                if (placed) changed(e);
                 v = v_next;
+                if (e >= scan_at) break;
             }
             if (e >= E) break;
             if (v < 0) {
@@ -965,9 +980,9 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
                     cnt -= 1;
                 }
                 n_res -= 1;
-                deferred = 0;
                 rebuild(hg);
                 ++e;
+                changed(e);
                 continue;
             }
             if (v >= N) {
@@ -976,7 +991,16 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
                 ++e;
                 continue;
             }
-            if (n_res < most) break;   // a run of deferrals
+            // ---- a run of deferrals: the events after it, by the other waves --
+            // later if they are still at the delay matrix (2000 models: half a
+            // millisecond, which this loop does not wait for)
+            if (n_res < most) {
+                if (__hip_atomic_load(&sc.ready, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP) == kScanLanes / 64)
+                    break;
+                changed(e);
+                continue;
+            }
             // ---- every device full (the only case left): arrivals up to the
             // next departure are deferred with an infinite mean (no device can
             // take them)
@@ -996,33 +1020,26 @@ __global__ __launch_bounds__(kPlaceThreads) void place_wave_kernel(
                 if (dep) break;
             }
             pf_v = -1;
-            nx_v = -1;
             e = e1;
         }
         if (e >= E) break;
-        // ---- a run of deferrals: the events after it, by all waves
         flush();
         sc.acc[lane] = racc;
-        sc.T[lane] = rTi;
-        sc.yT[lane] = rrT;
-        sc.yq[lane] = rrq;
         sc.r[lane] = r;
         sc.cnt[lane] = cnt;
-        sc.q[lane] = rq;
         if (lane == 0) {
             sc.stop[0] = 0x7fffffff;
             sc.e = e;
         }
         __syncthreads();
         const int32_t from = e;
-        e = scan_deferred<C, ISO>(sc, N, delay, iso, rT, rQ, q, s_rn, G, cap, E, events, lambda,
-                                  placed_device, placed_mu);
-        scan_after = e - from >= kScanAfter ? kScanAfter
-                                            : (2 * scan_after < kScanMost ? 2 * scan_after
-                                                                          : kScanMost);
-        deferred = 0;
+        e = await_scan(sc, e, scan_chunk(Gp));
+        if (e - from >= kScanAfter)
+            scan_after = scan_after > 4 ? scan_after / 4 : 1;
+        else
+            scan_after = 2 * scan_after < kScanMost ? 2 * scan_after : kScanMost;
+        changed(e);
         pf_v = -1;
-        nx_v = -1;
     }
     flush();
     dismiss();
