@@ -1592,10 +1592,11 @@ __device__ inline double from_order_key(uint64_t k)
 // so the loops stay rolled.  The maximum is taken with the members' range, and
 // the median by counting 8-bit digits from the highest bit in which two
 // members differ until at most 64 members share the digits so far (one or two
-// digits, mostly), which one wave ranks: a pair of 60-kernel models took 20 us
-// with the members compacted first and seven or eight byte-aligned digits, 13
-// us with the start pairs in registers of unrolled loops, 8.7 us now.
-constexpr int kReduceBlock = 1024, kReduceBatch = 4;
+// digits, mostly; none for 64 members or fewer), which one wave ranks: a pair of
+// 60-kernel models took 20 us with the members compacted first and seven or eight
+// byte-aligned digits, 13 us with the start pairs in registers of unrolled loops,
+// 8.7 us now.
+constexpr int kReduceBatch = 4;
 constexpr uint64_t kNoKey = ~0ull;
 
 struct ReduceScratch {
@@ -1643,11 +1644,12 @@ __device__ inline int32_t wave_scan(int32_t v)
     return v;
 }
 
-// The k-th smallest (0-based) of the workgroup's keys below kNoKey, and with
-// `two` the (k+1)-th (k + 1 below their number) in `next`.  mn and mx are the
+// The k-th smallest (0-based) of the n keys below kNoKey of the workgroup (B
+// lanes), and with `two` the (k+1)-th (k + 1 < n) in `next`.  mn and mx are the
 // smallest and the largest of them; sc's first histogram is clear.  Every thread
 // gets the result.
-__device__ inline uint64_t block_kth_key(const uint64_t* key, int32_t total, int32_t k,
+template <int B>
+__device__ inline uint64_t block_kth_key(const uint64_t* key, int32_t total, int32_t n, int32_t k,
                                          uint64_t mn, uint64_t mx, bool two, ReduceScratch& sc,
                                          uint64_t& next)
 {
@@ -1659,17 +1661,17 @@ __device__ inline uint64_t block_kth_key(const uint64_t* key, int32_t total, int
     // the bits above the first digit are common to every member
     uint64_t mask = shift == 56 ? 0 : ~0ull << (shift + 8);
     uint64_t prefix = mn & mask;
-    int32_t tie = 0;
-    for (int pass = 0;; ++pass) {
+    int32_t tie = n;   // members that share the digits so far
+    for (int pass = 0; tie > 64; ++pass) {
         int32_t* h = sc.hist[pass % 3];
 #pragma unroll 1
-        for (int32_t c = tid; c < total; c += kReduceBlock) {
+        for (int32_t c = tid; c < total; c += B) {
             const uint64_t x = key[c];
             if (x != kNoKey && (x & mask) == prefix) atomicAdd(&h[(x >> shift) & 0xff], 1);
         }
         // the next pass's histogram was last read two passes ago, before the
         // previous pass's barrier
-        if (tid < 256) sc.hist[(pass + 1) % 3][tid] = 0;
+        for (int t = tid; t < 256; t += B) sc.hist[(pass + 1) % 3][t] = 0;
         __syncthreads();
         // every wave finds the digit whose cumulative count spans rank k
         const int32_t c0 = h[4 * lane], c1 = h[4 * lane + 1], c2 = h[4 * lane + 2],
@@ -1686,7 +1688,7 @@ __device__ inline uint64_t block_kth_key(const uint64_t* key, int32_t total, int
         tie = __builtin_amdgcn_readlane(here, src);
         prefix |= (uint64_t)digit << shift;
         mask |= 0xffull << shift;
-        if (tie <= 64 || shift == 0) break;
+        if (shift == 0) break;
         shift = shift > 8 ? shift - 8 : 0;
     }
     // the members that share the digits, unless more than 64 share them all
@@ -1696,7 +1698,7 @@ __device__ inline uint64_t block_kth_key(const uint64_t* key, int32_t total, int
     const uint64_t top = prefix | ~mask;
     uint64_t up = kNoKey;
 #pragma unroll 1
-    for (int32_t c = tid; c < total; c += kReduceBlock) {
+    for (int32_t c = tid; c < total; c += B) {
         const uint64_t x = key[c];
         if (x == kNoKey) continue;
         if (ranked && (x & mask) == prefix) sc.list[atomicAdd(&sc.n_list, 1)] = x;
@@ -1737,7 +1739,8 @@ __device__ inline int32_t start_row(int32_t c, float r)
     return (int32_t)(((float)c + 0.5f) * r);
 }
 
-__global__ __launch_bounds__(kReduceBlock) void starts_reduce_kernel(SweepArgs g, int64_t n_pairs)
+template <int B>
+__global__ __launch_bounds__(B) void starts_reduce_kernel(SweepArgs g, int64_t n_pairs)
 {
     extern __shared__ uint64_t key[];   // starts_cap of them
     __shared__ ReduceScratch sc;
@@ -1757,12 +1760,12 @@ __global__ __launch_bounds__(kReduceBlock) void starts_reduce_kernel(SweepArgs g
                 if (g.slowdown) g.slowdown[p] = nan;
             }
             if (g.per_alignment)
-                for (int64_t c = tid; c < total64; c += kReduceBlock)
+                for (int64_t c = tid; c < total64; c += B)
                     g.per_alignment[(fa + c / qb) * nk + fb + c % qb] = nan;
             continue;
         }
         const int32_t total = (int32_t)total64;
-        if (tid < 256) sc.hist[0][tid] = 0;
+        for (int t = tid; t < 256; t += B) sc.hist[0][t] = 0;
         if (tid == 0) {
             sc.count = 0;
             sc.n_list = 0;
@@ -1777,17 +1780,17 @@ __global__ __launch_bounds__(kReduceBlock) void starts_reduce_kernel(SweepArgs g
         int32_t members = 0;
         double small = __builtin_nan(""), large = small;
 #pragma unroll 1
-        for (int32_t c0 = tid; c0 < total; c0 += kReduceBatch * kReduceBlock) {
+        for (int32_t c0 = tid; c0 < total; c0 += kReduceBatch * B) {
             // a batch's loads in flight before any value is used
             double v[kReduceBatch];
 #pragma unroll
             for (int u = 0; u < kReduceBatch; ++u) {
-                const int32_t c = c0 + u * kReduceBlock;
+                const int32_t c = c0 + u * B;
                 v[u] = g.starts[place(c < total ? c : c0)];
             }
 #pragma unroll
             for (int u = 0; u < kReduceBatch; ++u) {
-                const int32_t c = c0 + u * kReduceBlock;
+                const int32_t c = c0 + u * B;
                 if (c >= total) continue;
                 if (g.per_alignment) g.per_alignment[place(c)] = v[u];
                 const bool member = v[u] == v[u];
@@ -1820,7 +1823,7 @@ __global__ __launch_bounds__(kReduceBlock) void starts_reduce_kernel(SweepArgs g
                 D = m > 0.0 ? m : 0.0;
             } else {
                 uint64_t next;
-                const uint64_t mid = block_kth_key(key, total, (n - 1) / 2, mn, mx, (n & 1) == 0, sc, next);
+                const uint64_t mid = block_kth_key<B>(key, total, n, (n - 1) / 2, mn, mx, (n & 1) == 0, sc, next);
                 D = from_order_key(mid);
                 if ((n & 1) == 0) D = (D + from_order_key(next)) / 2.0;
             }
@@ -2467,14 +2470,16 @@ static hipError_t allow_lds(F kernel, size_t bytes)
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-// Workgroups for a one-pair-per-workgroup kernel that loops over pairs: the
-// dispatch holds fewer than 2^32 work-items; a multiple of 8 keeps every
-// pair on the XCD its first round put it on.
-static unsigned pair_grid(int64_t n_pairs)
+// Workgroups of `block` lanes for a one-pair-per-workgroup kernel that loops
+// over pairs: the dispatch holds fewer than 2^32 work-items; a multiple of 8
+// keeps every pair on the XCD its first round put it on.
+static constexpr unsigned pair_grid(int64_t n_pairs, int block)
 {
-    constexpr int64_t kMax = int64_t(1) << 22;
-    return (unsigned)(n_pairs < kMax ? n_pairs : kMax);
+    const int64_t most = (int64_t(1) << 31) / block;
+    return (unsigned)(n_pairs < most ? n_pairs : most);
 }
+static_assert((uint64_t)pair_grid(int64_t(1) << 40, 1024) * 1024 < (uint64_t(1) << 32),
+              "work-items of the largest dispatch");
 
 
 // One tile shape's kernel over all items: one workgroup per CU (it takes
@@ -2607,16 +2612,34 @@ hipError_t launch_sweep_starts(const SweepArgs& a, hipStream_t s)
     return launch_starts_group<64>(a, s);
 }
 
-hipError_t launch_starts_reduce(const SweepArgs& a, hipStream_t s)
+template <int B>
+static hipError_t launch_reduce_block(const SweepArgs& a, hipStream_t s)
 {
     const int64_t N = a.n_models;
     const int64_t n_pairs = N * N;
     const size_t lds = (size_t)a.starts_cap * sizeof(uint64_t);
-    const hipError_t e = allow_lds(starts_reduce_kernel, lds);
+    const hipError_t e = allow_lds(starts_reduce_kernel<B>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(starts_reduce_kernel, dim3(pair_grid(n_pairs)), dim3(kReduceBlock), lds, s,
-                       a, n_pairs);
+    hipLaunchKernelGGL(starts_reduce_kernel<B>, dim3(pair_grid(n_pairs, B)), dim3(B), lds, s, a,
+                       n_pairs);
     return hipGetLastError();
+}
+
+// Lanes per ordered pair, by the most start pairs a pair may have (q^2 for the
+// caller's bound q on a model's kernels).  A whole workgroup's chain of barriers
+// bounds a lone pair, the lanes that have no start pair of their own bound many
+// pairs; us a call with 64, 256 and 1024 lanes:
+//   1000 models of 2: 1627, 2916, 11585;  200 of 20: 476, 538, 1006;
+//   200 of 32: 1211, 1209, 1948;  60 of 50 (decode-like): 245, 209, 267;
+//   10 of 50: 50.0, 37.6, 35.7;  2 of 60: 46, 26, 22;
+//   60 of 90 (decode-like): 1081, 770, 764;  60 of 128: 5550, 4330, 3972.
+hipError_t launch_starts_reduce(const SweepArgs& a, hipStream_t s)
+{
+    const int64_t n_pairs = (int64_t)a.n_models * a.n_models;
+    if (a.starts_cap <= 512) return launch_reduce_block<64>(a, s);
+    if (a.starts_cap <= 1024 || (a.starts_cap <= 6400 && n_pairs >= 1024))
+        return launch_reduce_block<256>(a, s);
+    return launch_reduce_block<1024>(a, s);
 }
 
 hipError_t launch_offsets_reduce(const SweepArgs& a, hipStream_t s)
@@ -2626,8 +2649,8 @@ hipError_t launch_offsets_reduce(const SweepArgs& a, hipStream_t s)
     const size_t lds = (size_t)next_pow2((unsigned)a.num_offsets) * sizeof(double);
     hipError_t e = allow_lds(offsets_reduce_kernel, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(offsets_reduce_kernel, dim3(pair_grid(n_pairs)), dim3(kAlignBlock), lds, s,
-                       a, n_pairs);
+    hipLaunchKernelGGL(offsets_reduce_kernel, dim3(pair_grid(n_pairs, kAlignBlock)),
+                       dim3(kAlignBlock), lds, s, a, n_pairs);
     return hipGetLastError();
 }
 
@@ -2663,8 +2686,8 @@ hipError_t launch_sampled_reduce(const SweepArgs& a, hipStream_t s)
     const size_t lds = (size_t)next_pow2((unsigned)a.num_offsets) * sizeof(double);
     hipError_t e = allow_lds(sampled_reduce_kernel, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sampled_reduce_kernel, dim3(pair_grid(n_pairs)), dim3(kAlignBlock), lds, s,
-                       a, n_pairs);
+    hipLaunchKernelGGL(sampled_reduce_kernel, dim3(pair_grid(n_pairs, kAlignBlock)),
+                       dim3(kAlignBlock), lds, s, a, n_pairs);
     return hipGetLastError();
 }
 

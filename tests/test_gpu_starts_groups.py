@@ -33,6 +33,12 @@ CASES = {
     "sixteen-lanes-most": ([320, 51, 40], 320),        # pair cap 640, 320 x 51 start pairs
     "whole-wave": ([1000, 16, 15], 1000),
     "no-hint": ([60, 61, 3], 0),
+    # the reduction's lanes: 64 up to 512 start pairs a pair, 256 up to 1024 and for
+    # many pairs, 1024 beyond; 64 and 65 members are ranked and counted
+    "reduce-64": ([1, 8, 22, 0, 9, 16], 22),
+    "reduce-256": ([23, 32, 2, 13, 5], 32),
+    "reduce-256-many": ([33, 50, 1, 0, 13] + [3, 8, 5] * 9, 80),
+    "reduce-1024-few": ([33, 50, 1, 13], 80),
 }
 
 
@@ -82,3 +88,37 @@ def test_ties():
                     v = pa[off[i]:off[i + 1], off[j]:off[j + 1]].reshape(-1)
                     assert not np.isnan(v).any()
                     assert got["delay"][i, j] == (np.max(v) if red == "max" else np.median(v))
+
+
+@pytest.mark.parametrize("count", [1, 2, 63, 64, 65, 66, 127, 128, 300])
+def test_members_ranked_or_counted(count):
+    # one model of one kernel against `count` kernels that all interfere with it
+    L = library([1, count], seed=3)
+    L["grid"][:], L["threads"][:], L["regs"][:], L["smem"][:] = 4000, 1024, 40, 0
+    for hint in (count, 0):
+        for red in ("median", "max"):
+            got = gpu_pair(W.A100, L, align_mode=api.ALIGN_CONFLICT_STARTS, reduce_mode=red,
+                           max_kernels_per_model=hint, per_alignment=True)
+            v = got["per_alignment"].reshape(count + 1, count + 1)[0, 1:]
+            assert not np.isnan(v).any()
+            assert got["delay"][0, 1] == (np.max(v) if red == "max" else np.median(v))
+
+
+@pytest.mark.parametrize("sweep", ["temporal", "adjusted"])
+def test_many_models(sweep):
+    # 2,050^2 ordered pairs: more of them than workgroups of one dispatch
+    N = 2050
+    lengths = np.random.default_rng(8).integers(1, 3, N)
+    L = W.make_library(N, 2, "uniform", W.A100, seed=12)
+    take = np.concatenate([np.arange(n) + 2 * m for m, n in enumerate(lengths)])
+    for k in ("grid", "threads", "regs", "smem", "duration"):
+        L[k] = L[k][take]
+    L["offsets"] = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    mode = api.SWEEP_NAMES[sweep]
+    print("many models", sweep, flush=True)
+    want = oracle.pair_matrix(W.A100, L, align_mode=oracle.ALIGN_CONFLICT_STARTS, sweep_mode=mode)
+    for hint in (2, 0, 40):     # 64, 1024 and 256 lanes
+        got = gpu_pair(W.A100, L, align_mode=api.ALIGN_CONFLICT_STARTS, sweep_mode=mode,
+                       max_kernels_per_model=hint)
+        assert_rel(got["delay"], want["delay"], 1e-12, f"{sweep} {hint}")
+        assert_rel(got["slowdown"], want["slowdown"], 1e-12, f"{sweep} {hint}")
