@@ -53,6 +53,7 @@
 //    next one in flight while the current event is simulated.
 // Devices and tables beyond the usual form's range (sim_general) run the
 // same events with integer division constants and fp64 divisions.
+#include <algorithm>
 #include <type_traits>
 
 #include "rm_common.h"
@@ -515,6 +516,20 @@ __device__ inline void run_pair(int32_t N, int64_t x, int32_t& i, int32_t& j)
     }
 }
 
+// body(x, odd) for the runs x of this lane and its side of them; two lanes of a
+// run are neighbours.  A launch of few runs (AHEAD) has lanes for each.
+template <bool AHEAD, typename Body>
+__device__ inline void for_runs(int64_t n_runs, Body body)
+{
+    const int64_t lane = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (AHEAD) {
+        if (lane >> 1 < n_runs) body(lane >> 1, (bool)(threadIdx.x & 1));
+    } else {
+        for (int64_t x = lane >> 1; x < n_runs; x += ((int64_t)gridDim.x * blockDim.x) >> 1)
+            body(x, (bool)(threadIdx.x & 1));
+    }
+}
+
 // ---------------------------------------------------------------------------
 // FIRST: one run per pair of run_pair.
 // ---------------------------------------------------------------------------
@@ -522,22 +537,21 @@ template <int POLICY, typename KERNEL, bool AHEAD>
 __global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_first_kernel(SweepArgs g, int64_t n_runs)
 {
     if (KERNEL::kTable) build_quotients(g.max_beta);
-    const int64_t x = (int64_t)blockIdx.x * (blockDim.x >> 1) + (threadIdx.x >> 1);
-    if (x >= n_runs) return;
-    const bool odd = threadIdx.x & 1;
-    int32_t i, j;
-    run_pair<POLICY>(g.n_models, x, i, j);
-    const int32_t a = odd ? j : i, b = odd ? i : j;   // this side's model, the partner's
-    const ModelInfo ma = g.info[a], mb = g.info[b];
-    double D = 0.0;
-    if (ma.q > 0 && mb.q > 0)
-        D = run_side<POLICY, KERNEL, AHEAD>(g, ma, 0, g.sim[ma.first].d, kTogether);
-    // a self pair's two sides agree; under PRIORITY the odd side kept its blocks
-    if (odd && (POLICY == RM_POLICY_PRIORITY || i == j)) return;
-    const int64_t ab = (int64_t)a * g.n_models + b;
-    g.delay[ab] = D;
-    if (g.slowdown) g.slowdown[ab] = slowdown_of(D, ma.q, mb.q, ma.T);
-    if (g.per_alignment) g.per_alignment[ab] = D;
+    for_runs<AHEAD>(n_runs, [&](int64_t x, bool odd) {
+        int32_t i, j;
+        run_pair<POLICY>(g.n_models, x, i, j);
+        const int32_t a = odd ? j : i, b = odd ? i : j;   // this side's model, the partner's
+        const ModelInfo ma = g.info[a], mb = g.info[b];
+        double D = 0.0;
+        if (ma.q > 0 && mb.q > 0)
+            D = run_side<POLICY, KERNEL, AHEAD>(g, ma, 0, g.sim[ma.first].d, kTogether);
+        // a self pair's two sides agree; under PRIORITY the odd side kept its blocks
+        if (odd && (POLICY == RM_POLICY_PRIORITY || i == j)) return;
+        const int64_t ab = (int64_t)a * g.n_models + b;
+        g.delay[ab] = D;
+        if (g.slowdown) g.slowdown[ab] = slowdown_of(D, ma.q, mb.q, ma.T);
+        if (g.per_alignment) g.per_alignment[ab] = D;
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -550,49 +564,48 @@ template <int POLICY, typename KERNEL, bool AHEAD>
 __global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_offsets_kernel(SweepArgs g, int64_t n_runs)
 {
     if (KERNEL::kTable) build_quotients(g.max_beta);
-    const int64_t x = (int64_t)blockIdx.x * (blockDim.x >> 1) + (threadIdx.x >> 1);
-    if (x >= n_runs) return;
-    const bool odd = threadIdx.x & 1;
     const int64_t N = g.n_models;
     const int64_t NN = N * N;
     const int32_t K = g.num_offsets;
-    const int32_t r = (int32_t)(x / NN);
-    const int64_t p = x - (int64_t)r * NN;
-    const int32_t i = (int32_t)(p / N), j = (int32_t)(p - (int64_t)i * N);
-    const ModelInfo mi = g.info[i], mj = g.info[j];
-    double D = 0.0;
-    if (mi.q > 0 && mj.q > 0) {
-        const double tau = mi.T * (double)r / (double)K;
-        int32_t k = 0;
-        double ri = g.sim[mi.first].d;
-        bool i_first = false;
-        if (tau > 0.0) {
-            // kernels of i whose isolated interval ends by tau: P_i[k+1] <= tau
-            const Record* Pi = g.rec + mi.first;   // Pi[k].end = P_i[k+1]
-            int32_t lo = 0, hi = mi.q;
-            while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (Pi[mid].end <= tau)
-                    lo = mid + 1;
-                else
-                    hi = mid;
+    for_runs<AHEAD>(n_runs, [&](int64_t x, bool odd) {
+        const int32_t r = (int32_t)(x / NN);
+        const int64_t p = x - (int64_t)r * NN;
+        const int32_t i = (int32_t)(p / N), j = (int32_t)(p - (int64_t)i * N);
+        const ModelInfo mi = g.info[i], mj = g.info[j];
+        double D = 0.0;
+        if (mi.q > 0 && mj.q > 0) {
+            const double tau = mi.T * (double)r / (double)K;
+            int32_t k = 0;
+            double ri = g.sim[mi.first].d;
+            bool i_first = false;
+            if (tau > 0.0) {
+                // kernels of i whose isolated interval ends by tau: P_i[k+1] <= tau
+                const Record* Pi = g.rec + mi.first;   // Pi[k].end = P_i[k+1]
+                int32_t lo = 0, hi = mi.q;
+                while (lo < hi) {
+                    const int32_t mid = (lo + hi) >> 1;
+                    if (Pi[mid].end <= tau)
+                        lo = mid + 1;
+                    else
+                        hi = mid;
+                }
+                k = lo;
+                ri = k < mi.q ? Pi[k].end - tau : 0.0;
+                // kernel k started at P_i[k], before j's first kernel unless at tau
+                const double start_k = k > 0 ? Pi[k - 1].end : 0.0;
+                i_first = k < mi.q && start_k < tau;
             }
-            k = lo;
-            ri = k < mi.q ? Pi[k].end - tau : 0.0;
-            // kernel k started at P_i[k], before j's first kernel unless at tau
-            const double start_k = k > 0 ? Pi[k - 1].end : 0.0;
-            i_first = k < mi.q && start_k < tau;
+            if (k < mi.q) {
+                const int order = !i_first ? kTogether : odd ? kOtherFirst : kOwnFirst;
+                const double rj = g.sim[mj.first].d;
+                D = run_side<POLICY, KERNEL, AHEAD>(g, odd ? mj : mi, odd ? 0 : k, odd ? rj : ri,
+                                             order);
+            }
         }
-        if (k < mi.q) {
-            const int order = !i_first ? kTogether : odd ? kOtherFirst : kOwnFirst;
-            const double rj = g.sim[mj.first].d;
-            D = run_side<POLICY, KERNEL, AHEAD>(g, odd ? mj : mi, odd ? 0 : k, odd ? rj : ri,
-                                         order);
-        }
-    }
-    if (odd) return;
-    g.align_scratch[p * K + r] = D;
-    if (g.per_alignment) g.per_alignment[p * K + r] = D;
+        if (odd) return;
+        g.align_scratch[p * K + r] = D;
+        if (g.per_alignment) g.per_alignment[p * K + r] = D;
+    });
 }
 
 // Whether two kernels interfere (Eq. 2): their packed footprints, the device
@@ -647,31 +660,30 @@ __global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_sampled_kernel(Swe
                                                                 int64_t n_pairs)
 {
     if (KERNEL::kTable) build_quotients(g.max_beta);
-    const int64_t x = (int64_t)blockIdx.x * (blockDim.x >> 1) + (threadIdx.x >> 1);
-    if (x >= n_runs) return;
-    const bool odd = threadIdx.x & 1;
     const int64_t N = g.n_models;
     const int32_t K = g.num_offsets;
-    const int32_t r = (int32_t)(x / n_pairs);
-    int32_t i, j;
-    run_pair<POLICY>(g.n_models, x - (int64_t)r * n_pairs, i, j);
-    const ModelInfo mi = g.info[i], mj = g.info[j];
-    double D = __builtin_nan("");
-    if (mi.q > 0 && mj.q > 0) {
-        const int64_t lo = i < j ? i : j, hi = i < j ? j : i;
-        const uint64_t w = g.draws[(row_start(N, lo) + (hi - lo)) * K + r];
-        const uint32_t wi = i <= j ? (uint32_t)(w >> 32) : (uint32_t)w;
-        const uint32_t wj = i <= j ? (uint32_t)w : (uint32_t)(w >> 32);
-        const int32_t si = sampled_start(wi, mi.q), sj = sampled_start(wj, mj.q);
-        if (interfere(g, (int64_t)mi.first + si, (int64_t)mj.first + sj)) {
-            const int32_t k = odd ? sj : si;
-            const ModelInfo own = odd ? mj : mi;
-            D = run_side<POLICY, KERNEL, AHEAD>(g, own, k, g.sim[own.first + k].d, kTogether);
+    for_runs<AHEAD>(n_runs, [&](int64_t x, bool odd) {
+        const int32_t r = (int32_t)(x / n_pairs);
+        int32_t i, j;
+        run_pair<POLICY>(g.n_models, x - (int64_t)r * n_pairs, i, j);
+        const ModelInfo mi = g.info[i], mj = g.info[j];
+        double D = __builtin_nan("");
+        if (mi.q > 0 && mj.q > 0) {
+            const int64_t lo = i < j ? i : j, hi = i < j ? j : i;
+            const uint64_t w = g.draws[(row_start(N, lo) + (hi - lo)) * K + r];
+            const uint32_t wi = i <= j ? (uint32_t)(w >> 32) : (uint32_t)w;
+            const uint32_t wj = i <= j ? (uint32_t)w : (uint32_t)(w >> 32);
+            const int32_t si = sampled_start(wi, mi.q), sj = sampled_start(wj, mj.q);
+            if (interfere(g, (int64_t)mi.first + si, (int64_t)mj.first + sj)) {
+                const int32_t k = odd ? sj : si;
+                const ModelInfo own = odd ? mj : mi;
+                D = run_side<POLICY, KERNEL, AHEAD>(g, own, k, g.sim[own.first + k].d, kTogether);
+            }
         }
-    }
-    if (odd && (POLICY == RM_POLICY_PRIORITY || i == j)) return;
-    const int64_t a = odd ? j : i, b = odd ? i : j;
-    g.align_scratch[(a * N + b) * K + r] = D;
+        if (odd && (POLICY == RM_POLICY_PRIORITY || i == j)) return;
+        const int64_t a = odd ? j : i, b = odd ? i : j;
+        g.align_scratch[(a * N + b) * K + r] = D;
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -690,6 +702,7 @@ __global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_sampled_kernel(Swe
 // 2.81 ms with a table per wave.
 constexpr int64_t kAheadWaves = 5 * 256;
 constexpr size_t kAheadLds = 32 * 1024;
+constexpr int64_t kSimLanes = int64_t(1) << 31;   // of one dispatch, at most
 
 static size_t ahead_lds(const SweepArgs& a)
 {
@@ -720,14 +733,14 @@ static hipError_t pick_policy(const SweepArgs& a, Launch launch)
 }
 
 // launch(policy, kind of run, workgroups, lanes of one, LDS bytes) for n_runs
-// runs of two lanes.
+// runs of two lanes.  A dispatch holds fewer than 2^32 work-items; the workgroups
+// of a larger one loop over the runs.
 template <typename Launch>
 static hipError_t launch_runs(const SweepArgs& a, int64_t n_runs, Launch launch)
 {
     return pick_policy(a, [&](auto policy) {
         const auto with = [&](auto kind, int block, size_t lds) {
-            const int64_t blocks = (2 * n_runs + block - 1) / block;
-            if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+            const int64_t blocks = std::min((2 * n_runs + block - 1) / block, kSimLanes / block);
             return launch(policy, kind, dim3((unsigned)blocks), dim3((unsigned)block), lds);
         };
         if (a.sim_general) return with(GeneralRun{}, kSimBlock, 0);

@@ -101,3 +101,26 @@ def test_few_and_many_runs(models, policy):
     same(got["delay"], want["delay"], "delay")
     same(got["per_alignment"], want["delay"], "per alignment")
     same(got["slowdown"], want["slowdown"], "slowdown")
+
+
+def test_more_runs_than_lanes_of_a_dispatch():
+    # 520^2 ordered pairs of 4096 offsets are 1.1e9 runs of two lanes: more lanes
+    # than one dispatch takes.  Two kinds of models, so four kinds of pairs.
+    import torch
+    N, K = 520, 4096
+    two = library(W.A100, 2, 3, seed=21)
+    print("many runs", flush=True)
+    want = oracle.pair_matrix(W.A100, two, align_mode=api.ALIGN_OFFSETS, reduce_mode=oracle.REDUCE_MAX,
+                              num_offsets=K, sweep_mode=ADJ)
+    L = {k: np.tile(two[k], N // 2) for k in two if k != "offsets"}
+    L["offsets"] = np.arange(N + 1, dtype=np.int64) * 3
+    D = api.library_to_device(L)
+    out = dict(delay=torch.full((N * N,), -1.0, dtype=torch.float64, device="cuda"),
+               iso_time=torch.empty(N, dtype=torch.float64, device="cuda"),
+               kernel_count=torch.empty(N, dtype=torch.int32, device="cuda"))
+    got = api.rm_pair_slowdown_matrix(W.A100, D["offsets"], D["grid"], D["threads"], D["regs"],
+                                      D["smem"], D["duration"], align_mode="offsets",
+                                      reduce_mode="max", num_offsets=K, sweep_mode=ADJ, out=out)
+    torch.cuda.synchronize()
+    ref = torch.as_tensor(np.tile(np.asarray(want["delay"]).reshape(2, 2), (N // 2, N // 2))).cuda()
+    assert torch.equal(got["delay"].view(N, N), ref)
