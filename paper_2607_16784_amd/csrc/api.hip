@@ -279,8 +279,13 @@ int pair_matrix(const rm_device_desc* dev, int32_t n_models, const int64_t* kern
     rm::ModelInfo* info = reinterpret_cast<rm::ModelInfo*>(ws + L.info);
     rm::SimRecord* sim = adjusted ? reinterpret_cast<rm::SimRecord*>(ws + L.sim) : nullptr;
 
+    const bool many_alignments = opts->align_mode == RM_ALIGN_OFFSETS ||
+                                 opts->align_mode == RM_ALIGN_SAMPLED_STARTS;
+    const bool one_lane = rm::sim_one_lane(opts->policy, opts->align_mode, n_models,
+                                           many_alignments ? opts->num_offsets : 1);
     rm::SimForm form;
-    form.general = rm::sim_general(d, n_kernels);
+    form.general = rm::sim_general(d, n_kernels) ||
+                   (one_lane && opts->align_mode != RM_ALIGN_SAMPLED_STARTS);
     form.half = opts->policy == RM_POLICY_EQUAL;
     hipError_t e = rm::launch_prepare(d, pk, n_models, kernel_offsets, n_kernels, grid, threads,
                                       regs, smem, duration, records, sim, form, first,
@@ -320,6 +325,7 @@ int pair_matrix(const rm_device_desc* dev, int32_t n_models, const int64_t* kern
     a.policy = opts->policy;
     a.max_beta = rm::sim_max_beta(d);
     a.sim_general = form.general;
+    a.sim_one_lane = one_lane;
 
     if (opts->sweep_event_begin) {
         e = hipEventRecord((hipEvent_t)opts->sweep_event_begin, s);

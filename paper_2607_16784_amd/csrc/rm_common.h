@@ -38,8 +38,8 @@ static_assert(sizeof(ModelInfo) == 16, "ModelInfo must be 16 bytes");
 // One kernel as the adjusted-occupancy simulation sees it: its isolated
 // duration and, on the busiest SM, its resident blocks beta, its per-block
 // demands (W_b warps, R T registers, M shared bytes) and its footprint, in
-// one of two forms that the launcher picks by the device's capacities and the
-// table's size (sim_general).
+// one of two forms that the launcher picks by the device's capacities, the
+// table's size (sim_general) and the lanes of a run (sim_one_lane).
 // The usual form holds what an event needs ready to use, as floats:
 //   bytes   bits 0..7 beta, 8..15 2 left_w + 1, 16..23 left_b,
 //           24..31 max(beta, 1)
@@ -99,6 +99,16 @@ inline bool sim_general(const Desc& d, int64_t n_kernels)
 {
     return d.regs >= (1 << 22) - 1 || d.smem >= (1 << 22) - 1 || sim_max_beta(d) > 58 ||
            n_kernels > (int64_t(1) << 27) - 8;
+}
+
+// Whether the simulation of all pairs of n_models models, K runs each, takes one
+// lane a run: under PRIORITY, where the second lane would carry little, from so
+// many runs on that their lanes fill the chip (two lanes a run against one: 90,000
+// runs 98 and 128 us, 160,000 155 and 155 us, 360,000 177 and 160 us).
+inline bool sim_one_lane(int32_t policy, int32_t align_mode, int64_t n_models, int64_t K)
+{
+    return policy == RM_POLICY_PRIORITY && align_mode != RM_ALIGN_CONFLICT_STARTS &&
+           n_models * n_models > 250000 / K;
 }
 
 // Multiplier and shift that divide every integer n < 2^23 by x exactly:
@@ -204,6 +214,7 @@ struct SweepArgs {
     int32_t policy;          // RM_POLICY_* of the adjusted-occupancy simulation
     int32_t max_beta;        // most blocks a kernel can have on an SM
     bool sim_general;        // form of the SimRecords
+    bool sim_one_lane;       // one lane a run (sim_one_lane)
 };
 
 // *ok = the byte-addressed temporal sweep kernels declare no static LDS, so

@@ -52,7 +52,8 @@
 //  * Each lane streams its model's 32-byte records from memory in order, the
 //    next one in flight while the current event is simulated.
 // Devices and tables beyond the usual form's range (sim_general) run the
-// same events with integer division constants and fp64 divisions.
+// same events with integer division constants and reciprocals, and so do many
+// runs under PRIORITY, one lane each (simulate_victim).
 #include <algorithm>
 #include <type_traits>
 
@@ -113,6 +114,7 @@ __device__ inline double duration_of(Words lo)
 // no resident block, which never interferes) is {1, 1} throughout.
 typedef double Quotients __attribute__((ext_vector_type(2)));   // o/o~ and o~/o
 typedef __attribute__((address_space(3))) Quotients* LdsQuotients;
+typedef __attribute__((address_space(3))) double* LdsDouble;
 
 __host__ __device__ constexpr uint32_t quotient_row_bytes(uint32_t max_beta)
 {
@@ -201,56 +203,65 @@ struct PointerStream {
     __device__ Words hi() const { return at()[1]; }
 };
 
-// The running kernel of one side in the usual form.
+// The running kernel of one side in the usual form: blocks() counts the blocks
+// it keeps beside what its partner leaves (at least 1 for a kernel with no
+// resident block, which never interferes), entry() gives the quotients of that
+// count, of 0 (the two alternate) or of kWaits.
+constexpr uint32_t kWaits = ~0u;   // index -1
 struct ReadyKernel {
     static constexpr bool kTable = true;          // reads the table of quotients
+    static constexpr uint32_t kMany = 100;        // above the most blocks of a kernel
     using Stream = BufferStream;
     float inv_w, inv_r, inv_m;
     uint32_t beta;                                // the float's bits
     uint32_t left_w, left_r, left_m, left_b;      // floats' bits, for the partner
     uint32_t row;                                 // LDS address of its row of quotients
 
-    __device__ void set(Words lo, Words hi, uint32_t row_bytes)
+    static __device__ void build(int32_t max_beta) { build_quotients(max_beta); }
+
+    // What its own blocks need and what it leaves, of a record.
+    __device__ void set_own(Words lo, Words hi, uint32_t row_bytes)
     {
         const uint32_t bytes = lo.z;   // (converted, so copied)
         inv_w = float_of(taken(lo.w));
         inv_r = float_of(taken(hi.x));
         inv_m = float_of(taken(hi.y));
-        left_r = taken(hi.z);
-        left_m = taken(hi.w);
         beta = bits_of((float)(bytes >> 24));
-        left_w = bits_of((float)((bytes >> 8) & 0xffu));
-        left_b = bits_of((float)((bytes >> 16) & 0xffu));
         row = __umul24(bytes & 0xffu, row_bytes);
     }
+    static __device__ Words left_hi(const Stream& s) { return s.hi(); }
 
     template <int POLICY>
-    __device__ Quotients quotients(const SweepArgs& g, int order) const
+    __device__ void set_left(const SweepArgs&, Words lo, Words hi)
     {
-        uint32_t lw = other(left_w), lr = other(left_r), lm = other(left_m), lb = other(left_b);
-        if (POLICY == RM_POLICY_FCFS && order == kTogether) {
-            // equal partitioning: at least the upper half of each capacity
-            lw = max(lw, bits_of((float)(2u * (g.cap_w - g.cap_w / 2u) + 1u)));
-            lr = max(lr, bits_of((float)(g.cap_r - g.cap_r / 2u) + 0.5f));
-            lm = max(lm, bits_of((float)(g.cap_m - g.cap_m / 2u) + 0.5f));
-            lb = max(lb, bits_of((float)(g.cap_b - g.cap_b / 2u)));
-        }
+        const uint32_t bytes = lo.z;
+        left_r = taken(hi.z);
+        left_m = taken(hi.w);
+        left_w = bits_of((float)((bytes >> 8) & 0xffu));
+        left_b = bits_of((float)((bytes >> 16) & 0xffu));
+    }
+
+    // Equal partitioning: at least the upper half of each capacity is left.
+    static __device__ void at_least_half(const SweepArgs& g, uint32_t& lw, uint32_t& lr,
+                                         uint32_t& lm, uint32_t& lb)
+    {
+        lw = max(lw, bits_of((float)(2u * (g.cap_w - g.cap_w / 2u) + 1u)));
+        lr = max(lr, bits_of((float)(g.cap_r - g.cap_r / 2u) + 0.5f));
+        lm = max(lm, bits_of((float)(g.cap_m - g.cap_m / 2u) + 0.5f));
+        lb = max(lb, bits_of((float)(g.cap_b - g.cap_b / 2u)));
+    }
+
+    __device__ uint32_t blocks(uint32_t lw, uint32_t lr, uint32_t lm, uint32_t lb) const
+    {
         const uint32_t fit = min(min(bits_of(float_of(lw) * inv_w), bits_of(float_of(lr) * inv_r)),
                                  bits_of(float_of(lm) * inv_m));
-        const uint32_t v = min(min(beta, lb), fit);
-        uint32_t b = (uint32_t)float_of(v);
-        // together: alternating when either keeps no block (the factor, any
-        // above the table's most blocks, makes the partner's count a limit
-        // only when it is 0)
-        const uint32_t limit = (uint32_t)__umul24(other(b), 100u);
-        const uint32_t both = min(b, limit);
-        if (POLICY == RM_POLICY_EQUAL) {
-            b = both;
-        } else {
-            const uint32_t alone = b ? b : ~0u;   // index -1
-            const uint32_t own = (uint32_t)float_of(beta);
-            b = order == kOtherFirst ? alone : order == kOwnFirst ? own : both;
-        }
+        return (uint32_t)float_of(min(min(beta, lb), fit));
+    }
+
+    __device__ uint32_t all_blocks() const { return (uint32_t)float_of(beta); }
+
+    __device__ Quotients entry(uint32_t b) const
+    {
         return *(LdsQuotients)(size_t)(row + (b << 4) + 16u);
     }
 };
@@ -263,66 +274,126 @@ __device__ inline uint32_t fit(uint32_t left, uint32_t x, uint32_t mag, uint32_t
     return x ? q : none;
 }
 
-// The running kernel of one side in the general form.
+// The running kernel of one side in the general form.  The reciprocals 1 / n of
+// the block counts (at most 255) are at LDS address 0.
+constexpr size_t kReciprocalLds = 256 * sizeof(double);
 struct ShapeKernel {
     static constexpr bool kTable = false;
+    static constexpr uint32_t kMany = 256;
     using Stream = PointerStream;
-    uint32_t beta, wb, rt, m;
-    uint32_t fw, fr, fm;              // footprint: beta W_b warps, beta R T registers, beta M bytes
+    uint32_t beta, wb, rt, m;         // no demand of a kernel with no resident block
+    uint32_t left_w, left_r, left_m, left_b;
     uint32_t mag_wb, mag_rt, mag_m;   // division constants of the three demands
     uint32_t shifts;
 
-    __device__ void set(Words lo, Words hi, uint32_t)
+    static __device__ void build(int32_t)
     {
-        const uint64_t sh = ((uint64_t)taken(lo.w) << 32) | taken(lo.z);
+        static_assert(kSimBlock * sizeof(double) == kReciprocalLds, "one entry per lane");
+        *(LdsDouble)(size_t)(8u * threadIdx.x) = 1.0 / (double)(threadIdx.x ? threadIdx.x : 1u);
+        __syncthreads();
+    }
+    static __device__ double reciprocal(uint32_t n) { return *(LdsDouble)(size_t)(8u * n); }
+
+    static __device__ uint64_t shape_of(Words lo) { return ((uint64_t)lo.w << 32) | lo.z; }
+
+    __device__ void set_own(Words lo, Words hi, uint32_t)
+    {
+        const uint64_t sh = shape_of(lo);   // (taken apart, so copied)
         beta = (uint32_t)sh & 0xffu;
-        wb = (uint32_t)(sh >> 8) & 0xffu;
-        rt = (uint32_t)(sh >> 16) & 0xffffffu;
-        m = (uint32_t)(sh >> 40);
-        fw = beta * wb;
-        fr = beta * rt;
-        fm = beta * m;
+        wb = beta ? (uint32_t)(sh >> 8) & 0xffu : 0u;
+        rt = beta ? (uint32_t)(sh >> 16) & 0xffffffu : 0u;
+        m = beta ? (uint32_t)(sh >> 40) : 0u;
         mag_wb = taken(hi.x);
         mag_rt = taken(hi.y);
         mag_m = taken(hi.z);
         shifts = taken(hi.w);
     }
+    // (what it leaves follows from the first vector)
+    static __device__ Words left_hi(const Stream&) { return Words{0, 0, 0, 0}; }
 
     template <int POLICY>
-    __device__ Quotients quotients(const SweepArgs& g, int order) const
+    __device__ void set_left(const SweepArgs& g, Words lo, Words)
     {
-        const uint32_t cw = (uint32_t)g.cap_w, cr = (uint32_t)g.cap_r, cm = (uint32_t)g.cap_m,
-                       cb = (uint32_t)g.cap_b;
-        uint32_t ow = other(fw), orr = other(fr), om = other(fm), ob = other(beta);
-        // Eq. (2): the two kernels interfere when any resource overflows
-        const bool hit = (fw + ow > cw) | (fr + orr > cr) | (fm + om > cm) | (beta + ob > cb);
-        const bool together = POLICY == RM_POLICY_EQUAL || order == kTogether;
-        if (together) {   // the partner holds at most half of every resource
-            ow = min(ow, cw / 2u);
-            orr = min(orr, cr / 2u);
-            om = min(om, cm / 2u);
-            ob = min(ob, cb / 2u);
-        }
-        uint32_t b = min(beta, cb - ob);
-        b = min(b, fit(cw - ow, wb, mag_wb, shifts & 0xffu, b));
-        b = min(b, fit(cr - orr, rt, mag_rt, (shifts >> 8) & 0xffu, b));
-        b = min(b, fit(cm - om, m, mag_m, (shifts >> 16) & 0xffu, b));
-        const bool space = min(b, other(b)) >= 1u;
+        const uint64_t sh = shape_of(lo);
+        const uint32_t n = (uint32_t)sh & 0xffu;
+        // a kernel with resident blocks holds at most the capacities
+        left_w = (uint32_t)g.cap_w - n * ((uint32_t)(sh >> 8) & 0xffu);
+        left_r = (uint32_t)g.cap_r - n * ((uint32_t)(sh >> 16) & 0xffffffu);
+        left_m = (uint32_t)g.cap_m - n * (uint32_t)(sh >> 40);
+        left_b = (uint32_t)g.cap_b - n;
+        if (POLICY == RM_POLICY_EQUAL) at_least_half(g, left_w, left_r, left_m, left_b);
+    }
+
+    static __device__ void at_least_half(const SweepArgs& g, uint32_t& lw, uint32_t& lr,
+                                         uint32_t& lm, uint32_t& lb)
+    {
+        lw = max(lw, (uint32_t)(g.cap_w - g.cap_w / 2));
+        lr = max(lr, (uint32_t)(g.cap_r - g.cap_r / 2));
+        lm = max(lm, (uint32_t)(g.cap_m - g.cap_m / 2));
+        lb = max(lb, (uint32_t)(g.cap_b - g.cap_b / 2));
+    }
+
+    __device__ uint32_t blocks(uint32_t lw, uint32_t lr, uint32_t lm, uint32_t lb) const
+    {
+        uint32_t b = min(all_blocks(), lb);
+        b = min(b, fit(lw, wb, mag_wb, shifts & 0xffu, b));
+        b = min(b, fit(lr, rt, mag_rt, (shifts >> 8) & 0xffu, b));
+        return min(b, fit(lm, m, mag_m, (shifts >> 16) & 0xffu, b));
+    }
+
+    __device__ uint32_t all_blocks() const { return max(beta, 1u); }
+
+    __device__ Quotients entry(uint32_t b) const
+    {
+        const uint32_t n = min(b, 255u);
         Quotients e;
-        e.x = (double)beta / (double)b;
-        e.y = (double)b / (double)beta;
-        if (together && !space) {
+        e.x = div_by_recip((double)beta, (double)n, reciprocal(n));
+        e.y = div_by_recip((double)n, (double)beta, reciprocal(beta));
+        if (b == 0u) {
             e.x = 2.0;
             e.y = 0.5;
         }
-        if (!together && b == 0u) {
+        if (b == kWaits) {
             e.x = __builtin_inf();
             e.y = 0.0;
         }
-        if (!hit || (!together && order == kOwnFirst)) e.x = e.y = 1.0;
+        if (beta == 0u) e.x = e.y = 1.0;
         return e;
     }
 };
+
+// Both, of a whole record.
+template <int POLICY, typename KERNEL>
+__device__ inline void set_kernel(KERNEL& k, const SweepArgs& g, Words lo, Words hi,
+                                  uint32_t row_bytes)
+{
+    k.set_own(lo, hi, row_bytes);
+    k.template set_left<POLICY>(g, lo, hi);
+}
+
+// The quotients of this side's kernel beside the partner lane's.  Two kernels
+// that do not interfere (Eq. 2) need no test: what the partner leaves then holds
+// all beta blocks, and beta / beta = 1.
+template <int POLICY, typename KERNEL>
+__device__ inline Quotients quotients(const SweepArgs& g, const KERNEL& own, int order)
+{
+    uint32_t lw = other(own.left_w), lr = other(own.left_r), lm = other(own.left_m),
+             lb = other(own.left_b);
+    if (POLICY == RM_POLICY_FCFS && order == kTogether) KERNEL::at_least_half(g, lw, lr, lm, lb);
+    uint32_t b = own.blocks(lw, lr, lm, lb);
+    // together: alternating when either keeps no block (the factor makes the
+    // partner's count a limit only when it is 0)
+    const uint32_t limit = (uint32_t)__umul24(other(b), KERNEL::kMany);
+    const uint32_t both = min(b, limit);
+    if (POLICY == RM_POLICY_EQUAL) {
+        b = both;
+    } else {
+        const uint32_t alone = b ? b : kWaits;
+        const uint32_t all = own.all_blocks();   // (here: read in a branch it costs 10%)
+        b = order == kOtherFirst ? alone : order == kOwnFirst ? all : both;
+    }
+    return own.entry(b);
+}
 
 // min(x, y) of two times in one instruction; a NaN loses against a number,
 // as with fmin (the library minimum first quiets signalling NaNs, which
@@ -346,7 +417,7 @@ template <int POLICY, typename KERNEL>
 __device__ inline bool event(const SweepArgs& g, const KERNEL& own, double& r, double& delay,
                              int& order)
 {
-    const Quotients e = own.template quotients<POLICY>(g, order);
+    const Quotients e = quotients<POLICY>(g, own, order);
     const double t = r * e.x;          // wall time until this side's kernel completes
     const double to = other(t);
     // the stretch ends when the first kernel completes; the minimum and
@@ -376,7 +447,7 @@ __device__ inline double simulate(const SweepArgs& g, int32_t first, int32_t q, 
     const uint32_t row_bytes = quotient_row_bytes((uint32_t)g.max_beta);
     typename KERNEL::Stream stream(g, first, q, k);
     KERNEL own;
-    own.set(stream.lo(), stream.hi(), row_bytes);
+    set_kernel<POLICY>(own, g, stream.lo(), stream.hi(), row_bytes);
     stream.step();
     Words lo = stream.lo(), hi = stream.hi();   // the next kernel's record
     stream.step();
@@ -384,7 +455,7 @@ __device__ inline double simulate(const SweepArgs& g, int32_t first, int32_t q, 
     for (;;) {
         if (event<POLICY>(g, own, r, delay, order)) {
             r = duration_of(lo);
-            own.set(lo, hi, row_bytes);
+            set_kernel<POLICY>(own, g, lo, hi, row_bytes);
             __builtin_amdgcn_sched_barrier(0);   // the record has been read: load over it
             lo = stream.lo();
             hi = stream.hi();
@@ -431,7 +502,7 @@ __device__ inline double simulate_ahead(const SweepArgs& g, int32_t first, int32
     };
     BufferStream stream(g, first, q, k);
     ReadyKernel own;
-    own.set(stream.lo(), stream.hi(), row_bytes);
+    set_kernel<POLICY>(own, g, stream.lo(), stream.hi(), row_bytes);
     stream.step();
     Words lo = stream.lo(), hi = stream.hi();   // the next kernel's record
     stream.step();
@@ -468,7 +539,7 @@ __device__ inline double simulate_ahead(const SweepArgs& g, int32_t first, int32
             to[x] = spare;
             if (done) {
                 r = duration_of(lo);
-                own.set(lo, hi, row_bytes);
+                set_kernel<POLICY>(own, g, lo, hi, row_bytes);
                 __builtin_amdgcn_sched_barrier(0);   // the record has been read: read over it
                 lo = *(LdsWords)(size_t)slot;
                 hi = *(LdsWords)(size_t)(slot + kRingSlot);
@@ -489,67 +560,162 @@ __device__ inline double simulate_ahead(const SweepArgs& g, int32_t first, int32
     return result;
 }
 
-// A run's start on this lane's side, and the run.  PRIORITY: the odd lane's
-// kernels keep their blocks.  AHEAD: few runs (simulate_ahead).
-template <int POLICY, typename KERNEL, bool AHEAD = false>
-__device__ inline double run_side(const SweepArgs& g, const ModelInfo& own, int32_t k, double r,
-                                  int order)
+// PRIORITY with many runs (sim_one_lane): one lane a run.  Model j's kernels keep
+// all their blocks and their isolated speed, and only model i's delay is wanted,
+// so the second lane of a run would carry little: an event is what simulate()
+// does for the one side, and a step along j's isolated timeline.  The launch is
+// bound by the accesses of the lanes' record reads (address unit 80% busy, VALU
+// 30%): a wave's lanes share 16 models (run_pair), and in the general form a
+// kernel of model j is read with one access -- the float form's second access
+// costs more than its cheaper block counts save, but for sampled starts: 1000 x
+// 60 FIRST 291 us with two lanes a run, 257 us with one, 198 us in the general
+// form; 128 x 60 OFFSETS(64) 333, 296, 238 us; 128 x 50..500 sampled(64) 944, 851,
+// 1053 us.
+template <typename KERNEL>
+__device__ inline double simulate_victim(const SweepArgs& g, int32_t first_i, int32_t q_i,
+                                         int32_t k_i, double r, int32_t first_j, int32_t q_j,
+                                         int32_t k_j, double r_j)
 {
-    if (POLICY == RM_POLICY_PRIORITY) order = (threadIdx.x & 1) ? kOwnFirst : kOtherFirst;
-    if constexpr (AHEAD && KERNEL::kTable)
-        return simulate_ahead<POLICY>(g, own.first, own.q, k, r, order);
-    else
-        return simulate<POLICY, KERNEL>(g, own.first, own.q, k, r, order);
+    constexpr int kPolicy = RM_POLICY_PRIORITY;
+    const uint32_t row_bytes = quotient_row_bytes((uint32_t)g.max_beta);
+    typename KERNEL::Stream si(g, first_i, q_i, k_i), sj(g, first_j, q_j, k_j);
+    KERNEL own, first;
+    own.set_own(si.lo(), si.hi(), row_bytes);
+    first.template set_left<kPolicy>(g, sj.lo(), KERNEL::left_hi(sj));
+    si.step();
+    sj.step();
+    Words lo = si.lo(), hi = si.hi();        // the next kernels' records
+    Words lo_j = sj.lo(), hi_j = KERNEL::left_hi(sj);
+    si.step();
+    sj.step();
+    double delay = 0.0;
+    do {
+        const uint32_t b = own.blocks(first.left_w, first.left_r, first.left_m, first.left_b);
+        const Quotients e = own.entry(b ? b : kWaits);
+        const double t = r * e.x;   // wall time until i's kernel completes; j's: r_j
+        const double len = min_time(t, r_j);
+        const bool done = !(t > r_j), done_j = !(r_j > t);
+        const double w = len * e.y;
+        delay = delay + (len - (done ? r : w));
+        r = r - w;
+        r_j = r_j - len;
+        if (done) {
+            r = duration_of(lo);
+            own.set_own(lo, hi, row_bytes);
+            __builtin_amdgcn_sched_barrier(0);   // the record has been read: load over it
+            lo = si.lo();
+            hi = si.hi();
+            si.step();
+        }
+        if (done_j) {
+            r_j = duration_of(lo_j);
+            first.template set_left<kPolicy>(g, lo_j, hi_j);
+            __builtin_amdgcn_sched_barrier(0);
+            lo_j = sj.lo();
+            hi_j = KERNEL::left_hi(sj);
+            sj.step();
+        }
+    } while (!(si.done() || sj.done()));
+    return delay;
 }
 
-// Unordered pair x of the library under a symmetric policy (one run gives
-// both directions), ordered pair x under PRIORITY (the rule depends on the
-// roles: Delta_ij from the run in which model j's kernels keep their blocks).
-template <int POLICY>
-__device__ inline void run_pair(int32_t N, int64_t x, int32_t& i, int32_t& j)
+// How a launch runs: two lanes a run, two lanes a run with records requested
+// further ahead (few runs), or one lane a run (PRIORITY, many runs).
+constexpr int kTwoLanes = 0, kTwoAhead = 1, kOneLane = 2;
+
+// A run from kernel k_i of model i and kernel k_j of model j, both not begun, or
+// (BEGUN) with r_i isolated work left on model i's; the delay of this lane's side
+// (`odd`: model j's).  `order` is model i's.  PRIORITY: model j's kernels keep
+// their blocks.
+template <int POLICY, typename KERNEL, int MODE, bool BEGUN = false>
+__device__ inline double run(const SweepArgs& g, bool odd, const ModelInfo& mi, int32_t k_i,
+                             const ModelInfo& mj, int32_t k_j, int order, double r_i = 0.0)
 {
-    if (POLICY == RM_POLICY_PRIORITY) {
+    if constexpr (MODE == kOneLane) {
+        if (!BEGUN) r_i = g.sim[mi.first + k_i].d;
+        return simulate_victim<KERNEL>(g, mi.first, mi.q, k_i, r_i, mj.first, mj.q, k_j,
+                                       g.sim[mj.first + k_j].d);
+    } else {
+        if (POLICY == RM_POLICY_PRIORITY) order = kOtherFirst;
+        if (odd && order != kTogether) order = order == kOwnFirst ? kOtherFirst : kOwnFirst;
+        const int32_t first = odd ? mj.first : mi.first, q = odd ? mj.q : mi.q, k = odd ? k_j : k_i;
+        double r = g.sim[first + k].d;
+        if (BEGUN && !odd) r = r_i;
+        if constexpr (MODE == kTwoAhead)
+            return simulate_ahead<POLICY>(g, first, q, k, r, order);
+        else
+            return simulate<POLICY, KERNEL>(g, first, q, k, r, order);
+    }
+}
+
+// Pair x of a launch's pairs: all ordered pairs, or the unordered ones where a run
+// gives both directions (under PRIORITY the rule depends on the roles: Delta_ij
+// comes from the run in which model j's kernels keep their blocks).  With one lane
+// a run a wave takes a tile of 8 x 8 ordered pairs, so that it reads the records of
+// 16 models instead of 65; false for a pair of a tile past the last model.
+template <bool ORDERED, int MODE>
+__device__ inline bool run_pair(int32_t N, int64_t x, int32_t& i, int32_t& j)
+{
+    if (MODE == kOneLane) {
+        const int64_t tiles = (N + 7) / 8, t = x >> 6, row = t / tiles;
+        const int32_t l = (int32_t)(x & 63);
+        i = (int32_t)row * 8 + (l >> 3);
+        j = (int32_t)(t - row * tiles) * 8 + (l & 7);
+        return i < N && j < N;
+    }
+    if (ORDERED) {
         i = (int32_t)(x / N);
         j = (int32_t)(x - (int64_t)i * N);
     } else {
         row_pair_at(N, x, i, j);
     }
+    return true;
+}
+
+static int64_t run_pairs(int64_t N, bool ordered, int mode)
+{
+    const int64_t tiles = (N + 7) / 8;
+    return mode == kOneLane ? tiles * tiles * 64 : ordered ? N * N : N * (N + 1) / 2;
 }
 
 // body(x, odd) for the runs x of this lane and its side of them; two lanes of a
-// run are neighbours.  A launch of few runs (AHEAD) has lanes for each.
-template <bool AHEAD, typename Body>
+// run are neighbours.  A launch of few runs (kTwoAhead) has lanes for each.
+template <int MODE, typename Body>
 __device__ inline void for_runs(int64_t n_runs, Body body)
 {
     const int64_t lane = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (AHEAD) {
+    const int64_t lanes = (int64_t)gridDim.x * blockDim.x;
+    if (MODE == kTwoAhead) {
         if (lane >> 1 < n_runs) body(lane >> 1, (bool)(threadIdx.x & 1));
-    } else {
-        for (int64_t x = lane >> 1; x < n_runs; x += ((int64_t)gridDim.x * blockDim.x) >> 1)
+    } else if (MODE == kTwoLanes) {
+        for (int64_t x = lane >> 1; x < n_runs; x += lanes >> 1)
             body(x, (bool)(threadIdx.x & 1));
+    } else {
+        for (int64_t x = lane; x < n_runs; x += lanes) body(x, false);
     }
 }
 
 // ---------------------------------------------------------------------------
 // FIRST: one run per pair of run_pair.
 // ---------------------------------------------------------------------------
-template <int POLICY, typename KERNEL, bool AHEAD>
-__global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_first_kernel(SweepArgs g, int64_t n_runs)
+template <int POLICY, typename KERNEL, int MODE>
+__global__ __launch_bounds__(MODE == kTwoAhead ? 64 : kSimBlock) void sim_first_kernel(SweepArgs g, int64_t n_runs)
 {
-    if (KERNEL::kTable) build_quotients(g.max_beta);
-    for_runs<AHEAD>(n_runs, [&](int64_t x, bool odd) {
+    KERNEL::build(g.max_beta);
+    for_runs<MODE>(n_runs, [&](int64_t x, bool odd) {
         int32_t i, j;
-        run_pair<POLICY>(g.n_models, x, i, j);
-        const int32_t a = odd ? j : i, b = odd ? i : j;   // this side's model, the partner's
-        const ModelInfo ma = g.info[a], mb = g.info[b];
+        if (!run_pair<POLICY == RM_POLICY_PRIORITY, MODE>(g.n_models, x, i, j)) return;
+        const ModelInfo mi = g.info[i], mj = g.info[j];
         double D = 0.0;
-        if (ma.q > 0 && mb.q > 0)
-            D = run_side<POLICY, KERNEL, AHEAD>(g, ma, 0, g.sim[ma.first].d, kTogether);
+        if (mi.q > 0 && mj.q > 0)
+            D = run<POLICY, KERNEL, MODE>(g, odd, mi, 0, mj, 0, kTogether);
         // a self pair's two sides agree; under PRIORITY the odd side kept its blocks
         if (odd && (POLICY == RM_POLICY_PRIORITY || i == j)) return;
+        const int32_t a = odd ? j : i, b = odd ? i : j;   // this side's model, the partner's
         const int64_t ab = (int64_t)a * g.n_models + b;
         g.delay[ab] = D;
-        if (g.slowdown) g.slowdown[ab] = slowdown_of(D, ma.q, mb.q, ma.T);
+        if (g.slowdown)
+            g.slowdown[ab] = slowdown_of(D, odd ? mj.q : mi.q, odd ? mi.q : mj.q, odd ? mj.T : mi.T);
         if (g.per_alignment) g.per_alignment[ab] = D;
     });
 }
@@ -560,17 +726,17 @@ __global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_first_kernel(Sweep
 // a wave share r and have windows of similar length.  Model i runs alone
 // until tau: its kernel running at tau keeps P_i[k+1] - tau of work.
 // ---------------------------------------------------------------------------
-template <int POLICY, typename KERNEL, bool AHEAD>
-__global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_offsets_kernel(SweepArgs g, int64_t n_runs)
+template <int POLICY, typename KERNEL, int MODE>
+__global__ __launch_bounds__(MODE == kTwoAhead ? 64 : kSimBlock) void sim_offsets_kernel(SweepArgs g, int64_t n_runs,
+                                                                int64_t n_pairs)
 {
-    if (KERNEL::kTable) build_quotients(g.max_beta);
-    const int64_t N = g.n_models;
-    const int64_t NN = N * N;
+    KERNEL::build(g.max_beta);
     const int32_t K = g.num_offsets;
-    for_runs<AHEAD>(n_runs, [&](int64_t x, bool odd) {
-        const int32_t r = (int32_t)(x / NN);
-        const int64_t p = x - (int64_t)r * NN;
-        const int32_t i = (int32_t)(p / N), j = (int32_t)(p - (int64_t)i * N);
+    for_runs<MODE>(n_runs, [&](int64_t x, bool odd) {
+        const int32_t r = (int32_t)(x / n_pairs);
+        int32_t i, j;
+        if (!run_pair<true, MODE>(g.n_models, x - (int64_t)r * n_pairs, i, j)) return;
+        const int64_t p = (int64_t)i * g.n_models + j;
         const ModelInfo mi = g.info[i], mj = g.info[j];
         double D = 0.0;
         if (mi.q > 0 && mj.q > 0) {
@@ -595,12 +761,9 @@ __global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_offsets_kernel(Swe
                 const double start_k = k > 0 ? Pi[k - 1].end : 0.0;
                 i_first = k < mi.q && start_k < tau;
             }
-            if (k < mi.q) {
-                const int order = !i_first ? kTogether : odd ? kOtherFirst : kOwnFirst;
-                const double rj = g.sim[mj.first].d;
-                D = run_side<POLICY, KERNEL, AHEAD>(g, odd ? mj : mi, odd ? 0 : k, odd ? rj : ri,
-                                             order);
-            }
+            if (k < mi.q)
+                D = run<POLICY, KERNEL, MODE, true>(g, odd, mi, k, mj, 0,
+                                                    i_first ? kOwnFirst : kTogether, ri);
         }
         if (odd) return;
         g.align_scratch[p * K + r] = D;
@@ -624,7 +787,7 @@ __device__ inline bool interfere(const SweepArgs& g, int64_t u, int64_t v)
 template <int POLICY, typename KERNEL>
 __global__ __launch_bounds__(kSimBlock) void sim_starts_kernel(SweepArgs g, int64_t n_pairs)
 {
-    if (KERNEL::kTable) build_quotients(g.max_beta);
+    KERNEL::build(g.max_beta);
     const bool odd = threadIdx.x & 1;
     const int64_t N = g.n_models;
     const int64_t nk = g.n_kernels;
@@ -638,9 +801,7 @@ __global__ __launch_bounds__(kSimBlock) void sim_starts_kernel(SweepArgs g, int6
             const int32_t si = (int32_t)(c / mj.q), sj = (int32_t)(c - (int64_t)si * mj.q);
             double v = __builtin_nan("");
             if (interfere(g, (int64_t)mi.first + si, (int64_t)mj.first + sj)) {
-                const int32_t k = odd ? sj : si;
-                const ModelInfo own = odd ? mj : mi;
-                v = run_side<POLICY, KERNEL>(g, own, k, g.sim[own.first + k].d, kTogether);
+                v = run<POLICY, KERNEL, kTwoLanes>(g, odd, mi, si, mj, sj, kTogether);
             }
             if (!odd) g.starts[((int64_t)mi.first + si) * nk + mj.first + sj] = v;
         }
@@ -655,17 +816,18 @@ __global__ __launch_bounds__(kSimBlock) void sim_starts_kernel(SweepArgs g, int6
 // pair, so the runs of a wave share r.  The per-draw delays go to
 // align_scratch ([ordered pair][r]) for the reduction kernel.
 // ---------------------------------------------------------------------------
-template <int POLICY, typename KERNEL, bool AHEAD>
-__global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_sampled_kernel(SweepArgs g, int64_t n_runs,
+template <int POLICY, typename KERNEL, int MODE>
+__global__ __launch_bounds__(MODE == kTwoAhead ? 64 : kSimBlock) void sim_sampled_kernel(SweepArgs g, int64_t n_runs,
                                                                 int64_t n_pairs)
 {
-    if (KERNEL::kTable) build_quotients(g.max_beta);
+    KERNEL::build(g.max_beta);
     const int64_t N = g.n_models;
     const int32_t K = g.num_offsets;
-    for_runs<AHEAD>(n_runs, [&](int64_t x, bool odd) {
+    for_runs<MODE>(n_runs, [&](int64_t x, bool odd) {
         const int32_t r = (int32_t)(x / n_pairs);
         int32_t i, j;
-        run_pair<POLICY>(g.n_models, x - (int64_t)r * n_pairs, i, j);
+        if (!run_pair<POLICY == RM_POLICY_PRIORITY, MODE>(g.n_models, x - (int64_t)r * n_pairs, i, j))
+            return;
         const ModelInfo mi = g.info[i], mj = g.info[j];
         double D = __builtin_nan("");
         if (mi.q > 0 && mj.q > 0) {
@@ -675,9 +837,7 @@ __global__ __launch_bounds__(AHEAD ? 64 : kSimBlock) void sim_sampled_kernel(Swe
             const uint32_t wj = i <= j ? (uint32_t)w : (uint32_t)(w >> 32);
             const int32_t si = sampled_start(wi, mi.q), sj = sampled_start(wj, mj.q);
             if (interfere(g, (int64_t)mi.first + si, (int64_t)mj.first + sj)) {
-                const int32_t k = odd ? sj : si;
-                const ModelInfo own = odd ? mj : mi;
-                D = run_side<POLICY, KERNEL, AHEAD>(g, own, k, g.sim[own.first + k].d, kTogether);
+                D = run<POLICY, KERNEL, MODE>(g, odd, mi, si, mj, sj, kTogether);
             }
         }
         if (odd && (POLICY == RM_POLICY_PRIORITY || i == j)) return;
@@ -709,17 +869,10 @@ static size_t ahead_lds(const SweepArgs& a)
     return (size_t)quotient_bytes((uint32_t)a.max_beta) + kRingBytes;
 }
 
-struct PlainRun {
-    using Kernel = ReadyKernel;
-    static constexpr bool kAhead = false;
-};
-struct AheadRun {
-    using Kernel = ReadyKernel;
-    static constexpr bool kAhead = true;
-};
-struct GeneralRun {
-    using Kernel = ShapeKernel;
-    static constexpr bool kAhead = false;
+template <typename KERNEL, int MODE>
+struct RunKind {
+    using Kernel = KERNEL;
+    static constexpr int kMode = MODE;
 };
 
 template <typename Launch>
@@ -732,66 +885,74 @@ static hipError_t pick_policy(const SweepArgs& a, Launch launch)
     }
 }
 
-// launch(policy, kind of run, workgroups, lanes of one, LDS bytes) for n_runs
-// runs of two lanes.  A dispatch holds fewer than 2^32 work-items; the workgroups
+// launch(policy, kind of run, workgroups, lanes of one, LDS bytes, runs, pairs) for
+// K runs of each pair.  A dispatch holds fewer than 2^32 work-items; the workgroups
 // of a larger one loop over the runs.
 template <typename Launch>
-static hipError_t launch_runs(const SweepArgs& a, int64_t n_runs, Launch launch)
+static hipError_t launch_runs(const SweepArgs& a, bool ordered, int64_t K, Launch launch)
 {
     return pick_policy(a, [&](auto policy) {
         const auto with = [&](auto kind, int block, size_t lds) {
-            const int64_t blocks = std::min((2 * n_runs + block - 1) / block, kSimLanes / block);
-            return launch(policy, kind, dim3((unsigned)blocks), dim3((unsigned)block), lds);
+            constexpr int kMode = decltype(kind)::kMode;
+            const int64_t n_pairs = run_pairs(a.n_models, ordered, kMode), n_runs = n_pairs * K;
+            const int64_t lanes = kMode == kOneLane ? n_runs : 2 * n_runs;
+            const int64_t blocks = std::min((lanes + block - 1) / block, kSimLanes / block);
+            return launch(policy, kind, dim3((unsigned)blocks), dim3((unsigned)block), lds, n_runs,
+                          n_pairs);
         };
-        if (a.sim_general) return with(GeneralRun{}, kSimBlock, 0);
+        const int64_t n_runs = run_pairs(a.n_models, ordered, kTwoLanes) * K;
+        const size_t table = quotient_bytes((uint32_t)a.max_beta);
+        if constexpr (decltype(policy)::value == RM_POLICY_PRIORITY) {
+            if (a.sim_one_lane)
+                return a.sim_general
+                           ? with(RunKind<ShapeKernel, kOneLane>{}, kSimBlock, kReciprocalLds)
+                           : with(RunKind<ReadyKernel, kOneLane>{}, kSimBlock, table);
+        }
+        if (a.sim_general)
+            return with(RunKind<ShapeKernel, kTwoLanes>{}, kSimBlock, kReciprocalLds);
         if (2 * n_runs <= kAheadWaves * 64 && ahead_lds(a) <= kAheadLds)
-            return with(AheadRun{}, 64, ahead_lds(a));
-        return with(PlainRun{}, kSimBlock, (size_t)quotient_bytes((uint32_t)a.max_beta));
+            return with(RunKind<ReadyKernel, kTwoAhead>{}, 64, ahead_lds(a));
+        return with(RunKind<ReadyKernel, kTwoLanes>{}, kSimBlock, table);
     });
-}
-
-// Pairs of run_pair.
-static int64_t n_run_pairs(const SweepArgs& a)
-{
-    const int64_t N = a.n_models;
-    return a.policy == RM_POLICY_PRIORITY ? N * N : N * (N + 1) / 2;
 }
 
 hipError_t launch_sim_first(const SweepArgs& a, hipStream_t s)
 {
-    const int64_t n_runs = n_run_pairs(a);
-    return launch_runs(a, n_runs, [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds) {
-        using K = decltype(kind);
-        hipLaunchKernelGGL((sim_first_kernel<decltype(policy)::value, typename K::Kernel, K::kAhead>),
-                           blocks, block, lds, s, a, n_runs);
-        return hipGetLastError();
-    });
+    return launch_runs(a, a.policy == RM_POLICY_PRIORITY, 1,
+                       [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds,
+                           int64_t n_runs, int64_t) {
+                           using K = decltype(kind);
+                           hipLaunchKernelGGL((sim_first_kernel<decltype(policy)::value,
+                                                                typename K::Kernel, K::kMode>),
+                                              blocks, block, lds, s, a, n_runs);
+                           return hipGetLastError();
+                       });
 }
 
 hipError_t launch_sim_offsets(const SweepArgs& a, hipStream_t s)
 {
-    const int64_t N = a.n_models;
-    const int64_t n_runs = N * N * a.num_offsets;
-    return launch_runs(a, n_runs, [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds) {
-        using K = decltype(kind);
-        hipLaunchKernelGGL(
-            (sim_offsets_kernel<decltype(policy)::value, typename K::Kernel, K::kAhead>), blocks,
-            block, lds, s, a, n_runs);
-        return hipGetLastError();
-    });
+    return launch_runs(a, true, a.num_offsets,
+                       [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds,
+                           int64_t n_runs, int64_t n_pairs) {
+                           using K = decltype(kind);
+                           hipLaunchKernelGGL((sim_offsets_kernel<decltype(policy)::value,
+                                                                  typename K::Kernel, K::kMode>),
+                                              blocks, block, lds, s, a, n_runs, n_pairs);
+                           return hipGetLastError();
+                       });
 }
 
 hipError_t launch_sim_sampled(const SweepArgs& a, hipStream_t s)
 {
-    const int64_t n_pairs = n_run_pairs(a);
-    const int64_t n_runs = n_pairs * a.num_offsets;
-    return launch_runs(a, n_runs, [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds) {
-        using K = decltype(kind);
-        hipLaunchKernelGGL(
-            (sim_sampled_kernel<decltype(policy)::value, typename K::Kernel, K::kAhead>), blocks,
-            block, lds, s, a, n_runs, n_pairs);
-        return hipGetLastError();
-    });
+    return launch_runs(a, a.policy == RM_POLICY_PRIORITY, a.num_offsets,
+                       [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds,
+                           int64_t n_runs, int64_t n_pairs) {
+                           using K = decltype(kind);
+                           hipLaunchKernelGGL((sim_sampled_kernel<decltype(policy)::value,
+                                                                  typename K::Kernel, K::kMode>),
+                                              blocks, block, lds, s, a, n_runs, n_pairs);
+                           return hipGetLastError();
+                       });
 }
 
 hipError_t launch_sim_starts(const SweepArgs& a, hipStream_t s)
@@ -804,7 +965,7 @@ hipError_t launch_sim_starts(const SweepArgs& a, hipStream_t s)
         constexpr int kPolicy = decltype(policy)::value;
         if (a.sim_general)
             hipLaunchKernelGGL((sim_starts_kernel<kPolicy, ShapeKernel>), dim3(blocks),
-                               dim3(kSimBlock), 0, s, a, n_pairs);
+                               dim3(kSimBlock), kReciprocalLds, s, a, n_pairs);
         else
             hipLaunchKernelGGL((sim_starts_kernel<kPolicy, ReadyKernel>), dim3(blocks),
                                dim3(kSimBlock), quotient_bytes((uint32_t)a.max_beta), s, a,

@@ -103,6 +103,37 @@ def test_few_and_many_runs(models, policy):
     same(got["slowdown"], want["slowdown"], "slowdown")
 
 
+@pytest.mark.parametrize("name", ["a100", "general-blocks"])
+def test_priority_one_lane(name):
+    # more than 250,000 runs under PRIORITY take one lane each, in tiles of 8 x 8
+    # ordered pairs: model counts on and beside a multiple of 8, a bound on the
+    # number of offsets or draws at which the rule turns, invalid and empty models
+    device = W.A100 if name == "a100" else DEVICES[name]
+    pol = api.POLICY_NAMES["priority"]
+    for models, align, K in ((500, "first", 1), (501, "first", 1), (504, "first", 1),
+                             (62, "offsets", 66), (63, "offsets", 63), (64, "offsets", 62),
+                             (63, "sampled_starts", 64), (1, "offsets", 4096)):
+        L = library(device, models, 6, seed=models + K)
+        lens = np.random.default_rng(2).integers(0, 7, models)
+        take = np.concatenate([np.arange(n) + 6 * m for m, n in enumerate(lens)])
+        for k in ("grid", "threads", "regs", "smem", "duration"):
+            L[k] = L[k][take]
+        L["offsets"] = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        am = api.ALIGN_NAMES[align]
+        print("one lane", name, models, align, K, flush=True)
+        kw, gk = {}, {}
+        if align == "sampled_starts":
+            import torch
+            draws = W.start_draws(models, K, seed=3)
+            kw, gk = dict(start_draws=draws), dict(start_draws=torch.as_tensor(draws.reshape(-1)).cuda())
+        want = oracle.pair_matrix(device, L, align_mode=am, num_offsets=K, sweep_mode=ADJ,
+                                  policy=pol, **kw)
+        got = gpu_pair(device, L, align_mode=am, num_offsets=K, sweep_mode=ADJ, policy=pol, **gk)
+        same(got["delay"], want["delay"], f"{align} delay")
+        same(got["slowdown"], want["slowdown"], f"{align} slowdown")
+        assert got["status"] == want["status"]
+
+
 def test_more_runs_than_lanes_of_a_dispatch():
     # 520^2 ordered pairs of 4096 offsets are 1.1e9 runs of two lanes: more lanes
     # than one dispatch takes.  Two kinds of models, so four kinds of pairs.
