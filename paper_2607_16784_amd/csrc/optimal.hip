@@ -45,7 +45,8 @@ constexpr int kOptBlock = 256, kCostBlock = 64;
 // Every lane of a mask unranks it, so more lanes add more work than they
 // share: 24 models on 8 GPUs of 3 take 0.118 ms so, 0.16 ms with half as
 // many, 0.131 ms with twice and 0.147 ms with four times as many (1.18 ms
-// with every mask of a layer's popcounts, one lane each).
+// with every mask of a layer's popcounts, one lane each).  A layer of more masks
+// than that has min_log2_lanes of them.
 constexpr int64_t kLayerLanes = 256 * 4 * 2 * 64;
 
 // Binomial coefficient C(x, y) for 0 <= y <= 4, 0 <= x <= 31 (closed forms
@@ -524,6 +525,21 @@ __global__ __launch_bounds__(64) void finish_kernel(OptArgs a, LayerPlan prev)
     if (lane < n) a.best_device[lane] = device;
 }
 
+// Lanes of a mask, at least: so many that a workgroup's member tables and lists
+// stay within 64 KB of LDS, which every launch may take and which leaves two or
+// three workgroups a CU (two lanes a mask at capacity 3, four at capacity 4).
+// Twice and four times as many lanes: 24 models on 9 GPUs of 3 0.221, 0.249, 0.267
+// ms; on 12 of 3 0.57, 0.62, 0.68; on 6 of 4 0.292, 0.302, 0.339; on 12 of 4 5.27,
+// 5.22, 6.30; 20 on 8 of 4 0.310, 0.282, 0.306 (one lane a mask of all popcounts:
+// 4.57, 14.9, 3.62, 82.9, 2.34 ms).
+template <int C>
+constexpr int32_t min_log2_lanes()
+{
+    int32_t l = 0;
+    while ((kOptBlock >> l) * sizeof(Members<C>) + sizeof(LdsTables<C>) > 65536) ++l;
+    return l;
+}
+
 // Layers 2 .. G - 1 and the finish, for capacity C.
 template <int C>
 static hipError_t launch_layers(const OptArgs& a, LayerPlan prev, hipStream_t s)
@@ -532,7 +548,7 @@ static hipError_t launch_layers(const OptArgs& a, LayerPlan prev, hipStream_t s)
         const LayerPlan plan = layer_plan(k, a.n, C, a.G);
         const int32_t masks = plan.start[a.n + 1];
         if (masks > 0) {
-            int32_t log2_lanes = 0;
+            int32_t log2_lanes = min_log2_lanes<C>();
             while (log2_lanes < 6 && ((int64_t)masks << log2_lanes) < kLayerLanes) ++log2_lanes;
             const int64_t lanes = (int64_t)masks << log2_lanes;
             hipLaunchKernelGGL(layer_kernel<C>,
