@@ -286,8 +286,8 @@ size_t rm_pair_workspace_bytes(int32_t n_models, int64_t n_kernels,
  *   range, max_kernels_per_model < 0), RM_EWORKSPACE,
  *   RM_EUNSUPPORTED (descriptor, n_models > RM_MAX_MODELS or
  *   n_kernels >= 2^31, RM_SWEEP_LOCKSTEP, or a library build whose
- *   byte-addressed sweep kernels declare static LDS -- they need their
- *   dynamic LDS to start at address 0; checked once per process),
+ *   byte-addressed sweep or simulation kernels declare static LDS -- they
+ *   need their dynamic LDS to start at address 0; checked once per process),
  *   RM_ELAUNCH.
  */
 int rm_pair_slowdown_matrix(const rm_device_desc* dev, int32_t n_models,

@@ -97,8 +97,8 @@ bool opts_ok(const rm_pair_opts* o)
     return true;
 }
 
-// Limits of the adjusted-occupancy simulation: block counts index a
-// 256-entry reciprocal table, and capacities and per-block demands stay
+// Limits of the adjusted-occupancy simulation: block counts index the general
+// form's 256-entry reciprocal table, and capacities and per-block demands stay
 // below 2^23 so every packed field and 32-bit quotient is exact.
 bool adjusted_ok(const rm_device_desc* d)
 {
@@ -265,12 +265,10 @@ int pair_matrix(const rm_device_desc* dev, int32_t n_models, const int64_t* kern
     const rm::Desc d = to_desc(dev);
     rm::Packing pk;
     if (!rm::make_packing(d, &pk)) return RM_EUNSUPPORTED;
-    if (!adjusted) {
-        bool lds_ok = false;
-        const hipError_t le = rm::sweep_lds_from_zero(&lds_ok);
-        if (le != hipSuccess) return launch_failed(le);
-        if (!lds_ok) return RM_EUNSUPPORTED;
-    }
+    bool lds_ok = false;
+    const hipError_t le = adjusted ? rm::sim_lds_from_zero(&lds_ok) : rm::sweep_lds_from_zero(&lds_ok);
+    if (le != hipSuccess) return launch_failed(le);
+    if (!lds_ok) return RM_EUNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
     char* ws = static_cast<char*>(workspace);
     rm::Record* records = reinterpret_cast<rm::Record*>(ws + L.records);

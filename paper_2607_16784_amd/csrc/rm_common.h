@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
 
@@ -217,9 +218,30 @@ struct SweepArgs {
     bool sim_one_lane;       // one lane a run (sim_one_lane)
 };
 
-// *ok = the byte-addressed temporal sweep kernels declare no static LDS, so
-// their dynamic LDS starts at address 0.
+// Kernels that address LDS by plain byte addresses from 0 need their dynamic
+// allocation to start there, so they may declare no static LDS.  *ok = none of the
+// kernels does: checked once per process (a property of the code object) and kept
+// in `state` (0 unknown, 1 yes, 2 no).
+inline hipError_t lds_from_zero(const void* const* kernels, int n, std::atomic<int>& state, bool* ok)
+{
+    int v = state.load(std::memory_order_acquire);
+    if (v == 0) {
+        v = 1;
+        for (int x = 0; x < n; ++x) {
+            hipFuncAttributes attr;
+            const hipError_t e = hipFuncGetAttributes(&attr, kernels[x]);
+            if (e != hipSuccess) return e;
+            if (attr.sharedSizeBytes != 0) v = 2;
+        }
+        state.store(v, std::memory_order_release);
+    }
+    *ok = v == 1;
+    return hipSuccess;
+}
+
+// The check of the temporal sweep's kernels and of the simulation's.
 hipError_t sweep_lds_from_zero(bool* ok);
+hipError_t sim_lds_from_zero(bool* ok);
 
 hipError_t launch_sweep_first(const SweepArgs& a, hipStream_t s);
 hipError_t launch_sweep_offsets(const SweepArgs& a, hipStream_t s);

@@ -886,9 +886,10 @@ static hipError_t pick_policy(const SweepArgs& a, Launch launch)
 }
 
 // launch(policy, kind of run, workgroups, lanes of one, LDS bytes, runs, pairs) for
-// K runs of each pair.  A dispatch holds fewer than 2^32 work-items; the workgroups
+// K runs of each pair (FLOAT_ONE_LANE: also in the usual form on one lane each).  A
+// dispatch holds fewer than 2^32 work-items; the workgroups
 // of a larger one loop over the runs.
-template <typename Launch>
+template <bool FLOAT_ONE_LANE, typename Launch>
 static hipError_t launch_runs(const SweepArgs& a, bool ordered, int64_t K, Launch launch)
 {
     return pick_policy(a, [&](auto policy) {
@@ -903,10 +904,11 @@ static hipError_t launch_runs(const SweepArgs& a, bool ordered, int64_t K, Launc
         const int64_t n_runs = run_pairs(a.n_models, ordered, kTwoLanes) * K;
         const size_t table = quotient_bytes((uint32_t)a.max_beta);
         if constexpr (decltype(policy)::value == RM_POLICY_PRIORITY) {
+            if constexpr (FLOAT_ONE_LANE)
+                if (a.sim_one_lane && !a.sim_general)
+                    return with(RunKind<ReadyKernel, kOneLane>{}, kSimBlock, table);
             if (a.sim_one_lane)
-                return a.sim_general
-                           ? with(RunKind<ShapeKernel, kOneLane>{}, kSimBlock, kReciprocalLds)
-                           : with(RunKind<ReadyKernel, kOneLane>{}, kSimBlock, table);
+                return with(RunKind<ShapeKernel, kOneLane>{}, kSimBlock, kReciprocalLds);
         }
         if (a.sim_general)
             return with(RunKind<ShapeKernel, kTwoLanes>{}, kSimBlock, kReciprocalLds);
@@ -918,41 +920,38 @@ static hipError_t launch_runs(const SweepArgs& a, bool ordered, int64_t K, Launc
 
 hipError_t launch_sim_first(const SweepArgs& a, hipStream_t s)
 {
-    return launch_runs(a, a.policy == RM_POLICY_PRIORITY, 1,
-                       [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds,
-                           int64_t n_runs, int64_t) {
-                           using K = decltype(kind);
-                           hipLaunchKernelGGL((sim_first_kernel<decltype(policy)::value,
-                                                                typename K::Kernel, K::kMode>),
-                                              blocks, block, lds, s, a, n_runs);
-                           return hipGetLastError();
-                       });
+    return launch_runs<false>(a, a.policy == RM_POLICY_PRIORITY, 1, [&](auto policy, auto kind, dim3 blocks, dim3 block,
+            size_t lds, int64_t n_runs, int64_t) {
+        using K = decltype(kind);
+        hipLaunchKernelGGL(
+            (sim_first_kernel<decltype(policy)::value, typename K::Kernel, K::kMode>), blocks, block,
+            lds, s, a, n_runs);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_sim_offsets(const SweepArgs& a, hipStream_t s)
 {
-    return launch_runs(a, true, a.num_offsets,
-                       [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds,
-                           int64_t n_runs, int64_t n_pairs) {
-                           using K = decltype(kind);
-                           hipLaunchKernelGGL((sim_offsets_kernel<decltype(policy)::value,
-                                                                  typename K::Kernel, K::kMode>),
-                                              blocks, block, lds, s, a, n_runs, n_pairs);
-                           return hipGetLastError();
-                       });
+    return launch_runs<false>(a, true, a.num_offsets, [&](auto policy, auto kind, dim3 blocks, dim3 block,
+            size_t lds, int64_t n_runs, int64_t n_pairs) {
+        using K = decltype(kind);
+        hipLaunchKernelGGL(
+            (sim_offsets_kernel<decltype(policy)::value, typename K::Kernel, K::kMode>), blocks, block,
+            lds, s, a, n_runs, n_pairs);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_sim_sampled(const SweepArgs& a, hipStream_t s)
 {
-    return launch_runs(a, a.policy == RM_POLICY_PRIORITY, a.num_offsets,
-                       [&](auto policy, auto kind, dim3 blocks, dim3 block, size_t lds,
-                           int64_t n_runs, int64_t n_pairs) {
-                           using K = decltype(kind);
-                           hipLaunchKernelGGL((sim_sampled_kernel<decltype(policy)::value,
-                                                                  typename K::Kernel, K::kMode>),
-                                              blocks, block, lds, s, a, n_runs, n_pairs);
-                           return hipGetLastError();
-                       });
+    return launch_runs<true>(a, a.policy == RM_POLICY_PRIORITY, a.num_offsets, [&](auto policy, auto kind, dim3 blocks, dim3 block,
+            size_t lds, int64_t n_runs, int64_t n_pairs) {
+        using K = decltype(kind);
+        hipLaunchKernelGGL(
+            (sim_sampled_kernel<decltype(policy)::value, typename K::Kernel, K::kMode>), blocks, block,
+            lds, s, a, n_runs, n_pairs);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_sim_starts(const SweepArgs& a, hipStream_t s)
@@ -972,6 +971,40 @@ hipError_t launch_sim_starts(const SweepArgs& a, hipStream_t s)
                                n_pairs);
         return hipGetLastError();
     });
+}
+
+// The kernels of this file keep their tables and the ring at LDS address 0 and
+// after it (see lds_from_zero).
+template <int POLICY, typename KERNEL, int MODE>
+static void add_kernels(const void** list, int& n)
+{
+    list[n++] = reinterpret_cast<const void*>(sim_first_kernel<POLICY, KERNEL, MODE>);
+    list[n++] = reinterpret_cast<const void*>(sim_offsets_kernel<POLICY, KERNEL, MODE>);
+    list[n++] = reinterpret_cast<const void*>(sim_sampled_kernel<POLICY, KERNEL, MODE>);
+}
+
+template <int POLICY>
+static void add_policy(const void** list, int& n)
+{
+    add_kernels<POLICY, ReadyKernel, kTwoLanes>(list, n);
+    add_kernels<POLICY, ReadyKernel, kTwoAhead>(list, n);
+    add_kernels<POLICY, ShapeKernel, kTwoLanes>(list, n);
+    list[n++] = reinterpret_cast<const void*>(sim_starts_kernel<POLICY, ReadyKernel>);
+    list[n++] = reinterpret_cast<const void*>(sim_starts_kernel<POLICY, ShapeKernel>);
+}
+
+hipError_t sim_lds_from_zero(bool* ok)
+{
+    static std::atomic<int> state{0};
+    const void* list[3 * 11 + 4];
+    int n = 0;
+    add_policy<RM_POLICY_EQUAL>(list, n);
+    add_policy<RM_POLICY_PRIORITY>(list, n);
+    add_policy<RM_POLICY_FCFS>(list, n);
+    add_kernels<RM_POLICY_PRIORITY, ShapeKernel, kOneLane>(list, n);
+    list[n++] = reinterpret_cast<const void*>(
+        sim_sampled_kernel<RM_POLICY_PRIORITY, ReadyKernel, kOneLane>);
+    return lds_from_zero(list, n, state, ok);
 }
 
 }  // namespace rm

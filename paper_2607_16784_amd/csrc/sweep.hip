@@ -2428,40 +2428,28 @@ __global__ __launch_bounds__(kAlignBlock) void sweep_starts_kernel(SweepArgs g, 
 // launchers
 // ---------------------------------------------------------------------------
 
-// The temporal sweep kernels address LDS by plain byte
-// addresses counted from 0.  That holds when they declare no static LDS: the
-// dynamic allocation then starts at address 0.  Checked once per process
-// from the kernels' attributes (a property of the code object).
+// The temporal sweep kernels address LDS by plain byte addresses counted from 0
+// (see lds_from_zero).
 hipError_t sweep_lds_from_zero(bool* ok)
 {
-    static std::atomic<int> state{0};   // 0 unknown, 1 yes, 2 no
-    int v = state.load(std::memory_order_acquire);
-    if (v == 0) {
-        const void* kernels[] = {reinterpret_cast<const void*>(sweep_first_kernel<4, 4, 1>),
-                                 reinterpret_cast<const void*>(sweep_first_kernel<4, 2, 2>),
-                                 reinterpret_cast<const void*>(sweep_first_kernel<3, 2, 2>),
-                                 reinterpret_cast<const void*>(sweep_first_kernel<2, 2, 4>),
-                                 reinterpret_cast<const void*>(sweep_first_kernel<2, 1, 8>),
-                                 reinterpret_cast<const void*>(sweep_first_kernel<1, 1, 16>),
-                                 reinterpret_cast<const void*>(sweep_starts_kernel<8>),
-                                 reinterpret_cast<const void*>(sweep_starts_kernel<16>),
-                                 reinterpret_cast<const void*>(sweep_starts_kernel<64>),
-                                 reinterpret_cast<const void*>(sweep_offsets_kernel<8>),
-                                 reinterpret_cast<const void*>(sweep_offsets_kernel<16>),
-                                 reinterpret_cast<const void*>(sweep_offsets_kernel<64>),
-                                 reinterpret_cast<const void*>(sweep_sampled_kernel)};
-        v = 1;
-        for (const void* k : kernels) {
-            hipFuncAttributes attr;
-            const hipError_t e = hipFuncGetAttributes(&attr, k);
-            if (e != hipSuccess) return e;
-            if (attr.sharedSizeBytes != 0) v = 2;
-        }
-        state.store(v, std::memory_order_release);
-    }
-    *ok = v == 1;
-    return hipSuccess;
+    static std::atomic<int> state{0};
+    const void* kernels[] = {
+        reinterpret_cast<const void*>(sweep_first_kernel<4, 4, 1>),
+        reinterpret_cast<const void*>(sweep_first_kernel<4, 2, 2>),
+        reinterpret_cast<const void*>(sweep_first_kernel<3, 2, 2>),
+        reinterpret_cast<const void*>(sweep_first_kernel<2, 2, 4>),
+        reinterpret_cast<const void*>(sweep_first_kernel<2, 1, 8>),
+        reinterpret_cast<const void*>(sweep_first_kernel<1, 1, 16>),
+        reinterpret_cast<const void*>(sweep_starts_kernel<8>),
+        reinterpret_cast<const void*>(sweep_starts_kernel<16>),
+        reinterpret_cast<const void*>(sweep_starts_kernel<64>),
+        reinterpret_cast<const void*>(sweep_offsets_kernel<8>),
+        reinterpret_cast<const void*>(sweep_offsets_kernel<16>),
+        reinterpret_cast<const void*>(sweep_offsets_kernel<64>),
+        reinterpret_cast<const void*>(sweep_sampled_kernel)};
+    return lds_from_zero(kernels, sizeof kernels / sizeof *kernels, state, ok);
 }
+
 template <typename F>
 static hipError_t allow_lds(F kernel, size_t bytes)
 {

@@ -166,3 +166,30 @@ def test_byte_addressed_sweeps_declare_no_static_lds(lib):
         assert any(fam in k for k in found), (fam, sorted(sizes))
     assert sum("sweep_first_kernel" in k for k in found) == 6, sorted(found)
     assert all(v == 0 for v in found.values()), found
+
+
+def test_every_byte_addressed_kernel_declares_no_static_lds(lib):
+    # the same of every kernel that addresses LDS from 0: the start-pair sweep and
+    # the adjusted-occupancy simulation (per policy FIRST, OFFSETS and sampled in three
+    # forms and CONFLICT_STARTS in two, and under PRIORITY four on one lane a run)
+    sizes = _static_lds_per_kernel(_gfx950_code_objects(LIB))
+    starts = {k: v for k, v in sizes.items() if "sweep_starts_kernel" in k}
+    sims = {k: v for k, v in sizes.items() if re.search(r"\dsim_\w+_kernel", k)}
+    assert len(starts) == 3 and all(v == 0 for v in starts.values()), starts
+    assert len(sims) == 3 * 11 + 4 and all(v == 0 for v in sims.values()), sims
+
+
+def test_the_run_time_check_covers_every_byte_addressed_kernel():
+    # a kernel that builds its LDS addresses from integers is named in the list of
+    # its file's check, which rm_pair_slowdown_matrix asks for both sweep modes
+    csrc = os.path.join(ROOT, "paper_2607_16784_amd", "csrc")
+    text = {f: open(os.path.join(csrc, f)).read() for f in ("sweep.hip", "sim.hip", "api.hip")}
+    for f, check in (("sweep.hip", "sweep_lds_from_zero"), ("sim.hip", "sim_lds_from_zero")):
+        body = text[f].split("hipError_t " + check)[1].split("\n}\n")[0]
+        if f == "sim.hip":
+            body += text[f].split("static void add_kernels")[1].split("hipError_t " + check)[0]
+        kernels = set(re.findall(r"\b(s(?:weep|im)_\w+_kernel)\(SweepArgs|"
+                                 r"\b(s(?:weep|im)_\w+_kernel)\(\n", text[f]))
+        kernels = {a or b for a, b in kernels}
+        assert kernels and all(k in body for k in kernels), (f, kernels)
+        assert check + "(&lds_ok)" in text["api.hip"]
