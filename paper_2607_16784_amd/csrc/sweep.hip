@@ -2501,9 +2501,20 @@ static hipError_t launch_first_shape(const SweepArgs& a, hipStream_t s)
 // and the longest: one pair per item at a time then stages every model (48
 // models of 1000-4000 kernels 102.6 -> 56.7 us a call, 128 432 -> 233 us), or
 // three models per item where three of the longest fit (48 of 2600 129 -> 43
-// us, 48 of 100-3000 61 -> 43 us).  With a few long models among short ones
-// the 2 x 2 item is the better one (200 models, a tenth of them 4000 kernels
-// long, the others 200-1000: 199 us against 406 us).
+// us, 48 of 100-3000 61 -> 43 us; the line at 2100: of 64 models half of 1000,
+// half of 2600 kernels 95 -> 54 us).  Four one-pair items do the work of one
+// 2 x 2 item, though: beyond 64 models, where their number and not the slowest
+// pair from memory sets the time, most of the library has to be long, by its
+// mean at least half the longest.  us a call as 2 x 2 / one pair at a time, 160
+// models of s and L kernels:
+//   s 1000, L 4000, a twentieth long 152 / 274   s 200, L 9000, a twentieth 217 / 400
+//   s 1800, L 4000, a twentieth long 189 / 306   s 2400, L 9000, a twentieth 517 / 731
+//   s 2400, L 4000, a twentieth long 472 / 324   s 1000, L 4000, half long 603 / 337
+// and 64 models of s 1000, L 4000: a tenth long 92 / 73, three tenths 107 / 78.
+// Neither the mean nor the longest tells which pairs come from memory, and some
+// mixes stay on the slower side of the line: 160 of 1800, a tenth of 2600 129 /
+// 178 (2 x 1), 96 of 200, three tenths of 4000 158 / 125.  A kernel that looked
+// at the lengths and took its shape from them ran 5 % longer in every shape.
 static TileShape first_shape(const SweepArgs& a)
 {
     const TileShape usual = tile_shape((a.pair_cap + 1) / 2);
@@ -2514,7 +2525,8 @@ static TileShape first_shape(const SweepArgs& a)
     const int64_t fits3 = kTileSlots / 3 - (tile_model_slots(0));
     const int64_t fits4 = kTileSlots / 4 - (tile_model_slots(0));
     if (longest > fits4 && longest <= fits3 && typical > 2100) return tile_shape((int32_t)fits3);
-    if (typical > fits4) return tile_shape(kTileSlots / 2);
+    if (typical > fits4 && (a.n_models <= 64 || 2 * mean > longest))
+        return tile_shape(kTileSlots / 2);
     return usual;
 }
 

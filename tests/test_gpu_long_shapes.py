@@ -1,7 +1,7 @@
 """FIRST on libraries longer than two models per staging half, one for each way
 the tile shape is chosen there (one pair per item, two rows by one column, the
-usual shape with some pairs swept from memory, no bound given, a model longer
-than the whole LDS), against the CPU oracle: sums of some thousand fp64 terms
+usual shape with some pairs swept from memory, the same for few long models
+among more than 64, no bound given, a model longer than the whole LDS), against the CPU oracle: sums of some thousand fp64 terms
 of one sign in another order, 1e-12 relative."""
 import numpy as np
 import pytest
@@ -19,6 +19,7 @@ CASES = {
     "three-fit": ([2600] * 5, 2600),
     "three-fit-ragged": ([100, 3000, 2900, 1500, 1700, 3343], 3343),
     "mostly-short": ([300, 200, 4000, 500, 300, 250, 400, 300, 350, 10], 4000),
+    "few-long-of-65": ([1200, 4000] + [60, 90, 1100] * 21, 4000),
     "no-bound": ([2600, 2700, 5200, 3000, 1], 0),
     "longer-than-lds": ([10100, 60, 5100, 4000], 10100),
 }
