@@ -1,10 +1,14 @@
-"""The float block counts of the adjusted-occupancy simulation (Sec. 3.2):
-floor(left / x) as the truncated float32 product (left + 1/2) * (1/x), with
-1/x the correctly rounded float32 reciprocal, for 0 <= left <= 2^22 - 2.  The
-exact product is at least 1/(2x) from every integer and the two roundings
-shift it by less than 2^-23 (left + 1/2) / x, so the floor is exact; checked
-here against integer division around the multiples of every divisor class,
-where it could fail first."""
+"""Quotients of small numbers without a division.  Block counts of the
+adjusted-occupancy simulation (Sec. 3.2): floor(left / x) as the truncated
+float32 product (left + 1/2) * (1/x), with 1/x the correctly rounded float32
+reciprocal, for 0 <= left <= 2^22 - 2.  The exact product is at least 1/(2x)
+from every integer and the two roundings shift it by less than
+2^-23 (left + 1/2) / x, so the floor is exact; checked here against integer
+division around the multiples of every divisor class, where it could fail
+first.  Shares and slowdown factors: a / b as the product with the correctly
+rounded fp64 reciprocal and one correction step, for all integers up to 255."""
+from fractions import Fraction
+
 import numpy as np
 import pytest
 
@@ -55,3 +59,13 @@ def test_warps_as_half_integers():
 
 def test_zero_demand_sets_no_limit():
     assert (np.float32(0.5) * np.float32(np.inf)) == np.inf
+
+
+def test_quotients_up_to_255_are_correctly_rounded():
+    # float(Fraction) rounds once, as a fused multiply-add does
+    for b in range(1, 256):
+        y = 1.0 / b
+        for a in range(256):
+            q0 = a * y
+            r = float(a - Fraction(q0) * b)
+            assert float(Fraction(r) * Fraction(y) + Fraction(q0)) == a / b, (a, b)

@@ -1,7 +1,9 @@
 """The isolated timelines at the edges of the prepare kernel's blocks, spans,
 sub-chunks and chunks: iso_time (the last prefix sum) bit for bit against the
-sequential sum, and the boundaries through FIRST delays of the adjusted
-simulation's OFFSETS, which reads every one of them."""
+sequential sum, and the boundaries through the delays of the adjusted
+simulation's OFFSETS: the kernel of model i that runs when j joins at tau has
+P_i[k + 1] - tau of work left, so the delay depends on that boundary's last
+bit."""
 import numpy as np
 import pytest
 
@@ -36,8 +38,7 @@ def test_iso_time_is_the_sequential_sum():
 
 @pytest.mark.parametrize("pair", [(17, 130), (513, 40), (2049, 33), (4097, 20)])
 def test_boundaries(pair):
-    # offsets that fall between boundaries of the longer model, one near each
-    # of its kernels for the short pairs
+    # 64 boundaries of either model, each ordered pair
     L = library(list(pair), seed=11)
     K = 64
     kw = dict(align_mode=api.ALIGN_OFFSETS, reduce_mode="max", num_offsets=K,
@@ -46,6 +47,24 @@ def test_boundaries(pair):
     kw["reduce_mode"] = oracle.REDUCE_MAX
     want = oracle.pair_matrix(W.A100, L, **kw)
     same(got["per_alignment"], want["per_alignment"], f"{pair}")
+
+
+def test_every_boundary():
+    # kernels of nearly one length, each longer than the step between two
+    # offsets: every boundary of the long model ends the kernel that some
+    # offset falls into
+    L = library([2600, 3], seed=13)
+    rng = np.random.default_rng(13)
+    L["duration"][:2600] = rng.uniform(0.8, 1.2, 2600)
+    K = 4096
+    end = np.cumsum(L["duration"][:2600])
+    running = np.searchsorted(end, end[-1] * np.arange(K) / K, side="right")
+    assert np.array_equal(np.unique(running), np.arange(2600))
+    kw = dict(align_mode=api.ALIGN_OFFSETS, reduce_mode="max", num_offsets=K,
+              sweep_mode=api.SWEEP_ADJUSTED, per_alignment=True)
+    got = gpu_pair(W.A100, L, **kw)
+    kw["reduce_mode"] = oracle.REDUCE_MAX
+    same(got["per_alignment"], oracle.pair_matrix(W.A100, L, **kw)["per_alignment"], "2600")
 
 
 def test_bad_durations_are_flagged_wherever_they_are():
