@@ -17,18 +17,18 @@
 //    merge-path (binary search on the cross diagonal, A before B on ties), so
 //    every lane walks the same number of boundaries; per-lane sums are
 //    combined with DPP reductions.
-//  * FIRST: one alignment per pair; the window is symmetric, so one sweep of
-//    the unordered pair yields both Delta_ij and Delta_ji; 1 to 16 waves
-//    split it, by the models' lengths (persistent workgroups, pipelined
-//    loads).  One walk of a start pair (CONFLICT_STARTS, SAMPLED_STARTS)
-//    yields both as well.  OFFSETS sweeps ordered pairs.  Short windows are split over 8 or 16 lanes, so that a wave
-//    carries several alignments, long or few ones over the whole wave.
-//  * Every stretch contributes (e - lo) * a_k / (a_k + a_l): the length times
-//    the tabulated reciprocal, then a_k times that added with a fused
-//    multiply-add.  The walk of a start pair adds both directions that way;
-//    FIRST adds one, and the other is the conflicting time minus it (a
-//    stretch's two shares add up to its length).  Pairs too long to stage
-//    form each share as the correctly rounded quotient and add both.  Only the rounding of each term (a few ulp) and the
+//  * FIRST: one alignment per pair; the window is symmetric, so one sweep of the
+//    unordered pair yields both Delta_ij and Delta_ji; 1 to 16 waves split it, by
+//    the models' lengths (persistent workgroups, pipelined loads).  One walk of a
+//    start pair (CONFLICT_STARTS, SAMPLED_STARTS) yields both as well.  OFFSETS
+//    sweeps ordered pairs.  Short windows are split over 8 or 16 lanes, so that a
+//    wave carries several alignments, long or few ones over the whole wave.
+//  * Every stretch contributes (e - lo) * a_k / (a_k + a_l): the length times the
+//    tabulated reciprocal, then a_k times that added with a fused multiply-add.
+//    The walk of a start pair adds both directions that way; FIRST adds one, and
+//    the other is the conflicting time minus it (a stretch's two shares add up to
+//    its length).  Pairs too long to stage form each share as the correctly rounded
+//    quotient and add both.  Only the rounding of each term (a few ulp) and the
 //    order of the final sums differ from a sequential evaluation.
 #include <atomic>
 
