@@ -1592,10 +1592,11 @@ __device__ inline double from_order_key(uint64_t k)
 // so the loops stay rolled.  The maximum is taken with the members' range, and
 // the median by counting 8-bit digits from the highest bit in which two
 // members differ until at most 64 members share the digits so far (one or two
-// digits, mostly; none for 64 members or fewer), which one wave ranks: a pair of
-// 60-kernel models took 20 us with the members compacted first and seven or eight
-// byte-aligned digits, 13 us with the start pairs in registers of unrolled loops,
-// 8.7 us now.
+// digits, mostly), which one wave ranks.  Workgroups of up to 256 lanes rank 64
+// members or fewer at once; 16 waves count a digit sooner than one ranks 64 (1000
+// models of 8, no bound given: 55.0 against 58.7 ms).  A pair of 60-kernel models
+// took 20 us with the members compacted first and seven or eight byte-aligned
+// digits, 13 us with the start pairs in registers of unrolled loops, 8.7 us now.
 constexpr int kReduceBatch = 4;
 constexpr uint64_t kNoKey = ~0ull;
 
@@ -1662,7 +1663,7 @@ __device__ inline uint64_t block_kth_key(const uint64_t* key, int32_t total, int
     uint64_t mask = shift == 56 ? 0 : ~0ull << (shift + 8);
     uint64_t prefix = mn & mask;
     int32_t tie = n;   // members that share the digits so far
-    for (int pass = 0; tie > 64; ++pass) {
+    for (int pass = 0; tie > 64 || (B == 1024 && pass == 0); ++pass) {
         int32_t* h = sc.hist[pass % 3];
 #pragma unroll 1
         for (int32_t c = tid; c < total; c += B) {
